@@ -208,6 +208,9 @@ void Batch::finish_layout()
     o = off_scratch + sizeof(uint64_t) * (size_t)n_scratch;
     total_bytes = align_up(o, 256);
 
+    if (!sorts.empty())
+        for (ChunkDesc &d : chunks)
+            d.geo = box_offset(d.n, d.geo, off_sigma, off_scratch, off_coords);
     host_tables.assign(tables_bytes, 0);
     std::memcpy(host_tables.data() + (off_chunks - off_tables), chunks.data(), sizeof(ChunkDesc) * chunks.size());
     std::memcpy(host_tables.data() + (off_items - off_tables), item_start.data(),
@@ -228,6 +231,23 @@ bool sorting_enabled()
 {
     const char *v = std::getenv("TE_NO_SORT");
     return !(v && *v && *v != '0');
+}
+
+// Float offset from `base` of the block boxes of an ordered space of n points whose map
+// (n <= kSortLds) or key scratch starts `at` entries into its area; byte offsets in one workspace.
+int64_t box_offset(int64_t n, int64_t at, size_t off_sigma, size_t off_scratch, size_t off_base)
+{
+    const int64_t words = n <= kSortLds ? (int64_t)(off_sigma / 4) + at + box_words_behind_map(n)
+                                        : (int64_t)(off_scratch / 4) + 2 * at;
+    return words - (int64_t)(off_base / 4);
+}
+
+// EmbedTask::box of a space of n points with its key scratch at `scratch`.
+int32_t embed_box(int64_t n, int64_t scratch)
+{
+    if (n <= kWave)
+        return -1;
+    return n <= kSortLds ? 0 : (int32_t)(scratch / kBoxScratchUnit) + 1;
 }
 
 // Padded sort length: the next power of two >= n.
@@ -301,7 +321,9 @@ te_status Plan::build_group_batch(const std::vector<int> &groups, int n_surr, Ba
             ChunkDesc d{};
             d.tp = tp;
             d.s = fl;
-            d.ld = N;
+            // unordered: the stride; ordered: finish_layout turns the map (or, from kSortLds points on,
+            // the key scratch) into the offset of the boxes that lie there
+            d.geo = !sorted ? N : (N <= kSortLds ? sig : b->sorts.back().scratch);
             d.out = -1;
             d.perm = -1;
             if (opt.local_outputs && s == 0) {        // per-point outputs of the original, in window order
@@ -316,6 +338,7 @@ te_status Plan::build_group_batch(const std::vector<int> &groups, int n_surr, Ba
             t.s = fl;
             t.perm = -1;
             t.sig = sig;
+            t.box = (s == 0 && sorted) ? embed_box(N, b->sorts.back().scratch) : -1;
             if (opt.delays)
                 t.u = (*opt.delays)[s];
             if (opt.delay_from_device)
@@ -467,14 +490,15 @@ te_status Plan::enqueue_batch(const Batch &b, const float *x, const float *y, co
             return hip_fail(e, "permutation launch");
     }
     int32_t *sigma = reinterpret_cast<int32_t *>(ws + b.off_sigma);
-    e = launch_sort(y, nullptr, reinterpret_cast<const SortTask *>(ws + b.off_sorts), (int)b.sorts.size(), sigma,
-                    reinterpret_cast<uint64_t *>(ws + b.off_scratch), p.n_trials, p.n_samples, st);
-    if (e != hipSuccess)
-        return hip_fail(e, "sort launch");
+    uint64_t *scratch = reinterpret_cast<uint64_t *>(ws + b.off_scratch);
     int max_n = 0;
     for (const EmbedTask &t : b.tasks)
         max_n = std::max(max_n, t.n);
-    e = launch_embed(x, y, parea, sigma, u_dev, reinterpret_cast<const EmbedTask *>(ws + b.off_tasks),
+    e = launch_sort(y, nullptr, 0, reinterpret_cast<const SortTask *>(ws + b.off_sorts), (int)b.sorts.size(), max_n,
+                    sigma, scratch, p.n_trials, p.n_samples, p.d_y, p.tau, st);
+    if (e != hipSuccess)
+        return hip_fail(e, "sort launch");
+    e = launch_embed(x, y, parea, sigma, scratch, u_dev, reinterpret_cast<const EmbedTask *>(ws + b.off_tasks),
                      (int)b.tasks.size(), max_n, base, p.n_trials, p.n_samples, p.d_y, p.d_x, p.tau, p.u,
                      p.cond_source, ctr + 1, st);
     if (e != hipSuccess)

@@ -354,7 +354,7 @@ te_status Plan::estimate_each(const float *x, const float *y, const int32_t *per
             ChunkDesc d{};
             d.tp = 0;
             d.s = (int64_t)dT * N;
-            d.ld = N;
+            d.geo = sorted ? box_offset(N, 0, L.sigma, L.scratch, L.coords) : N;
             d.out = -1;
             d.perm = -1;
             d.n = N;
@@ -368,6 +368,7 @@ te_status Plan::estimate_each(const float *x, const float *y, const int32_t *per
             t.s = (int64_t)dT * N;
             t.perm = -1;
             t.sig = sorted ? 0 : -1;
+            t.box = (s == 0 && sorted) ? embed_box(N, 0) : -1;
             t.pair = pair;
             t.w = wstart[c];
             t.W = wlen[c];
@@ -408,7 +409,8 @@ te_status Plan::estimate_each(const float *x, const float *y, const int32_t *per
         const int c = g % p.n_points;
         const int64_t items = (npts[c] + kWave - 1) / kWave;
         int32_t *gerr = ctr + 4 * (int64_t)g * S1 + 1;   // the window's error word: its original's
-        if (sorted && (e = launch_sort(y, nullptr, ds + g, 1, sigma, scratch, p.n_trials, p.n_samples, st)) !=
+        if (sorted && (e = launch_sort(y, nullptr, 0, ds + g, 1, (int)npts[c], sigma, scratch, p.n_trials, p.n_samples, p.d_y,
+                                       p.tau, st)) !=
                           hipSuccess)
             break;
         if (n_surr > 0 &&
@@ -416,7 +418,7 @@ te_status Plan::estimate_each(const float *x, const float *y, const int32_t *per
             break;
         for (int s = 0; s < S1 && e == hipSuccess; ++s) {
             const int64_t ci = (int64_t)g * S1 + s;
-            e = launch_embed(x, y, parea, sigma, nullptr, dt + ci, 1, (int)npts[c], base, p.n_trials, p.n_samples,
+            e = launch_embed(x, y, parea, sigma, scratch, nullptr, dt + ci, 1, (int)npts[c], base, p.n_trials, p.n_samples,
                              p.d_y, p.d_x, p.tau, p.u, p.cond_source, gerr, st);
             if (e != hipSuccess)
                 break;
@@ -541,12 +543,11 @@ te_status knn_counts_run(const float *pts, int64_t dim_stride, const int64_t *of
             // searched in a sorted copy: coordinate m of sorted point q at copy[offsets[c] * D + m * n + q]
             d.tp = offsets[c] * D;
             d.s = offsets[c] * D + (int64_t)(1 + d_y) * n;
-            d.ld = n;
             d.perm = offsets[c];
         } else {
             d.tp = offsets[c];
             d.s = offsets[c] + (int64_t)(1 + d_y) * dim_stride;
-            d.ld = dim_stride;
+            d.geo = dim_stride;
             d.perm = -1;
         }
         d.out = offsets[c];
@@ -571,6 +572,7 @@ te_status knn_counts_run(const float *pts, int64_t dim_stride, const int64_t *of
         gt.dst = offsets[c] * D;
         gt.sig = offsets[c];
         gt.n = (int32_t)n;
+        gt.box = so.scratch >= 0 ? (int32_t)(so.scratch / kBoxScratchUnit) : 0;
         gathers[c] = gt;
     }
     // longest first
@@ -616,6 +618,12 @@ te_status knn_counts_run(const float *pts, int64_t dim_stride, const int64_t *of
     o = align_up(o + (sorted ? sizeof(uint64_t) * (size_t)n_scratch : 0), 256);
     if (ws_bytes < o)
         return fail(TE_ERR_NOMEM, "%s too small (%zu < %zu bytes)", ws_name, ws_bytes, o);
+    if (sorted)
+        for (int i = 0; i < n_chunks; ++i) {
+            const int c = order[i];
+            sorted_chunks[i].geo = box_offset(sorted_chunks[i].n, sorts[c].scratch >= 0 ? sorts[c].scratch : sorts[c].sig,
+                                              off_sigma, off_scratch, off_copy);
+        }
     const size_t out_off = align_up(tbytes, 256);
     const size_t stg_bytes = out_off + sizeof(double) * n_chunks + 64;
     std::vector<char> host_stage;
@@ -638,11 +646,13 @@ te_status knn_counts_run(const float *pts, int64_t dim_stride, const int64_t *of
     if (e == hipSuccess)
         e = launch_fill_i32(ctr, 0, 4, st);
     if (e == hipSuccess && sorted)
-        e = launch_sort(nullptr, pts, reinterpret_cast<const SortTask *>(ws + off_sorts), n_chunks, sigma,
-                        reinterpret_cast<uint64_t *>(ws + off_scratch), 0, 0, st);
+        e = launch_sort(nullptr, pts, dim_stride, reinterpret_cast<const SortTask *>(ws + off_sorts), n_chunks,
+                        sorted_chunks[0].n, sigma,
+                        reinterpret_cast<uint64_t *>(ws + off_scratch), 0, 0, d_y, 0, st);
     if (e == hipSuccess && sorted)
-        e = launch_gather(pts, reinterpret_cast<const GatherTask *>(ws + off_gathers), n_chunks, sigma,
-                          reinterpret_cast<float *>(ws + off_copy), D, st);
+        e = launch_gather(pts, reinterpret_cast<const GatherTask *>(ws + off_gathers), n_chunks,
+                          sorted_chunks[0].n, sigma, reinterpret_cast<uint64_t *>(ws + off_scratch),
+                          reinterpret_cast<float *>(ws + off_copy), D, d_y, st);
     SearchArgs a{};
     a.base = sorted ? reinterpret_cast<const float *>(ws + off_copy) : pts;
     a.chunks = reinterpret_cast<const ChunkDesc *>(ws + off_chunks);

@@ -19,10 +19,13 @@ constexpr int kMaxWavesPerWG = 4;         // search kernel workgroup: up to 4 in
 //   base[tp + m * ld + j]                 for m <  1 + d_y  (y_t' and target past)
 //   base[s + (m - 1 - d_y) * ld + j]      for m >= 1 + d_y  (source past)
 // so the originals and surrogates of one window share the (y_t', Y_past) block.
+// In an ordered chunk ld is n, and base[geo + (2 m) nb + b], base[geo + (2 m + 1) nb + b]
+// are the smallest and largest target-past coordinate m < d_y of points 64 b .. 64 b + 63
+// (nb = ceil(n / 64); a chunk of one block has none).
 struct ChunkDesc {
     int64_t tp;       // float offset of the target block
     int64_t s;        // float offset of the source block
-    int64_t ld;       // stride between coordinates, in floats
+    int64_t geo;      // ordered chunks: float offset of the block boxes; else: ld, the stride between coordinates
     int64_t out;      // per-point output offset (eps / counts), or -1
     int64_t pbase;    // index in the partial-sum array of the chunk's block 0
     int64_t perm;     // offset in perm_base of the sorted-to-original point map, or -1
@@ -43,7 +46,8 @@ struct EmbedTask {
     int32_t n;        // Rc * W
     int32_t u;        // source delay of this block; 0: the launch's delay
     int32_t u_slot;   // > 0: the delay is read on the device from u_dev[u_slot - 1] (overrides u)
-    int32_t pad_;
+    int32_t box;      // writes the block boxes: -1 no, 0 behind the order map, > 0 in the key scratch at
+                      // (box - 1) * kBoxScratchUnit
 };
 
 // One surrogate's trial permutation in a batch's permutation area.  It is either
@@ -59,23 +63,64 @@ struct PermTask {
     int32_t pair, point, surr, pad_;
 };
 
-// Sorting of one search space by its first target-past coordinate p0.  The
-// result sigma[sig + q] is the original index of the point at sorted position q.
-// Keys are (order-preserving bits of p0) << 32 | original index: a total order,
-// so the permutation is unique.
+// Ordering of one search space: 64 consecutive points of the order (a block) are
+// close together in the target past (order_kernel).  The map's entry q, at sigma + sig
+// (order_at in te_device.h), is the original index of the point at position q.
 struct SortTask {
     int64_t sig;      // int32 offset of the output map
     int64_t scratch;  // uint64 offset of global key scratch (npad > kSortLds), else -1
-    int64_t key_off;  // mode 1: float offset of the key coordinate (point q at key_off + q)
-    int32_t mode;     // 0: key = y[pair][r][t'-1] of window point q = r W + (t' - w); 1: stored coordinate
+    int64_t key_off;  // mode 1: float offset of the first target-past coordinate (point q at key_off + q)
+    int32_t mode;     // 0: keys from y of window point q = r W + (t' - w); 1: stored coordinates
     int32_t pair, w, W, Rc, n, npad, pad_;
 };
 constexpr int kSortLds = 16384;   // keys sorted in LDS (128 KiB) up to this many (padded) points
 
-// Copy of one pre-embedded chunk into sorted order: dst[dst + m n + q] = src[src + m ld + sigma[sig + q]].
+// Where the block boxes of an ordered space of n points live: up to kSortLds points in the
+// words behind its 16-bit map, above that in its key scratch, which the ordering is done with.
+constexpr int64_t box_words_behind_map(int64_t n) { return (n + 1) / 2; }
+constexpr int kBoxScratchUnit = 2 * kSortLds;   // scratch offsets are multiples of this many keys
+
+// Slabs: runs of whole blocks.  A run of `leaves` blocks is cut along one coordinate into as many
+// slabs as the rem-th root of their number, rounded, when rem coordinates (this one included) are
+// left, so that every coordinate gets its share; slab i of s holds blocks [slab_first(i), slab_first(i + 1)).
+__host__ __device__ constexpr int slab_count(int leaves, int rem)
+{
+    if (rem <= 1)
+        return 1;
+    int s = 1;
+    for (;; ++s) {
+        int64_t p = 1;                    // (s + 1/2)^rem against leaves, both times 2^rem
+        for (int j = 0; j < rem; ++j)
+            p *= 2 * s + 1;
+        if (p > ((int64_t)leaves << rem))
+            return s;
+    }
+}
+__host__ __device__ constexpr int slab_first(int leaves, int slabs, int i) { return (int)((int64_t)leaves * i / slabs); }
+
+// A space of more than kSlabMax points is first cut into slabs of at most that many, which
+// workgroups of their own then order in LDS; 0: too large for that (order_big_kernel).
+constexpr int kSlabMax = 8192;
+constexpr int kMaxSlabs = 64;
+__host__ __device__ constexpr int order_slabs(int n, int nd)
+{
+    if (n <= kSlabMax)
+        return 1;
+    const int nl = (n - 1) / kWave + 1;
+    const int least = (nl + kSlabMax / kWave - 1) / (kSlabMax / kWave);   // slabs of at most kSlabMax points
+    if (least > kMaxSlabs)
+        return 0;
+    int s = slab_count(nl, nd);
+    s = s < least ? least : s;
+    return s > kMaxSlabs ? kMaxSlabs : s;
+}
+
+// Copy of one pre-embedded chunk into its order, with its block boxes:
+// dst[dst + m n + q] = src[src + m ld + map[q]].
 struct GatherTask {
     int64_t src, ld, dst, sig;
-    int32_t n, pad_;
+    int32_t n;
+    int32_t box;      // boxes in the key scratch (n > kSortLds): its offset / kBoxScratchUnit
 };
 
 // Arguments of the search kernel (passed by value; read from the kernarg segment).
@@ -96,7 +141,7 @@ struct SearchArgs {
     unsigned long long *work;   // optional: [0] += pairs evaluated in pass 1, [1] += in pass 2 (a pair per chunk),
                                 // [2], [3] += the same counted once per set of chunks
     double *lte_out;            // optional per-point local TE (at out + original index)
-    int32_t sorted;             // chunks are sorted by the first target-past coordinate
+    int32_t sorted;             // chunks are in order_kernel's order, with block boxes
     int32_t n_parts;            // > 1: items split into n_parts queues (counter[p] heads queue p), see kQueues
     const int32_t *part_start;  // [n_parts + 1] first item of each queue (n_parts > 1)
     const int32_t *set_first;   // non-null: chunk-set search; n_chunks counts sets, set c holds the chunks
@@ -125,7 +170,7 @@ constexpr int kQueues = 8;
 
 // Tunable launch shape of the search kernel.
 struct SearchConfig {
-    int slots;        // candidate slots per lane in the counting pass (4 or 8)
+    int slots;        // candidate blocks counted together in pass 2: 4 -> one, 8 and 16 -> two
     int waves_per_wg; // independent wavefronts per workgroup
     int wg_per_cu;    // persistent workgroups per compute unit
 };
@@ -138,19 +183,27 @@ struct DeviceInfo {
 
 // Kernel launchers (te_kernels.hip).  All return hipSuccess or the launch error.
 hipError_t launch_fill_i32(int32_t *p, int32_t v, int64_t n, hipStream_t st);
-hipError_t launch_embed(const float *x, const float *y, const int32_t *perms, const int32_t *sigma,
+hipError_t launch_embed(const float *x, const float *y, const int32_t *perms, int32_t *sigma, uint64_t *scratch,
                         const int32_t *u_dev, const EmbedTask *tasks, int n_tasks, int max_n, float *base, int R,
                         int T, int d_y, int d_x, int tau, int u, int cond, int32_t *err, hipStream_t st);
-hipError_t launch_sort(const float *y, const float *pts, const SortTask *tasks, int n_tasks, int32_t *sigma,
-                       uint64_t *scratch, int R, int T, hipStream_t st);
-hipError_t launch_gather(const float *src, const GatherTask *tasks, int n_tasks, const int32_t *sigma, float *dst,
-                         int D, hipStream_t st);
+// Order maps of n_tasks search spaces by their d_y target-past coordinates (ld: the stride
+// between the coordinates of pts, mode 1; tau: the embedding delay, mode 0).
+hipError_t launch_sort(const float *y, const float *pts, int64_t ld, const SortTask *tasks, int n_tasks, int max_n,
+                       int32_t *sigma, uint64_t *scratch, int R, int T, int d_y, int tau, hipStream_t st);
+hipError_t launch_gather(const float *src, const GatherTask *tasks, int n_tasks, int max_n, int32_t *sigma,
+                         uint64_t *scratch, float *dst, int D, int d_y, hipStream_t st);
 // Fill a batch's permutation area: copy (and check) the caller's rows when src is
 // given, else draw every row from `seed`.  Sets bit 2 of *err for an invalid row.
 hipError_t launch_perms(const int32_t *src, const PermTask *tasks, int n_tasks, int32_t *dst,
                         uint64_t seed, int32_t *err, hipStream_t st);
 hipError_t launch_search(const SearchArgs &a, int d_y, int d_x, const SearchConfig &cfg, int grid_waves,
                          hipStream_t st);
+// A kernel of the search over ordered chunks and its dynamic LDS bytes (te_search.hip).
+struct ordered_search {
+    void (*fn)(SearchArgs);
+    size_t lds;
+};
+ordered_search pick_ordered(int d_y, int d_x, int k, int slots, bool sets, int waves_per_wg);
 // With pv != nullptr the launch also computes the n_groups p-values (results laid
 // out [group][original, surrogates...]; NaN when *err is set) and copies *err to
 // *err_out when that is given: in its last-finishing workgroup, counted on `done`

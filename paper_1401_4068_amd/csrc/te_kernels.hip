@@ -1,233 +1,43 @@
-// te_kernels.hip -- HIP kernels of libte for gfx950 (CDNA4, wave64).
+// te_kernels.hip -- HIP kernels of libte for gfx950 (CDNA4, wave64) around the search.
 //
+//   split_kernel, order_kernel, order_big_kernel  order a search space so that
+//                    64 consecutive points are close together in the target past.
 //   embed_kernel     eq. 6-7 / eq. 10: gathers the pooled points of a window
 //                    from the raw [pair][trial][sample] series into
 //                    coordinate-major blocks; bit copies only.
-//   search_kernel    the KSG type-1 searches (text before eq. 9): per point
-//                    the max-norm k-NN radius in the joint space, then strict
-//                    range counts in the three marginal spaces of eq. 8, then
-//                    the per-point digamma terms of eq. 9 summed per work item.
+//   search_unordered_kernel  the KSG type-1 searches (text before eq. 9) over
+//                    chunks in the caller's order; the searches over ordered
+//                    chunks are in te_search.hip.
 //   reduce_kernel    eq. 9/10 per chunk: psi(k) + mean of the terms.
 //   pvalue_kernel    fraction of surrogate estimates >= the original.
 //   argmax_u_kernel  eq. 5: the assumed delay with the largest estimate.
-//
-// The search kernel is persistent: every wavefront pulls work items (one
-// chunk, 64 consecutive reference points) from a global counter until the
-// queue is empty, so one launch covers any mix of chunk sizes.
-//
-// Pass 1 (radius): lane = reference point.  Candidates are wave-uniform and
-// read with scalar loads straight into SGPRs, so each coordinate difference is
-// one v_sub_f32 with an SGPR operand.  Each lane keeps the k+1 smallest joint
-// distances in registers (self included, distance 0), inserted with a
-// min / med3 network only when some lane of the wave improves its k+1-th
-// distance; the radius is the k+1-th entry, i.e. the k-th neighbour without self.
-//
-// Pass 2 (counts): lane = candidate point.  Each wave holds a tile of 64 x
-// SLOTS candidates in VGPRs and walks its 64 references uniformly (scalar
-// loads), with the reference radius in an SGPR: the three strict comparisons
-// become wave ballots and the counting is SALU popcounts.  The (y_t', Y_past)
-// and (Y_past, X_past) conditions share the Y_past comparison:
-// n_TP counts  [d_P < eps] & [d_T < eps],  n_PS counts [d_P < eps] & [d_S < eps].
+//   take_perms_kernel, draw_perms_kernel  the surrogates' trial permutations.
 
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stddef.h>
 #include <stdint.h>
 
+#include <algorithm>
+
+#include "te_device.h"
 #include "te_internal.h"
 
 namespace te {
 
 namespace {
 
-typedef float f4v __attribute__((ext_vector_type(4)));
-typedef const __attribute__((address_space(4))) float cfloat_t;
-typedef const __attribute__((address_space(4))) int32_t cint_t;
-typedef const __attribute__((address_space(4))) int64_t cint64_t;
-typedef const __attribute__((address_space(4))) f4v __attribute__((aligned(4))) cf4_t;
-typedef float f8v __attribute__((ext_vector_type(8)));
-typedef const __attribute__((address_space(4))) f8v __attribute__((aligned(4))) cf8_t;
+// ------------------------------------------------- the search over unordered chunks
+//
+// TE_NO_SORT=1: every pair of a chunk is examined in both passes.  The measure of what
+// the ordered search (te_search.hip) prunes, and a check that does not depend on it.
 
-// Wave-uniform loads through the constant address space: the address is the
-// same in every lane, so these become scalar (SMEM) loads into SGPRs.  Only
-// scalar and vector-typed values are loaded this way (aggregate copies would
-// be lowered to vector-memory loads).
-__device__ __forceinline__ float uload(const float *p) { return *(cfloat_t *)p; }
-__device__ __forceinline__ f4v uload4(const float *p) { return *(cf4_t *)p; }
-__device__ __forceinline__ f8v uload8_at(const float *p, uint32_t byte_off)
-{
-    typedef const __attribute__((address_space(4))) char cchar_t;
-    return *(cf8_t *)((cchar_t *)p + byte_off);
-}
-// the same at a 32-bit byte offset from a wave-uniform base: one SGPR offset shared
-// by several bases, so the loads need no 64-bit address arithmetic
-__device__ __forceinline__ f4v uload4_at(const float *p, uint32_t byte_off)
-{
-    typedef const __attribute__((address_space(4))) char cchar_t;
-    return *(cf4_t *)((cchar_t *)p + byte_off);
-}
-// per-lane load at a 32-bit byte offset from a wave-uniform base: the base stays in
-// SGPRs and the offset in one VGPR (no 64-bit address per lane)
-__device__ __forceinline__ float vload_at(const float *p, uint32_t byte_off)
-{
-    return *reinterpret_cast<const float *>(reinterpret_cast<const char *>(p) + byte_off);
-}
-__device__ __forceinline__ int32_t uload_i(const int32_t *p) { return *(cint_t *)p; }
-__device__ __forceinline__ int64_t uload_l(const int64_t *p) { return *(cint64_t *)p; }
-
-// Compiler barrier that keeps a uniform branch a branch (a block containing it
-// cannot be speculated and if-converted into selects).
-__device__ __forceinline__ void keep_branch() { asm volatile("" ::: "memory"); }
-
-constexpr float kInf = __builtin_inff();
-
-// Sorted chunks of at least this many points walk pass 1 outward from the reference
-// block in tiles (lane = candidate); smaller ones in groups (lane = reference).
-constexpr int kTileScanMin = 8192;
-
-__device__ __forceinline__ float absdiff(float a, float b) { return __builtin_fabsf(a - b); }
-
-__device__ __forceinline__ uint64_t ballot(bool p) { return __builtin_amdgcn_ballot_w64(p); }
-
-// psi(n + 1) = -gamma + H_n for integer n >= 0 in float64: upward recurrence
-// psi(x) = psi(x + 1) - 1/x to x >= 16, then the asymptotic (Stirling-type)
-// series psi(x) ~ ln x - 1/(2x) - sum_j B_2j / (2j x^2j) through B_10
-// (Abramowitz & Stegun 6.3.18); truncation error < 1e-16 at x >= 16.
-// Not inlined: its float64 constants (and those of log) would otherwise be
-// hoisted out of the persistent work loop and held in VGPRs for the whole
-// search, costing waves per SIMD.
-__device__ __attribute__((noinline)) double psi_of_count(int n)
-{
-    double x = (double)n + 1.0;
-    double shift = 0.0;
-    while (x < 16.0) {
-        shift -= 1.0 / x;
-        x += 1.0;
-    }
-    const double r = 1.0 / x;
-    const double r2 = r * r;
-    const double series =
-        r2 * (1.0 / 12 - r2 * (1.0 / 120 - r2 * (1.0 / 252 - r2 * (1.0 / 240 - r2 * (1.0 / 132)))));
-    return log(x) - 0.5 * r - series + shift;
-}
-
-// Fixed-order butterfly sum over the 64 lanes (same order on every call).
-__device__ __forceinline__ double wave_sum(double v)
-{
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1)
-        v += __shfl_xor(v, o, 64);
-    return v;
-}
-
-// Per-chunk coordinate base pointers (wave-uniform).
-template <int DY, int DX>
-struct Coords {
-    static constexpr int D = 1 + DY + DX;
-    const float *p[D];
-    __device__ __forceinline__ Coords(const float *base, const ChunkDesc &c)
-    {
-#pragma unroll
-        for (int m = 0; m < D; ++m)
-            p[m] = (m < 1 + DY) ? base + c.tp + (int64_t)m * c.ld : base + c.s + (int64_t)(m - 1 - DY) * c.ld;
-    }
-};
-
-// Joint, target-future, target-past and source-past distances of one pair.
-template <int DY, int DX>
-struct PairDist {
-    float t, p, s;
-};
-
-template <int DY, int DX>
-__device__ __forceinline__ PairDist<DY, DX> pair_dist(const float (&a)[1 + DY + DX], const float (&b)[1 + DY + DX])
-{
-    PairDist<DY, DX> d;
-    d.t = absdiff(a[0], b[0]);
-    float p = absdiff(a[1], b[1]);
-#pragma unroll
-    for (int m = 2; m < 1 + DY; ++m)
-        p = fmaxf(p, absdiff(a[m], b[m]));
-    float s = absdiff(a[1 + DY], b[1 + DY]);
-#pragma unroll
-    for (int m = 2 + DY; m < 1 + DY + DX; ++m)
-        s = fmaxf(s, absdiff(a[m], b[m]));
-    d.p = p;
-    d.s = s;
-    return d;
-}
-
-template <int DY, int DX, int RW>
-__device__ __forceinline__ PairDist<DY, DX> pair_dist_row(const float (&a)[RW], const float (&b)[1 + DY + DX])
-{
-    float t[1 + DY + DX];
-#pragma unroll
-    for (int m = 0; m < 1 + DY + DX; ++m)
-        t[m] = a[m];
-    return pair_dist<DY, DX>(t, b);
-}
-
-// v_writelane_b32: returns old with lane `lane` replaced by the uniform value v.
-__device__ __forceinline__ uint32_t writelane(uint32_t old, uint32_t v, int lane)
-{
-    // gfx9 allows one SGPR source per VALU op, so the lane select goes in M0.
-    asm("v_writelane_b32 %0, %1, m0" : "+v"(old) : "s"(v), "{m0}"(lane));
-    return old;
-}
-
-// Sorted-list insertion of x into the KP1 smallest values b[0] <= ... <= b[KP1-1]:
-// from the top down, bi' = med3(b(i-1), bi, x), then b0' = min(b0, x).  Each
-// step reads only entries not yet updated, so the list is rewritten in place
-// (KP1 VALU ops, no copies).  Leaves the list unchanged when x >= b[KP1-1], so
-// it can run on every lane of the wave.  All values are non-negative floats
-// (+0 .. +inf), whose bit patterns order like unsigned integers; the minimum
-// is taken on the bits (no NaN canonicalisation needed).
-template <int KP1>
-__device__ __forceinline__ void insert_sorted(float (&b)[KP1], float x)
-{
-#pragma unroll
-    for (int i = KP1 - 1; i >= 1; --i)
-        b[i] = __builtin_amdgcn_fmed3f(b[i - 1], b[i], x);
-    const uint32_t lo = min(__builtin_bit_cast(uint32_t, b[0]), __builtin_bit_cast(uint32_t, x));
-    b[0] = __builtin_bit_cast(float, lo);
-}
-
-template <int KP1, bool GENERIC>
-__device__ __forceinline__ float kth(const float (&b)[KP1], int k)
-{
-    if (!GENERIC)
-        return b[KP1 - 1];
-    float r = b[0];
-#pragma unroll
-    for (int i = 1; i < KP1; ++i)
-        r = (k == i) ? b[i] : r;
-    return r;
-}
-
-// Work item -> chunk: the largest c with item_start[c] <= q (binary search on
-// scalar loads).
-__device__ __forceinline__ int find_chunk(const int32_t *item_start, int n_chunks, int q)
-{
-    int lo = 0, hi = n_chunks - 1;
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (uload_i(item_start + mid) <= q)
-            lo = mid;
-        else
-            hi = mid - 1;
-    }
-    return lo;
-}
-
-// ---------------------------------------------------------------- the search
-
-template <int DY, int DX, int KP1, bool GENERIC, int SLOTS, bool SORTED>
-__global__ void __launch_bounds__(kMaxWavesPerWG * 64) search_kernel(SearchArgs a)
+template <int DY, int DX, int KP1, bool GENERIC>
+__global__ void __launch_bounds__(kMaxWavesPerWG * 64) search_unordered_kernel(SearchArgs a)
 {
     constexpr int D = 1 + DY + DX;
     constexpr int RW = (D + 1 + 3) & ~3;       // LDS row: D coordinates + radius, 16-byte aligned
-    constexpr bool kGroup8 = D <= 7;           // pass-1 groups of eight candidates (8 D SGPRs of data;
-                                               // wider rows keep groups of four, within the SGPR budget)
+    constexpr int SLOTS = 4;                   // candidates per lane in pass 2
     __shared__ __attribute__((aligned(16))) float rows[kMaxWavesPerWG * kWave * RW];
     const int lane = threadIdx.x & (kWave - 1);
     const int k = GENERIC ? a.k : KP1 - 1;
@@ -266,7 +76,7 @@ __global__ void __launch_bounds__(kMaxWavesPerWG * 64) search_kernel(SearchArgs 
             const char *w = reinterpret_cast<const char *>(a.chunks + ci);
             cd.tp = uload_l(reinterpret_cast<const int64_t *>(w + offsetof(ChunkDesc, tp)));
             cd.s = uload_l(reinterpret_cast<const int64_t *>(w + offsetof(ChunkDesc, s)));
-            cd.ld = uload_l(reinterpret_cast<const int64_t *>(w + offsetof(ChunkDesc, ld)));
+            cd.geo = uload_l(reinterpret_cast<const int64_t *>(w + offsetof(ChunkDesc, geo)));
             cd.out = uload_l(reinterpret_cast<const int64_t *>(w + offsetof(ChunkDesc, out)));
             cd.pbase = uload_l(reinterpret_cast<const int64_t *>(w + offsetof(ChunkDesc, pbase)));
             cd.perm = uload_l(reinterpret_cast<const int64_t *>(w + offsetof(ChunkDesc, perm)));
@@ -275,19 +85,7 @@ __global__ void __launch_bounds__(kMaxWavesPerWG * 64) search_kernel(SearchArgs 
             cd.block0 = uload_i(reinterpret_cast<const int32_t *>(w + offsetof(ChunkDesc, block0)));
         }
         const int n = cd.n;
-        int blk = q - cd.item0 + cd.block0;
-        const int nb = (n + kWave - 1) / kWave;
-        if (a.sorted && cd.block0 == 0 && last_hi - last_lo == nb) {
-            // a whole sorted chunk: blocks are taken middle first (the middle of
-            // the p0 order is densest, so those blocks scan most); the cheap outer
-            // blocks come last and the waves of a queue end together
-            const int mid = nb >> 1, kk = blk;
-            const int pairs = min(mid, nb - mid);
-            if (kk < 2 * pairs)
-                blk = (kk & 1) ? mid - 1 - (kk >> 1) : mid + (kk >> 1);
-            else
-                blk = nb - mid > mid ? mid + pairs + (kk - 2 * pairs) : mid - 1 - pairs - (kk - 2 * pairs);
-        }
+        const int blk = q - cd.item0 + cd.block0;
         const int r0 = blk * kWave;
         const Coords<DY, DX> cp(a.base, cd);
 
@@ -360,38 +158,6 @@ __global__ void __launch_bounds__(kMaxWavesPerWG * 64) search_kernel(SearchArgs 
             load4(j, c);
             visit_group(c);
         };
-        // eight consecutive candidates j..j+7, one scalar load per coordinate
-        auto load8 = [&](int j, float (&c)[8][D]) {
-            const uint32_t off = (uint32_t)j * 4u;
-#pragma unroll
-            for (int m = 0; m < D; ++m) {
-                const f8v v = uload8_at(cp.p[m], off);
-#pragma unroll
-                for (int u = 0; u < 8; ++u)
-                    c[u][m] = v[u];
-            }
-        };
-        auto visit_group8 = [&](const float (&c)[8][D]) {
-            float dj[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const PairDist<DY, DX> d = pair_dist<DY, DX>(ref, c[u]);
-                dj[u] = fmaxf(d.t, fmaxf(d.p, d.s));
-            }
-            const float m = fminf(fminf(fminf(dj[0], dj[1]), fminf(dj[2], dj[3])),
-                                  fminf(fminf(dj[4], dj[5]), fminf(dj[6], dj[7])));
-            if (ballot(m < cur())) {
-                keep_branch();
-#pragma unroll
-                for (int u = 0; u < 8; ++u)
-                    if (ballot(dj[u] < cur())) {
-                        keep_branch();
-                        insert_sorted<KP1>(best, dj[u]);
-                        if (GENERIC)
-                            thr = kth<KP1, GENERIC>(best, k);
-                    }
-            }
-        };
         auto visit1 = [&](int j) {
             float c[D];
 #pragma unroll
@@ -399,218 +165,12 @@ __global__ void __launch_bounds__(kMaxWavesPerWG * 64) search_kernel(SearchArgs 
                 c[m] = uload(cp.p[m] + j);
             visit(c);
         };
-        // In a chunk sorted by the first target-past coordinate p0, the joint
-        // distance to candidate j is at least |fl32(p0_i - p0_j)|, which grows
-        // monotonically away from the reference block (rounding is monotone).
-
-        // (reference, candidate) pairs examined in pass 1
-        unsigned long long pass1_pairs = (unsigned long long)n * (unsigned long long)min(kWave, n - r0);
-        int scan_lo = 0, scan_hi = n;                     // pass 1 examined [scan_lo, scan_hi)
-        if (!SORTED) {
-            int j = 0;
-            for (; j + 4 <= n; j += 4)
-                visit4(j);
-            for (; j < n; ++j)
-                visit1(j);
-        } else {
-            const int e0 = min(n, r0 + kWave);
-            int j = r0;                                   // the block's own points first
-            if constexpr (kGroup8)
-                for (; j + 8 <= e0; j += 8) {
-                    float c[8][D];
-                    load8(j, c);
-                    visit_group8(c);
-                }
-            for (; j + 4 <= e0; j += 4)
-                visit4(j);
-            for (; j < e0; ++j)
-                visit1(j);
-            // Outward from the block: for chunks of at least kTileScanMin points in tiles of
-            // 64 x TS candidates against the references whose windows reach them, below
-            // that in groups of candidates against all 64 references (where a chunk is
-            // small, the 64 windows nearly coincide and the groups' scalar loads cost less).
-            int f, b;
-            unsigned long long ev = (unsigned long long)(e0 - r0) * (unsigned long long)min(kWave, n - r0);
-            if (n >= kTileScanMin) {
-                // Then outward in tiles of 64 candidates, one per lane, alternating forward
-                // (p0 increasing) and backward: a tile is compared only with the references
-                // whose p0 window [p0 - r, p0 + r] (r their current (k+1)-th distance) reaches
-                // the tile's p0 span, read back as LDS broadcasts; a candidate below a
-                // reference's current (k+1)-th distance is moved to the reference's lane and
-                // inserted there.  A direction ends at the first tile that no reference
-                // reaches: every later candidate on that side is farther in p0.
-                // LDS row of a reference: its coordinates, then its current (k+1)-th distance
-                float *prow = rows + (threadIdx.x / kWave) * (kWave * RW);
-                __builtin_amdgcn_wave_barrier();
-#pragma unroll
-                for (int m = 0; m < D; ++m)
-                    prow[lane * RW + m] = ref[m];
-                prow[lane * RW + D] = cur();
-                __builtin_amdgcn_wave_barrier();
-                constexpr int TS = 2;                        // a tile: 64 x TS candidates
-                auto read_row = [&](int r, float (&rr)[RW]) {
-                    const f4v *rowv = reinterpret_cast<const f4v *>(prow + r * RW);
-#pragma unroll
-                    for (int x = 0; x < RW / 4; ++x) {
-                        const f4v q4 = rowv[x];
-                        rr[4 * x + 0] = q4.x;
-                        rr[4 * x + 1] = q4.y;
-                        rr[4 * x + 2] = q4.z;
-                        rr[4 * x + 3] = q4.w;
-                    }
-                };
-                auto tile = [&](int t0, int t1) {
-                    float cand[TS][D];
-#pragma unroll
-                    for (int sl = 0; sl < TS; ++sl) {
-                        const int idx = t0 + sl * kWave + lane;
-                        const bool ok = idx < t1;
-                        const uint32_t ic4 = (uint32_t)(ok ? idx : t0) * 4u;
-#pragma unroll
-                        for (int m = 0; m < D; ++m) {
-                            const float v = vload_at(cp.p[m], ic4);
-                            cand[sl][m] = ok ? v : kInf;
-                        }
-                    }
-                    const float tlo = uload(cp.p[1] + t0), thi = uload(cp.p[1] + t1 - 1);
-                    const float c0 = cur();
-                    uint64_t todo = ballot(valid && !(tlo - ref[1] >= c0 || ref[1] - thi >= c0));
-                    ev += (unsigned long long)__builtin_popcountll(todo) * (unsigned long long)(t1 - t0);
-                    // the candidates of the tile against reference r (row rr), in the reference's lane
-                    auto against = [&](int r, const float (&rr)[RW]) {
-                        float ut = rr[D];
-#pragma unroll
-                        for (int sl = 0; sl < TS; ++sl) {
-                            const PairDist<DY, DX> d = pair_dist_row<DY, DX, RW>(rr, cand[sl]);
-                            const float dj = fmaxf(d.t, fmaxf(d.p, d.s));
-                            uint64_t hit = ballot(dj < ut);
-                            while (hit != 0) {
-                                keep_branch();
-                                const int c = __builtin_ctzll(hit);
-                                const float x =
-                                    __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, dj), c));
-                                if (lane == r) {
-                                    insert_sorted<KP1>(best, x);
-                                    if (GENERIC)
-                                        thr = kth<KP1, GENERIC>(best, k);
-                                    prow[r * RW + D] = cur();
-                                }
-                                ut = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, cur()), r));
-                                hit &= hit - 1;
-                                hit &= ballot(dj < ut);
-                            }
-                        }
-                    };
-                    // two row buffers used in turn: the next reference's row is read while the
-                    // current one is compared (rows of different references: an insertion
-                    // rewrites only its own reference's row)
-                    if (todo != 0) {
-                        float ra[RW], rb[RW];
-                        int ia = __builtin_ctzll(todo);
-                        todo &= todo - 1;
-                        read_row(ia, ra);
-                        for (;;) {
-                            const bool mb = todo != 0;
-                            int ib = ia;
-                            if (mb) {
-                                ib = __builtin_ctzll(todo);
-                                todo &= todo - 1;
-                                read_row(ib, rb);
-                            }
-                            __builtin_amdgcn_sched_barrier(0);
-                            against(ia, ra);
-                            if (!mb)
-                                break;
-                            const bool mc = todo != 0;
-                            int ic = ib;
-                            if (mc) {
-                                ic = __builtin_ctzll(todo);
-                                todo &= todo - 1;
-                                read_row(ic, ra);
-                            }
-                            __builtin_amdgcn_sched_barrier(0);
-                            against(ib, rb);
-                            if (!mc)
-                                break;
-                            ia = ic;
-                        }
-                    }
-                };
-                f = e0;
-                b = r0;
-                bool fgo = f < n && ballot(valid && absdiff(ref[1], uload(cp.p[1] + f)) < cur()) != 0;
-                bool bgo = b > 0 && ballot(valid && absdiff(ref[1], uload(cp.p[1] + b - 1)) < cur()) != 0;
-                while (fgo || bgo) {
-                    if (fgo) {
-                        const int t1 = min(n, f + kWave * TS);
-                        tile(f, t1);
-                        f = t1;
-                        fgo = f < n && ballot(valid && absdiff(ref[1], uload(cp.p[1] + f)) < cur()) != 0;
-                    }
-                    if (bgo) {
-                        const int t0 = max(0, b - kWave * TS);
-                        tile(t0, b);
-                        b = t0;
-                        bgo = b > 0 && ballot(valid && absdiff(ref[1], uload(cp.p[1] + b - 1)) < cur()) != 0;
-                    }
-                }
-            } else {
-                // then outward: forward (p0 increasing), then backward, a group of eight
-                // (four for wide rows, then four for the remainder) at a time.  After
-                // each group, its candidate farthest from the block is tested: if no
-                // lane could still use it, no later candidate of that direction could
-                // either (so the next group is not loaded).  All loads of a group feed
-                // its distances unconditionally: one wait per group.
-                f = e0;
-                bool go = f < n;
-                while (kGroup8 && go && f + 8 <= n) {
-                    float c[8][D];
-                    load8(f, c);
-                    visit_group8(c);
-                    f += 8;
-                    go = f < n && ballot(absdiff(ref[1], c[7][1]) < cur()) != 0;
-                }
-                while (go && f + 4 <= n) {
-                    float c[4][D];
-                    load4(f, c);
-                    visit_group(c);
-                    f += 4;
-                    go = f < n && ballot(absdiff(ref[1], c[3][1]) < cur()) != 0;
-                }
-                while (go && f < n) {
-                    const float p0 = uload(cp.p[1] + f);
-                    visit1(f);
-                    ++f;
-                    go = f < n && ballot(absdiff(ref[1], p0) < cur()) != 0;
-                }
-                b = r0;
-                go = b > 0;
-                while (kGroup8 && go && b >= 8) {
-                    float c[8][D];
-                    load8(b - 8, c);
-                    visit_group8(c);
-                    b -= 8;
-                    go = b > 0 && ballot(absdiff(ref[1], c[0][1]) < cur()) != 0;
-                }
-                while (go && b >= 4) {
-                    float c[4][D];
-                    load4(b - 4, c);
-                    visit_group(c);
-                    b -= 4;
-                    go = b > 0 && ballot(absdiff(ref[1], c[0][1]) < cur()) != 0;
-                }
-                while (go && b > 0) {
-                    const float p0 = uload(cp.p[1] + b - 1);
-                    visit1(b - 1);
-                    --b;
-                    go = b > 0 && ballot(absdiff(ref[1], p0) < cur()) != 0;
-                }
-                ev = (unsigned long long)(f - b) * (unsigned long long)min(kWave, n - r0);
-            }
-            pass1_pairs = ev;
-            scan_lo = b;
-            scan_hi = f;
-        }
+        const unsigned long long pass1_pairs = (unsigned long long)n * (unsigned long long)min(kWave, n - r0);
+        int j = 0;
+        for (; j + 4 <= n; j += 4)
+            visit4(j);
+        for (; j < n; ++j)
+            visit1(j);
         // k+1-th smallest including self (distance 0) = k-th neighbour without self
         const float eps = cur();
 
@@ -626,32 +186,15 @@ __global__ void __launch_bounds__(kMaxWavesPerWG * 64) search_kernel(SearchArgs 
         myrows[lane * RW + D] = eps;
         __builtin_amdgcn_wave_barrier();
 
-        // Candidate range [lo, hi): in a sorted chunk every point outside it is at
-        // |fl32(p0_i - p0_j)| >= eps_i from every reference of the block, hence
-        // outside all three marginal balls (each contains the target-past block).
-        // Pass 1 stopped each direction at a candidate no lane could use with a
-        // radius >= eps_i, so the range lies inside the one pass 1 examined; it is
-        // narrowed from there in steps of 64 points that no reference reaches.
-        int lo = 0, hi = n;
-        if (SORTED) {
-            const int e0 = min(n, r0 + kWave);
-            hi = scan_hi;
-            while (hi - kWave >= e0 && !ballot(valid && absdiff(ref[1], uload(cp.p[1] + hi - kWave)) < eps))
-                hi -= kWave;
-            lo = scan_lo;
-            while (lo + kWave <= r0 && !ballot(valid && absdiff(ref[1], uload(cp.p[1] + lo + kWave - 1)) < eps))
-                lo += kWave;
-        }
-
         const int nref = min(kWave, n - r0);
         uint32_t accP = 0, accTP = 0, accPS = 0;
         unsigned long long evaluated2 = 0;                // candidate-reference pairs examined in pass 2
-        for (int t0 = lo; t0 < hi; t0 += kWave * SLOTS) {
+        for (int t0 = 0; t0 < n; t0 += kWave * SLOTS) {
             float cand[SLOTS][D];
 #pragma unroll
             for (int sl = 0; sl < SLOTS; ++sl) {
                 const int idx = t0 + sl * kWave + lane;
-                const bool ok = idx < hi;
+                const bool ok = idx < n;
                 // in-bounds load, lanes past the range masked below
                 const uint32_t ic4 = (uint32_t)(ok ? idx : n - 1) * 4u;
 #pragma unroll
@@ -661,33 +204,12 @@ __global__ void __launch_bounds__(kMaxWavesPerWG * 64) search_kernel(SearchArgs 
                 }
             }
             uint32_t tP = 0, tTP = 0, tPS = 0;
-            // p0 range of this tile's candidates (sorted chunks): first and last in range
-            float tlo = 0.0f, thi = 0.0f;
-            if (SORTED) {
-                tlo = uload(cp.p[1] + t0);
-                thi = uload(cp.p[1] + min(t0 + kWave * SLOTS, hi) - 1);
-            }
-            // references that can reach this tile: one lane-parallel test (each lane
-            // holds its own reference); in a sorted chunk a reference whose window
-            // [p0 - eps, p0 + eps] misses the tile's p0 range has nothing to count
-            // here and keeps the zero its lane starts the tile with
-            bool reach = valid;
-            if (SORTED)
-                reach = reach && !(tlo - ref[1] >= eps || ref[1] - thi >= eps);
-            uint64_t todo = ballot(reach);
-            evaluated2 += (unsigned long long)__builtin_popcountll(todo) *
-                          (unsigned long long)min(kWave * SLOTS, hi - t0);
+            evaluated2 += (unsigned long long)nref * (unsigned long long)min(kWave * SLOTS, n - t0);
             auto read_row = [&](int r, f4v (&row)[RW / 4]) {
                 const f4v *rowv = reinterpret_cast<const f4v *>(myrows + r * RW);
 #pragma unroll
                 for (int v = 0; v < RW / 4; ++v)
                     row[v] = rowv[v];
-            };
-            // orders a row's counting after the reads issued before it
-            auto pin_row = [&](f4v (&row)[RW / 4]) {
-#pragma unroll
-                for (int v = 0; v < RW / 4; ++v)
-                    asm volatile("" : "+v"(row[v]));
             };
             auto count_ref = [&](const f4v (&row)[RW / 4], int r) {
                 float rr[RW];
@@ -714,50 +236,10 @@ __global__ void __launch_bounds__(kMaxWavesPerWG * 64) search_kernel(SearchArgs 
                 tTP = writelane(tTP, sTP, r);
                 tPS = writelane(tPS, sPS, r);
             };
-            // rows of up to 8 floats (D <= 7): two row buffers used in turn, the
-            // next reference's row read from LDS while the current one is counted.  Each round counts two
-            // references; with an odd number the last one is counted twice, which
-            // writes the same sums to the same lane.
-            if constexpr (RW <= 8) {
-            if (todo != 0) {
-                f4v ra[RW / 4], rb[RW / 4];
-                int ia = __builtin_ctzll(todo);
-                todo &= todo - 1;
-                read_row(ia, ra);
-                for (;;) {
-                    int ib = ia;
-                    if (todo != 0) {
-                        ib = __builtin_ctzll(todo);
-                        todo &= todo - 1;
-                    }
-                    read_row(ib, rb);
-                    __builtin_amdgcn_sched_barrier(0);
-                    pin_row(ra);
-                    count_ref(ra, ia);
-                    const bool more = todo != 0;
-                    int in = ib;
-                    if (more) {
-                        in = __builtin_ctzll(todo);
-                        todo &= todo - 1;
-                    }
-                    read_row(in, ra);
-                    __builtin_amdgcn_sched_barrier(0);
-                    pin_row(rb);
-                    count_ref(rb, ib);
-                    if (!more)
-                        break;
-                    ia = in;
-                }
-            }
-            } else {
-            // wider rows (D > 7): one buffer, so that the occupancy is kept
-            while (todo != 0) {
-                const int r = __builtin_ctzll(todo);
-                todo &= todo - 1;
+            for (int r = 0; r < nref; ++r) {
                 f4v ra[RW / 4];
                 read_row(r, ra);
                 count_ref(ra, r);
-            }
             }
             accP += tP;
             accTP += tTP;
@@ -777,14 +259,14 @@ __global__ void __launch_bounds__(kMaxWavesPerWG * 64) search_kernel(SearchArgs 
         work1 += pass1_pairs;
         work2 += evaluated2;
         if (a.lte_out != nullptr && cd.out >= 0 && valid) {
-            int o = (cd.perm >= 0) ? a.perm_base[cd.perm + i] : i;
+            int o = (cd.perm >= 0) ? order_at(a.perm_base + cd.perm, n, i) : i;
             if (o < 0 || o >= n)
                 o = i;
             a.lte_out[cd.out + o] = psi_of_count(k - 1) + term;
         }
         if (a.eps_out != nullptr && cd.out >= 0 && valid) {
             // per-point outputs go to the point's index before sorting
-            int o = (cd.perm >= 0) ? a.perm_base[cd.perm + i] : i;
+            int o = (cd.perm >= 0) ? order_at(a.perm_base + cd.perm, n, i) : i;
             if (o < 0 || o >= n)         // keep writes inside the chunk's output range regardless
                 o = i;
             a.eps_out[cd.out + o] = eps;
@@ -800,567 +282,6 @@ __global__ void __launch_bounds__(kMaxWavesPerWG * 64) search_kernel(SearchArgs 
         atomicAdd(a.work + 2, work1);
         atomicAdd(a.work + 3, work2);
     }
-}
-
-// ------------------------------------------------ the search over chunk sets
-//
-// The chunks of one window (its original and its surrogates, or its delays)
-// share the (y_t', Y_past) block and its sorted order and differ only in the
-// source block.  This variant searches a set of up to V such chunks per work
-// item: for every (reference, candidate) pair the target-future and
-// target-past differences are taken once, and only the source-past part is
-// evaluated per chunk.  Radii, counts and per-item sums are those of the
-// single-chunk search bit for bit (the same float operations decide every
-// comparison; only the order in which independent pairs are visited and which
-// lanes share a step differ).  Sorted chunks only.
-//
-//   d_J(v) = max(d_TP, d_S(v)),  d_TP = max(d_T, d_P)
-//   n_TP  counts [d_TP < eps_v],  n_PS counts [max(d_P, d_S(v)) < eps_v]
-//
-// A set is a run of consecutive chunk descriptors [set_first[c], set_first[c+1]);
-// its first descriptor supplies tp, ld, n, item0 and block0, each descriptor
-// its own s and pbase.  Sets with fewer than V chunks repeat their last chunk
-// in the unused variant slots and do not store those slots' sums.
-
-// Wide sets (a candidate's coordinates, 1 + d_y + V d_x, at least 16) keep their per-tile counts packed three
-// to a register (PACK) and are compiled for six waves per SIMD; see the kernels after this body.
-template <int DY, int DX, int V, int SLOTS, bool PACK>
-__device__ __forceinline__ void sets_search(const SearchArgs &a)
-{
-    constexpr int DT = 1 + DY;                 // shared coordinates: y_t' and the target past
-    constexpr int KP1 = 5;                     // k = 4: the k+1 smallest distances, self included
-    constexpr int NR = DT + V * DX + V;        // LDS row: shared coordinates, V source blocks, V radii
-    constexpr int RW = (NR + 3) & ~3;
-    constexpr int MO = DT > DX ? DT : DX;      // coordinate offsets shared by the target and source blocks
-    extern __shared__ __attribute__((aligned(16))) float rows[];   // waves per workgroup x 64 x RW floats
-    const int lane = threadIdx.x & (kWave - 1);
-
-    const int nq = a.n_parts > 1 ? a.n_parts : 1;
-    int qp = (int)(blockIdx.x % (unsigned)nq);
-    int drained = 0;
-    int last_ci = 0, last_lo = 0, last_hi = 0;
-    unsigned long long work1 = 0, work2 = 0, shared1 = 0, shared2 = 0;
-    for (;;) {
-        int q = 0;
-        if (lane == 0)
-            q = atomicAdd(a.counter + qp, 1);
-        q = __builtin_amdgcn_readlane(q, 0);
-        if (nq > 1) {
-            q += uload_i(a.part_start + qp);
-            if (q >= uload_i(a.part_start + qp + 1)) {
-                if (++drained >= nq)
-                    break;
-                qp = qp + 1 == nq ? 0 : qp + 1;
-                continue;
-            }
-        } else if (q >= a.n_items) {
-            break;
-        }
-        if (q < last_lo || q >= last_hi) {
-            last_ci = find_chunk(a.item_start, a.n_chunks, q);
-            last_lo = uload_i(a.item_start + last_ci);
-            last_hi = last_ci + 1 < a.n_chunks ? uload_i(a.item_start + last_ci + 1) : a.n_items;
-        }
-        const int c0 = uload_i(a.set_first + last_ci);
-        const int cnt = uload_i(a.set_first + last_ci + 1) - c0;   // chunks in the set, 1..V
-        const char *w0 = reinterpret_cast<const char *>(a.chunks + c0);
-        const int64_t tp = uload_l(reinterpret_cast<const int64_t *>(w0 + offsetof(ChunkDesc, tp)));
-        const int64_t ld = uload_l(reinterpret_cast<const int64_t *>(w0 + offsetof(ChunkDesc, ld)));
-        const int n = uload_i(reinterpret_cast<const int32_t *>(w0 + offsetof(ChunkDesc, n)));
-        const int item0 = uload_i(reinterpret_cast<const int32_t *>(w0 + offsetof(ChunkDesc, item0)));
-        const int block0 = uload_i(reinterpret_cast<const int32_t *>(w0 + offsetof(ChunkDesc, block0)));
-        const float *tb = a.base + tp;                 // target block of the set
-        const float *sb[V];                            // source block of each variant
-        int64_t pb[V];
-#pragma unroll
-        for (int v = 0; v < V; ++v) {
-            const char *wv = reinterpret_cast<const char *>(a.chunks + c0 + min(v, cnt - 1));
-            sb[v] = a.base + uload_l(reinterpret_cast<const int64_t *>(wv + offsetof(ChunkDesc, s)));
-            pb[v] = uload_l(reinterpret_cast<const int64_t *>(wv + offsetof(ChunkDesc, pbase)));
-        }
-        uint32_t moff[MO];                             // byte offset of coordinate m within a block
-#pragma unroll
-        for (int m = 0; m < MO; ++m)
-            moff[m] = (uint32_t)((int64_t)m * ld * 4);
-
-        int blk = q - item0 + block0;
-        const int nb = (n + kWave - 1) / kWave;
-        if (block0 == 0 && last_hi - last_lo == nb) {
-            // middle blocks (densest in the p0 order) first, as in the single-chunk search
-            const int mid = nb >> 1, kk = blk;
-            const int pairs = min(mid, nb - mid);
-            if (kk < 2 * pairs)
-                blk = (kk & 1) ? mid - 1 - (kk >> 1) : mid + (kk >> 1);
-            else
-                blk = nb - mid > mid ? mid + pairs + (kk - 2 * pairs) : mid - 1 - pairs - (kk - 2 * pairs);
-        }
-        const int r0 = blk * kWave;
-
-        // ---- pass 1: lane = reference i
-        const int i = r0 + lane;
-        const bool valid = i < n;
-        const int ii = valid ? i : n - 1;
-        float rt[DT];
-        float rs[V][DX];
-#pragma unroll
-        for (int m = 0; m < DT; ++m)
-            rt[m] = tb[(int64_t)m * ld + ii];
-#pragma unroll
-        for (int v = 0; v < V; ++v)
-#pragma unroll
-            for (int m = 0; m < DX; ++m)
-                rs[v][m] = sb[v][(int64_t)m * ld + ii];
-        float best[V][KP1];
-#pragma unroll
-        for (int v = 0; v < V; ++v)
-#pragma unroll
-            for (int s = 0; s < KP1; ++s)
-                best[v][s] = kInf;
-        // largest current k+1-th distance over the variants: a candidate farther
-        // than it in p0 is of no use to any variant
-        auto curmax = [&]() {
-            float c = best[0][KP1 - 1];
-#pragma unroll
-            for (int v = 1; v < V; ++v)
-                c = fmaxf(c, best[v][KP1 - 1]);
-            return c;
-        };
-        // four consecutive candidates j..j+3: target coordinates ct, source coordinates cs
-        auto load4 = [&](int j, float (&ct)[4][DT], float (&cs)[V][4][DX]) {
-            const uint32_t off = (uint32_t)j * 4u;
-#pragma unroll
-            for (int m = 0; m < DT; ++m) {
-                const f4v x = uload4_at(tb, moff[m] + off);
-                ct[0][m] = x.x;
-                ct[1][m] = x.y;
-                ct[2][m] = x.z;
-                ct[3][m] = x.w;
-            }
-#pragma unroll
-            for (int v = 0; v < V; ++v)
-#pragma unroll
-                for (int m = 0; m < DX; ++m) {
-                    const f4v x = uload4_at(sb[v], moff[m] + off);
-                    cs[v][0][m] = x.x;
-                    cs[v][1][m] = x.y;
-                    cs[v][2][m] = x.z;
-                    cs[v][3][m] = x.w;
-                }
-        };
-        auto visit4 = [&](const float (&ct)[4][DT], const float (&cs)[V][4][DX]) {
-            float dtp[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                float d = absdiff(rt[0], ct[u][0]);
-#pragma unroll
-                for (int m = 1; m < DT; ++m)
-                    d = fmaxf(d, absdiff(rt[m], ct[u][m]));
-                dtp[u] = d;
-            }
-#pragma unroll
-            for (int v = 0; v < V; ++v) {
-                float dj[4];
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    float d = absdiff(rs[v][0], cs[v][u][0]);
-#pragma unroll
-                    for (int m = 1; m < DX; ++m)
-                        d = fmaxf(d, absdiff(rs[v][m], cs[v][u][m]));
-                    dj[u] = fmaxf(dtp[u], d);
-                }
-                const float mn = fminf(fminf(dj[0], dj[1]), fminf(dj[2], dj[3]));
-                if (ballot(mn < best[v][KP1 - 1])) {
-                    keep_branch();
-#pragma unroll
-                    for (int u = 0; u < 4; ++u)
-                        if (ballot(dj[u] < best[v][KP1 - 1])) {
-                            keep_branch();
-                            insert_sorted<KP1>(best[v], dj[u]);
-                        }
-                }
-            }
-        };
-        auto visit1 = [&](int j) {
-            float dtp = absdiff(rt[0], uload(tb + j));
-#pragma unroll
-            for (int m = 1; m < DT; ++m)
-                dtp = fmaxf(dtp, absdiff(rt[m], uload(tb + (int64_t)m * ld + j)));
-#pragma unroll
-            for (int v = 0; v < V; ++v) {
-                float d = absdiff(rs[v][0], uload(sb[v] + j));
-#pragma unroll
-                for (int m = 1; m < DX; ++m)
-                    d = fmaxf(d, absdiff(rs[v][m], uload(sb[v] + (int64_t)m * ld + j)));
-                const float dj = fmaxf(dtp, d);
-                if (ballot(dj < best[v][KP1 - 1])) {
-                    keep_branch();
-                    insert_sorted<KP1>(best[v], dj);
-                }
-            }
-        };
-
-        // the block's own points, then outward in p0 order, forward then backward;
-        // a direction stops at the first group whose farthest candidate no lane of
-        // any variant could use (p0 is coordinate 1, a target-past coordinate)
-        const int e0 = min(n, r0 + kWave);
-        int j = r0;
-        for (; j + 4 <= e0; j += 4) {
-            float ct[4][DT], cs[V][4][DX];
-            load4(j, ct, cs);
-            visit4(ct, cs);
-        }
-        for (; j < e0; ++j)
-            visit1(j);
-        // Outward from the block: for chunks of at least kTileScanMin points in tiles of 64
-        // candidates against the references whose windows reach them, below that in groups
-        // of four candidates against all 64 references.
-        int f, b;
-        unsigned long long ev = (unsigned long long)(e0 - r0) * (unsigned long long)min(kWave, n - r0);
-        if (n >= kTileScanMin) {
-            // then outward in tiles of 64 candidates (lane = candidate), alternating forward and
-            // backward, each compared only with the references whose p0 window at their largest
-            // current radius reaches the tile; the LDS row of a reference holds its coordinates
-            // and its current (k+1)-th distance per variant
-            float *prow = rows + (threadIdx.x / kWave) * (kWave * RW);
-            __builtin_amdgcn_wave_barrier();
-#pragma unroll
-            for (int m = 0; m < DT; ++m)
-                prow[lane * RW + m] = rt[m];
-#pragma unroll
-            for (int v = 0; v < V; ++v) {
-#pragma unroll
-                for (int m = 0; m < DX; ++m)
-                    prow[lane * RW + DT + v * DX + m] = rs[v][m];
-                prow[lane * RW + DT + V * DX + v] = best[v][KP1 - 1];
-            }
-            __builtin_amdgcn_wave_barrier();
-            auto read_row = [&](int r, float (&rr)[RW]) {
-                const f4v *rowv = reinterpret_cast<const f4v *>(prow + r * RW);
-#pragma unroll
-                for (int x = 0; x < RW / 4; ++x) {
-                    const f4v q4 = rowv[x];
-                    rr[4 * x + 0] = q4.x;
-                    rr[4 * x + 1] = q4.y;
-                    rr[4 * x + 2] = q4.z;
-                    rr[4 * x + 3] = q4.w;
-                }
-            };
-            // a tile: 64 x TS candidates; two slots only where their coordinates stay few (the
-            // candidate registers of a second slot would otherwise cost a wave per SIMD)
-            constexpr int TS = (DT + V * DX <= 8) ? 2 : 1;
-            auto tile = [&](int t0, int t1) {
-                float ct[TS][DT], cs[TS][V][DX];
-#pragma unroll
-                for (int sl = 0; sl < TS; ++sl) {
-                    const int idx = t0 + sl * kWave + lane;
-                    const bool ok = idx < t1;
-                    const uint32_t ic4 = (uint32_t)(ok ? idx : t0) * 4u;
-#pragma unroll
-                    for (int m = 0; m < DT; ++m) {
-                        const float x = vload_at(tb, moff[m] + ic4);
-                        ct[sl][m] = ok ? x : kInf;
-                    }
-#pragma unroll
-                    for (int v = 0; v < V; ++v)
-#pragma unroll
-                        for (int m = 0; m < DX; ++m) {
-                            const float x = vload_at(sb[v], moff[m] + ic4);
-                            cs[sl][v][m] = ok ? x : kInf;
-                        }
-                }
-                const float tlo = uload(tb + ld + t0), thi = uload(tb + ld + t1 - 1);
-                const float c0 = curmax();
-                uint64_t todo = ballot(valid && !(tlo - rt[1] >= c0 || rt[1] - thi >= c0));
-                ev += (unsigned long long)__builtin_popcountll(todo) * (unsigned long long)(t1 - t0);
-                // the tile against reference r (row rr): one branch per slot when no variant of the
-                // reference improves, which is the common case once its lists have settled
-                auto against = [&](int r, const float (&rr)[RW]) {
-                    float ut[V];
-#pragma unroll
-                    for (int v = 0; v < V; ++v)
-                        ut[v] = rr[DT + V * DX + v];
-#pragma unroll
-                    for (int sl = 0; sl < TS; ++sl) {
-                        float dtp = absdiff(rr[0], ct[sl][0]);
-#pragma unroll
-                        for (int m = 1; m < DT; ++m)
-                            dtp = fmaxf(dtp, absdiff(rr[m], ct[sl][m]));
-                        float dj[V];
-                        uint64_t hm[V], any = 0;
-#pragma unroll
-                        for (int v = 0; v < V; ++v) {
-                            float d = absdiff(rr[DT + v * DX], cs[sl][v][0]);
-#pragma unroll
-                            for (int m = 1; m < DX; ++m)
-                                d = fmaxf(d, absdiff(rr[DT + v * DX + m], cs[sl][v][m]));
-                            dj[v] = fmaxf(dtp, d);
-                            hm[v] = ballot(dj[v] < ut[v]);
-                            any |= hm[v];
-                        }
-                        if (any == 0)
-                            continue;
-                        keep_branch();
-#pragma unroll
-                        for (int v = 0; v < V; ++v) {
-                            uint64_t hit = hm[v];
-                            while (hit != 0) {
-                                keep_branch();
-                                const int c = __builtin_ctzll(hit);
-                                const float x = __builtin_bit_cast(
-                                    float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, dj[v]), c));
-                                if (lane == r) {
-                                    insert_sorted<KP1>(best[v], x);
-                                    prow[r * RW + DT + V * DX + v] = best[v][KP1 - 1];
-                                }
-                                ut[v] = __builtin_bit_cast(
-                                    float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, best[v][KP1 - 1]), r));
-                                hit &= hit - 1;
-                                hit &= ballot(dj[v] < ut[v]);
-                            }
-                        }
-                    }
-                };
-                while (todo != 0) {
-                    const int r = __builtin_ctzll(todo);
-                    todo &= todo - 1;
-                    float rr[RW];
-                    read_row(r, rr);
-                    against(r, rr);
-                }
-            };
-            f = e0;
-            b = r0;
-            bool fgo = f < n && ballot(valid && absdiff(rt[1], uload(tb + ld + f)) < curmax()) != 0;
-            bool bgo = b > 0 && ballot(valid && absdiff(rt[1], uload(tb + ld + b - 1)) < curmax()) != 0;
-            while (fgo || bgo) {
-                if (fgo) {
-                    const int t1 = min(n, f + kWave * TS);
-                    tile(f, t1);
-                    f = t1;
-                    fgo = f < n && ballot(valid && absdiff(rt[1], uload(tb + ld + f)) < curmax()) != 0;
-                }
-                if (bgo) {
-                    const int t0 = max(0, b - kWave * TS);
-                    tile(t0, b);
-                    b = t0;
-                    bgo = b > 0 && ballot(valid && absdiff(rt[1], uload(tb + ld + b - 1)) < curmax()) != 0;
-                }
-            }
-        } else {
-            f = e0;
-            bool go = f < n;
-            while (go && f + 4 <= n) {
-                float ct[4][DT], cs[V][4][DX];
-                load4(f, ct, cs);
-                visit4(ct, cs);
-                f += 4;
-                go = f < n && ballot(absdiff(rt[1], ct[3][1]) < curmax()) != 0;
-            }
-            while (go && f < n) {
-                const float p0 = uload(tb + ld + f);
-                visit1(f);
-                ++f;
-                go = f < n && ballot(absdiff(rt[1], p0) < curmax()) != 0;
-            }
-            b = r0;
-            go = b > 0;
-            while (go && b >= 4) {
-                float ct[4][DT], cs[V][4][DX];
-                load4(b - 4, ct, cs);
-                visit4(ct, cs);
-                b -= 4;
-                go = b > 0 && ballot(absdiff(rt[1], ct[0][1]) < curmax()) != 0;
-            }
-            while (go && b > 0) {
-                const float p0 = uload(tb + ld + b - 1);
-                visit1(b - 1);
-                --b;
-                go = b > 0 && ballot(absdiff(rt[1], p0) < curmax()) != 0;
-            }
-            ev = (unsigned long long)(f - b) * (unsigned long long)min(kWave, n - r0);
-        }
-        float eps[V];
-#pragma unroll
-        for (int v = 0; v < V; ++v)
-            eps[v] = best[v][KP1 - 1];
-        const float emax = curmax();
-
-        // ---- pass 2: lane = candidate, references uniform from this wave's LDS rows
-        float *myrows = rows + (threadIdx.x / kWave) * (kWave * RW);
-        __builtin_amdgcn_wave_barrier();
-#pragma unroll
-        for (int m = 0; m < DT; ++m)
-            myrows[lane * RW + m] = rt[m];
-#pragma unroll
-        for (int v = 0; v < V; ++v) {
-#pragma unroll
-            for (int m = 0; m < DX; ++m)
-                myrows[lane * RW + DT + v * DX + m] = rs[v][m];
-            myrows[lane * RW + DT + V * DX + v] = eps[v];
-        }
-        __builtin_amdgcn_wave_barrier();
-
-        // candidate range: outside it every point is at |fl32(p0_i - p0_j)| >= the
-        // largest radius of every reference of the block
-        int hi = f;
-        while (hi - kWave >= e0 && !ballot(valid && absdiff(rt[1], uload(tb + ld + hi - kWave)) < emax))
-            hi -= kWave;
-        int lo = b;
-        while (lo + kWave <= r0 && !ballot(valid && absdiff(rt[1], uload(tb + ld + lo + kWave - 1)) < emax))
-            lo += kWave;
-
-        const int nref = min(kWave, n - r0);
-        uint32_t accP[V], accTP[V], accPS[V];
-#pragma unroll
-        for (int v = 0; v < V; ++v)
-            accP[v] = accTP[v] = accPS[v] = 0;
-        unsigned long long evaluated2 = 0;
-        for (int t0 = lo; t0 < hi; t0 += kWave * SLOTS) {
-            float ct[SLOTS][DT], cs[SLOTS][V][DX];
-#pragma unroll
-            for (int sl = 0; sl < SLOTS; ++sl) {
-                const int idx = t0 + sl * kWave + lane;
-                const bool ok = idx < hi;
-                const uint32_t ic4 = (uint32_t)(ok ? idx : n - 1) * 4u;
-#pragma unroll
-                for (int m = 0; m < DT; ++m) {
-                    const float x = vload_at(tb, moff[m] + ic4);
-                    ct[sl][m] = ok ? x : kInf;
-                }
-#pragma unroll
-                for (int v = 0; v < V; ++v)
-#pragma unroll
-                    for (int m = 0; m < DX; ++m) {
-                        const float x = vload_at(sb[v], moff[m] + ic4);
-                        cs[sl][v][m] = ok ? x : kInf;
-                    }
-            }
-            const float tlo = uload(tb + ld + t0);
-            const float thi = uload(tb + ld + min(t0 + kWave * SLOTS, hi) - 1);
-            const bool reach = valid && !(tlo - rt[1] >= emax || rt[1] - thi >= emax);
-            uint64_t todo = ballot(reach);
-            evaluated2 += (unsigned long long)__builtin_popcountll(todo) *
-                          (unsigned long long)min(kWave * SLOTS, hi - t0);
-            // per-tile counts of every reference in its lane; with PACK as n_P | n_TP << 10 | n_PS << 20 (a
-            // tile has at most 64 x SLOTS candidates), one register and one v_writelane per variant
-            static_assert(!PACK || kWave * SLOTS < 1024, "packed per-tile counts take 10 bits each");
-            uint32_t tP[V], tTP[V], tPS[V];
-#pragma unroll
-            for (int v = 0; v < V; ++v)
-                tP[v] = tTP[v] = tPS[v] = 0;
-            while (todo != 0) {
-                const int r = __builtin_ctzll(todo);
-                todo &= todo - 1;
-                float rr[RW];
-                {
-                    const f4v *rowv = reinterpret_cast<const f4v *>(myrows + r * RW);
-#pragma unroll
-                    for (int x = 0; x < RW / 4; ++x) {
-                        const f4v q4 = rowv[x];
-                        rr[4 * x + 0] = q4.x;
-                        rr[4 * x + 1] = q4.y;
-                        rr[4 * x + 2] = q4.z;
-                        rr[4 * x + 3] = q4.w;
-                    }
-                }
-                uint32_t sP[V], sTP[V], sPS[V];
-#pragma unroll
-                for (int v = 0; v < V; ++v)
-                    sP[v] = sTP[v] = sPS[v] = 0;
-#pragma unroll
-                for (int sl = 0; sl < SLOTS; ++sl) {
-                    float dp = absdiff(rr[1], ct[sl][1]);
-#pragma unroll
-                    for (int m = 2; m < DT; ++m)
-                        dp = fmaxf(dp, absdiff(rr[m], ct[sl][m]));
-                    const float dtp = fmaxf(absdiff(rr[0], ct[sl][0]), dp);
-#pragma unroll
-                    for (int v = 0; v < V; ++v) {
-                        float ds = absdiff(rr[DT + v * DX], cs[sl][v][0]);
-#pragma unroll
-                        for (int m = 1; m < DX; ++m)
-                            ds = fmaxf(ds, absdiff(rr[DT + v * DX + m], cs[sl][v][m]));
-                        const float er = rr[DT + V * DX + v];
-                        sP[v] += (uint32_t)__builtin_popcountll(ballot(dp < er));
-                        sTP[v] += (uint32_t)__builtin_popcountll(ballot(dtp < er));
-                        sPS[v] += (uint32_t)__builtin_popcountll(ballot(fmaxf(dp, ds) < er));
-                    }
-                }
-#pragma unroll
-                for (int v = 0; v < V; ++v) {
-                    if constexpr (PACK) {
-                        tP[v] = writelane(tP[v], sP[v] | (sTP[v] << 10) | (sPS[v] << 20), r);
-                    } else {
-                        tP[v] = writelane(tP[v], sP[v], r);
-                        tTP[v] = writelane(tTP[v], sTP[v], r);
-                        tPS[v] = writelane(tPS[v], sPS[v], r);
-                    }
-                }
-            }
-#pragma unroll
-            for (int v = 0; v < V; ++v) {
-                if constexpr (PACK) {
-                    accP[v] += tP[v] & 1023u;
-                    accTP[v] += (tP[v] >> 10) & 1023u;
-                    accPS[v] += tP[v] >> 20;
-                } else {
-                    accP[v] += tP[v];
-                    accTP[v] += tTP[v];
-                    accPS[v] += tPS[v];
-                }
-            }
-        }
-
-        // ---- digamma terms per variant, summed over the item in fixed order
-#pragma unroll
-        for (int v = 0; v < V; ++v) {
-            const uint32_t self = eps[v] > 0.0f ? 1u : 0u;
-            double term = 0.0;
-            if (valid)
-                term = psi_of_count((int)(accP[v] - self)) - psi_of_count((int)(accTP[v] - self)) -
-                       psi_of_count((int)(accPS[v] - self));
-            const double sum = wave_sum(term);
-            if (lane == 0 && v < cnt)
-                a.partial[pb[v] + blk] = sum;
-        }
-        work1 += ev * (unsigned long long)cnt;
-        work2 += evaluated2 * (unsigned long long)cnt;
-        shared1 += ev;
-        shared2 += evaluated2;
-    }
-    if (a.work != nullptr && lane == 0) {
-        atomicAdd(a.work, work1);
-        atomicAdd(a.work + 1, work2);
-        atomicAdd(a.work + 2, shared1);
-        atomicAdd(a.work + 3, shared2);
-    }
-}
-
-template <int DY, int DX, int V, int SLOTS>
-__global__ void __launch_bounds__(kMaxWavesPerWG * 64) search_sets_kernel(SearchArgs a)
-{
-    sets_search<DY, DX, V, SLOTS, false>(a);
-}
-
-// Wide sets: at (3, 3, four chunks) the plain body needs 93 VGPRs (five waves per SIMD); packed counts and a
-// six-wave bound bring it to 80 with a few spills to scratch, 2 % faster on the uneven-surrogate batch, while the
-// narrower sets lost 2-4 % the same way.
-template <int DY, int DX, int V, int SLOTS>
-__global__ void __launch_bounds__(kMaxWavesPerWG * 64) __attribute__((amdgpu_waves_per_eu(6, 8)))
-search_sets_wide_kernel(SearchArgs a)
-{
-    sets_search<DY, DX, V, SLOTS, true>(a);
-}
-
-constexpr bool wide_set(int d_y, int d_x) { return 1 + d_y + set_variants(d_y, d_x) * d_x >= 16; }
-
-template <int DY, int DX, int SLOTS>
-void (*sets_fn())(SearchArgs)
-{
-    if constexpr (wide_set(DY, DX))
-        return search_sets_wide_kernel<DY, DX, set_variants(DY, DX), SLOTS>;
-    else
-        return search_sets_kernel<DY, DX, set_variants(DY, DX), SLOTS>;
 }
 
 // ------------------------------------------------------------ small kernels
@@ -1386,8 +307,25 @@ __global__ void fill_i32_kernel(int32_t *p, int32_t v, int64_t n)
         p[i] = v;
 }
 
+// Box of a wave's 64 values: their smallest and largest, in every lane; unbounded if one is no
+// number (its distances then say nothing, so nothing may be skipped for them).
+__device__ __forceinline__ void wave_box(float v, float *lo, float *hi)
+{
+    float a = v != v ? -kInf : v, b = v != v ? kInf : v;
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) {
+        a = fminf(a, __shfl_xor(a, o, 64));
+        b = fmaxf(b, __shfl_xor(b, o, 64));
+    }
+    *lo = a;
+    *hi = b;
+}
+
+// One wave per block of 64 points at a time: the block's coordinates gathered through the order
+// map, and with the window's first target block the block's box (target-past coordinates; the
+// current source sample, which shuffles with the source, stays unbounded).
 __global__ void embed_kernel(const float *__restrict__ x, const float *__restrict__ y,
-                             const int32_t *__restrict__ perms, const int32_t *__restrict__ sigma,
+                             const int32_t *__restrict__ perms, int32_t *sigma, uint64_t *scratch,
                              const int32_t *__restrict__ u_dev, const EmbedTask *__restrict__ tasks,
                              float *__restrict__ base, int R, int T, int d_y, int d_x, int tau, int u, int cond,
                              int32_t *err)
@@ -1402,13 +340,22 @@ __global__ void embed_kernel(const float *__restrict__ x, const float *__restric
     // the host checks every delay against the window starts; keep reads in bounds regardless
     const bool u_ok = u >= 1 && tk.w - u - (d_x - 1) * tau >= 0 && tk.w + tk.W - u <= T;
     const int64_t pr = (int64_t)tk.pair * R;
+    const int lane = threadIdx.x & (kWave - 1);
+    const int nb = (n + kWave - 1) / kWave;
+    float *box = nullptr;
+    if (tk.box == 0)
+        box = reinterpret_cast<float *>(sigma + tk.sig + box_words_behind_map(n));
+    else if (tk.box > 0)
+        box = reinterpret_cast<float *>(scratch + (int64_t)(tk.box - 1) * kBoxScratchUnit);
     bool bad = false;
-    for (int q = blockIdx.y * blockDim.x + threadIdx.x; q < n; q += blockDim.x * gridDim.y) {
-        // position q of the (sorted) chunk holds window point qo = r W + (t' - w)
+    for (int qb = blockIdx.y * blockDim.x + (threadIdx.x - lane); qb < n; qb += blockDim.x * gridDim.y) {
+        const bool ok = qb + lane < n;
+        const int q = ok ? qb + lane : n - 1;
+        // position q of the (ordered) chunk holds window point qo = r W + (t' - w)
         int qo = q;
         if (tk.sig >= 0) {
-            qo = sigma[tk.sig + q];
-            if (qo < 0 || qo >= n) {   // cannot happen for maps made by sort_kernel; keep reads in bounds
+            qo = order_at(sigma + tk.sig, n, q);
+            if (qo < 0 || qo >= n) {   // cannot happen for maps made by order_kernel; keep reads in bounds
                 bad = true;
                 qo = q;
             }
@@ -1428,11 +375,21 @@ __global__ void embed_kernel(const float *__restrict__ x, const float *__restric
         if (tk.tp >= 0) {
             const float v0 = yr[t];
             bad |= !isfinite(v0);
-            base[tk.tp + q] = v0;
+            if (ok)
+                base[tk.tp + q] = v0;
             for (int m = 0; m < d_y; ++m) {
                 const float v = yr[t - 1 - m * tau];
                 bad |= !isfinite(v);
-                base[tk.tp + (int64_t)(1 + m) * n + q] = v;
+                if (ok)
+                    base[tk.tp + (int64_t)(1 + m) * n + q] = v;
+                if (box != nullptr) {
+                    float lo, hi;
+                    wave_box(v, &lo, &hi);
+                    if (lane == 0) {
+                        box[(int64_t)(2 * m) * nb + qb / kWave] = lo;
+                        box[(int64_t)(2 * m + 1) * nb + qb / kWave] = hi;
+                    }
+                }
             }
         }
         bad |= !u_ok;
@@ -1441,25 +398,29 @@ __global__ void embed_kernel(const float *__restrict__ x, const float *__restric
             // target-past row of this chunk's own target block (it follows the shuffle)
             const float v = xr[t];
             bad |= !isfinite(v);
-            base[tk.tp + (int64_t)(1 + d_y) * n + q] = v;
+            if (ok)
+                base[tk.tp + (int64_t)(1 + d_y) * n + q] = v;
+            if (box != nullptr && lane == 0) {
+                box[(int64_t)(2 * d_y) * nb + qb / kWave] = -kInf;
+                box[(int64_t)(2 * d_y + 1) * nb + qb / kWave] = kInf;
+            }
         }
         for (int m = 0; m < d_x; ++m) {
             const float v = u_ok ? xr[t - u - m * tau] : 0.0f;
             bad |= !isfinite(v);
-            base[tk.s + (int64_t)m * n + q] = v;
+            if (ok)
+                base[tk.s + (int64_t)m * n + q] = v;
         }
     }
     if (bad)
         atomicOr(err, 1);
 }
 
-// Order-preserving unsigned image of a float (negative values reversed), joined
-// with the point index so that every key is distinct.
-__device__ __forceinline__ uint64_t sort_key(float f, uint32_t q)
+// Order-preserving unsigned image of a float (negative values reversed).
+__device__ __forceinline__ uint32_t orderable(float f)
 {
-    uint32_t u = __builtin_bit_cast(uint32_t, f);
-    u = (u & 0x80000000u) ? ~u : (u | 0x80000000u);
-    return ((uint64_t)u << 32) | q;
+    const uint32_t u = __builtin_bit_cast(uint32_t, f);
+    return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
 // One bitonic compare-exchange pass with stride jj inside stage kk over the
@@ -1532,133 +493,417 @@ __device__ void bitonic_lds(uint64_t *A, int len, int kk_first, int kk_last, int
     }
 }
 
-// One workgroup sorts one search space by its first target-past coordinate:
-// a bitonic network over npad = 2^m keys (padding keys sort last).  Up to
-// kSortLds keys the whole network runs in LDS.  Above that the keys live in
-// global scratch; every stage's passes with stride below kSortLds only pair
-// elements of the same kSortLds-aligned tile, so each tile is loaded into LDS
-// once per stage for those passes and only the wider strides touch global memory.
-// Stable LSD radix sort of up to kRadixMax packed keys (order key in the high 32
-// bits, point index in the low 32) by their high 32 bits, 4 bits per pass, with
-// kRadixThreads threads: thread t owns a contiguous run of keys, counts its
-// digits into column t of L (digit-major), an exclusive scan over L gives every
-// (digit, thread) its first output slot, and each thread scatters its run in
-// order.  Keys enter in index order, so equal keys stay in index order: the
-// result is the order of the full 64-bit keys.  Returns the buffer holding it.
-constexpr int kRadixMax = 8192;
-constexpr int kRadixThreads = 512;
-
-__device__ uint64_t *radix_sort_lds(uint64_t *A, uint64_t *B, uint16_t *L, uint32_t *wsum, int n)
+// First block of the slab that block `leaf` of nl lies in after `levels` cuts.
+__device__ __forceinline__ int slab_start(int leaf, int nl, int nd, int levels)
 {
-    const int t = threadIdx.x;
-    const bool act = t < kRadixThreads;
-    const int c = (n + kRadixThreads - 1) / kRadixThreads;
-    const int i0 = min(n, t * c), i1 = min(n, i0 + c);
-    const int lane = t & (kWave - 1), wave = t / kWave;
-    for (int shift = 32; shift < 64; shift += 4) {
-        if (act) {
-#pragma unroll
-            for (int d = 0; d < 16; ++d)
-                L[d * kRadixThreads + t] = 0;
-            for (int i = i0; i < i1; ++i) {
-                const int d = (int)((A[i] >> shift) & 15u);
-                L[d * kRadixThreads + t] = (uint16_t)(L[d * kRadixThreads + t] + 1);
-            }
-        }
-        __syncthreads();
-        // exclusive scan over the 16 x kRadixThreads counts, digit-major: thread s
-        // owns the 16 consecutive entries [16 s, 16 s + 16)
-        uint32_t own = 0;
-        if (act)
-#pragma unroll
-            for (int e = 0; e < 16; ++e)
-                own += L[16 * t + e];
-        uint32_t inc = own;                       // inclusive scan over the wave
-#pragma unroll
-        for (int off = 1; off < kWave; off <<= 1) {
-            const uint32_t v = __shfl_up(inc, off);
-            if (lane >= off)
-                inc += v;
-        }
-        if (act && lane == kWave - 1)
-            wsum[wave] = inc;
-        __syncthreads();
-        if (act) {
-            uint32_t base = inc - own;
-            for (int w = 0; w < wave; ++w)
-                base += wsum[w];
-#pragma unroll
-            for (int e = 0; e < 16; ++e) {
-                const uint32_t v = L[16 * t + e];
-                L[16 * t + e] = (uint16_t)base;
-                base += v;
-            }
-        }
-        __syncthreads();
-        if (act)
-            for (int i = i0; i < i1; ++i) {
-                const uint64_t key = A[i];
-                const int d = (int)((key >> shift) & 15u);
-                const int slot = L[d * kRadixThreads + t];
-                L[d * kRadixThreads + t] = (uint16_t)(slot + 1);
-                B[slot] = key;
-            }
-        __syncthreads();
-        uint64_t *tmp = A;
-        A = B;
-        B = tmp;
+    int first = 0, cnt = nl;
+    for (int j = 0; j < levels; ++j) {
+        const int s = slab_count(cnt, nd - j);
+        // slab i of the run holds its blocks [cnt i / s, cnt (i + 1) / s)
+        const int i = (int)(((int64_t)s * (leaf - first + 1) - 1) / cnt);
+        const int a = (int)((int64_t)cnt * i / s), b = (int)((int64_t)cnt * (i + 1) / s);
+        first += a;
+        cnt = b - a;
     }
-    return A;
+    return first;
 }
 
-__global__ void __launch_bounds__(1024) sort_kernel(const float *__restrict__ y, const float *__restrict__ pts,
-                                                    const SortTask *__restrict__ tasks, int32_t *__restrict__ sigma,
-                                                    uint64_t *__restrict__ scratch, int R, int T)
+// Whether cutting at level m leaves every slab of nl blocks whole: its sort would be for nothing.
+__device__ __forceinline__ bool idle_level(int nl, int nd, int m)
 {
-    __shared__ uint64_t lds[kSortLds];
-    __shared__ uint16_t radix_cnt[16 * kRadixThreads];
-    __shared__ uint32_t radix_wsum[kRadixThreads / kWave];
-    const SortTask tk = tasks[blockIdx.x];
-    const int np = tk.npad;
-    if (tk.n <= kRadixMax) {
-        // small windows: radix sort in LDS (8 passes instead of a log^2 network)
-        for (int i = threadIdx.x; i < tk.n; i += blockDim.x) {
-            float f;
-            if (tk.mode == 0) {
-                const int r = i / tk.W;
-                const int t = tk.w + (i - r * tk.W);
-                f = y[((int64_t)tk.pair * R + r) * T + t - 1];
-            } else {
-                f = pts[tk.key_off + i];
-            }
-            lds[i] = sort_key(f, (uint32_t)i);
-        }
-        __syncthreads();
-        const uint64_t *S = radix_sort_lds(lds, lds + kRadixMax, radix_cnt, radix_wsum, tk.n);
-        for (int i = threadIdx.x; i < tk.n; i += blockDim.x)
-            sigma[tk.sig + i] = (int32_t)(S[i] & 0xffffffffu);
-        return;
+    int cnt = nl;
+    for (int j = 0; j < m; ++j) {
+        const int s = slab_count(cnt, nd - j);
+        cnt = (cnt + s - 1) / s;
     }
-    uint64_t *A = (np <= kSortLds) ? lds : scratch + tk.scratch;
-    for (int i = threadIdx.x; i < np; i += blockDim.x) {
-        uint64_t key = ~0ull;
-        if (i < tk.n) {
-            float f;
-            if (tk.mode == 0) {
-                const int r = i / tk.W;
-                const int t = tk.w + (i - r * tk.W);
-                f = y[((int64_t)tk.pair * R + r) * T + t - 1];
-            } else {
-                f = pts[tk.key_off + i];
-            }
-            key = sort_key(f, (uint32_t)i);
-        }
-        A[i] = key;
+    return m + 1 < nd && slab_count(cnt, nd - m) == 1;
+}
+
+// Target-past coordinate m of point i of a task's search space.
+struct CoordSource {
+    const float *y, *pts;
+    int64_t ld;
+    int R, T, tau;
+    __device__ __forceinline__ float at(const SortTask &tk, int i, int m) const
+    {
+        if (tk.mode != 0)
+            return pts[tk.key_off + (int64_t)m * ld + i];
+        const int r = i / tk.W;
+        const int t = tk.w + (i - r * tk.W);
+        return y[((int64_t)tk.pair * R + r) * T + t - 1 - m * tau];
+    }
+};
+
+constexpr int kOrderThreads = 1024;
+constexpr int kOrderWaves = kOrderThreads / kWave;
+constexpr int kOrderEach = kSlabMax / kOrderThreads;   // points per thread at most
+
+// Smallest and largest of the workgroup's values (red: 2 x kOrderWaves words of LDS).
+__device__ __forceinline__ void block_range(uint32_t &lo, uint32_t &hi, uint32_t *red)
+{
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) {
+        lo = min(lo, (uint32_t)__shfl_xor((int)lo, o, 64));
+        hi = max(hi, (uint32_t)__shfl_xor((int)hi, o, 64));
+    }
+    const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
+    if (lane == 0) {
+        red[w] = lo;
+        red[kOrderWaves + w] = hi;
     }
     __syncthreads();
-    if (np <= kSortLds) {
-        bitonic_lds(lds, np, 2, np, 0);
-    } else {
+    lo = red[lane & (kOrderWaves - 1)];
+    hi = red[kOrderWaves + (lane & (kOrderWaves - 1))];
+#pragma unroll
+    for (int o = kOrderWaves / 2; o >= 1; o >>= 1) {
+        lo = min(lo, (uint32_t)__shfl_xor((int)lo, o, 64));
+        hi = max(hi, (uint32_t)__shfl_xor((int)hi, o, 64));
+    }
+    __syncthreads();
+}
+
+// Right shift that fits the range hi - lo into `bits` bits.
+__device__ __forceinline__ int code_shift(uint32_t lo, uint32_t hi, int bits)
+{
+    return max(0, 32 - bits - (hi == lo ? 32 : __builtin_clz(hi - lo)));
+}
+
+// Lanes of the wave that hold the same BITS-bit digit as this one (inactive lanes hold none).
+template <int BITS>
+__device__ __forceinline__ uint64_t match_digit(uint32_t d, bool active)
+{
+    uint64_t m = ballot(active);
+#pragma unroll
+    for (int b = 0; b < BITS; ++b) {
+        const bool one = (d >> b) & 1u;
+        const uint64_t mb = ballot(one);
+        m &= one ? mb : ~mb;
+    }
+    return m;
+}
+
+__device__ __forceinline__ int rank_in(uint64_t m)
+{
+    return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+}
+
+// Exclusive scan of cnt[w][d] over (d, w) in that order, in place, for DIGITS <= kOrderThreads
+// digits and kOrderWaves waves: where each wave's elements of a digit go.  part: kOrderWaves words.
+template <int DIGITS>
+__device__ __forceinline__ void scan_digits(uint32_t *cnt, uint32_t *part)
+{
+    const int t = threadIdx.x, lane = t & (kWave - 1), w = t / kWave;
+    uint32_t c[kOrderWaves], own = 0;
+    if (t < DIGITS)
+#pragma unroll
+        for (int v = 0; v < kOrderWaves; ++v) {
+            c[v] = cnt[v * DIGITS + t];
+            own += c[v];
+        }
+    uint32_t inc = own;
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) {
+        const uint32_t v = (uint32_t)__shfl_up((int)inc, o, 64);
+        if (lane >= o)
+            inc += v;
+    }
+    if (lane == kWave - 1)
+        part[w] = inc;
+    __syncthreads();
+    if (t < DIGITS) {
+        uint32_t base = inc - own;
+        for (int v = 0; v < w; ++v)
+            base += part[v];
+#pragma unroll
+        for (int v = 0; v < kOrderWaves; ++v) {
+            cnt[v * DIGITS + t] = base;
+            base += c[v];
+        }
+    }
+    __syncthreads();
+}
+
+// Ordering, part 1 of 2, for spaces above kSlabMax points: one workgroup cuts the space into
+// order_slabs() slabs of whole blocks along the first target-past coordinate.  The coordinate
+// is coded in 15 bits (its orderable image less the smallest, shifted to fit, so the code keeps
+// at least the sign, the exponent and six bits of the mantissa, and everything where the values
+// span little); the codes' histogram gives the code in which each cut falls.  A stable counting
+// sort by the runs between those codes then puts every point on its side of every cut (points of
+// a cut's own code by index), and leaves the point indices of each slab in index order in the map.
+// The codes live behind the 16-bit map or in the key scratch, where the boxes will be written later.
+constexpr int kCodeBits = 15;
+constexpr int kClasses = 128;          // runs between cuts: 2 (kMaxSlabs - 1) + 1 at most
+
+__global__ void __launch_bounds__(kOrderThreads) split_kernel(CoordSource src, const SortTask *__restrict__ tasks,
+                                                              int32_t *sigma, uint64_t *scratch, int nd)
+{
+    __shared__ uint32_t hist[1 << kCodeBits];             // code counts; then each code's class
+    __shared__ uint32_t cnt[kOrderWaves * kClasses];
+    __shared__ uint32_t part[2 * kOrderWaves];
+    __shared__ int32_t cut_code[kMaxSlabs];
+    const SortTask tk = tasks[blockIdx.x];
+    const int n = tk.n;
+    const int slabs = order_slabs(n, nd);
+    if (slabs <= 1)
+        return;
+    const int t = threadIdx.x, lane = t & (kWave - 1), w = t / kWave;
+    const int nl = (n + kWave - 1) / kWave;
+    int32_t *map = sigma + tk.sig;
+    uint16_t *code = n <= kSortLds ? reinterpret_cast<uint16_t *>(map) + n
+                                   : reinterpret_cast<uint16_t *>(scratch + tk.scratch);
+    for (int i = t; i < (1 << kCodeBits); i += kOrderThreads)
+        hist[i] = 0;
+    for (int i = t; i < kOrderWaves * kClasses; i += kOrderThreads)
+        cnt[i] = 0;
+    uint32_t lo = ~0u, hi = 0;
+    for (int i = t; i < n; i += kOrderThreads) {
+        const uint32_t o = orderable(src.at(tk, i, 0));
+        lo = min(lo, o);
+        hi = max(hi, o);
+    }
+    block_range(lo, hi, part);
+    const int shift = code_shift(lo, hi, kCodeBits);
+    for (int i = t; i < n; i += kOrderThreads) {
+        const uint32_t c = (orderable(src.at(tk, i, 0)) - lo) >> shift;
+        code[i] = (uint16_t)c;
+        atomicAdd(&hist[c], 1u);
+    }
+    __syncthreads();
+    // thread t owns 32 consecutive codes: the code of each cut, then the class of every code
+    constexpr int kOwn = (1 << kCodeBits) / kOrderThreads;
+    uint32_t own = 0;
+    for (int e = 0; e < kOwn; ++e)
+        own += hist[t * kOwn + e];
+    uint32_t inc = own;
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) {
+        const uint32_t v = (uint32_t)__shfl_up((int)inc, o, 64);
+        if (lane >= o)
+            inc += v;
+    }
+    if (lane == kWave - 1)
+        part[w] = inc;
+    __syncthreads();
+    uint32_t before = inc - own;
+    for (int v = 0; v < w; ++v)
+        before += part[v];
+    if (own > 0) {
+        // cuts whose rank lies in [before, before + own)
+        uint32_t cum = before;
+        int e = 0;
+        for (int s = 1; s < slabs; ++s) {
+            const uint32_t rank = (uint32_t)slab_first(nl, slabs, s) * kWave;
+            if (rank < before || rank >= before + own)
+                continue;
+            while (cum + hist[t * kOwn + e] <= rank)
+                cum += hist[t * kOwn + e++];
+            cut_code[s] = t * kOwn + e;
+        }
+    }
+    __syncthreads();
+    {
+        int s = 1, below = 0;                             // distinct cut codes below this thread's codes
+        while (s < slabs && cut_code[s] < t * kOwn) {
+            below += (s == 1 || cut_code[s] != cut_code[s - 1]);
+            ++s;
+        }
+        for (int e = 0; e < kOwn; ++e) {
+            const int c = t * kOwn + e;
+            const bool cut = s < slabs && cut_code[s] == c;
+            hist[c] = (uint32_t)(2 * below + (cut ? 1 : 0));
+            if (cut) {
+                ++below;
+                while (s < slabs && cut_code[s] == c)
+                    ++s;
+            }
+        }
+    }
+    __syncthreads();
+    // stable counting sort by class: wave w takes a contiguous run of points
+    const int run = ((n + kOrderThreads - 1) / kOrderThreads) * kWave;
+    const int i1 = min(n, (w + 1) * run);
+    for (int i = w * run + lane; i < i1; i += kWave)
+        atomicAdd(&cnt[w * kClasses + hist[code[i]]], 1u);
+    __syncthreads();
+    scan_digits<kClasses>(cnt, part);
+    for (int i0 = w * run; i0 < i1; i0 += kWave) {
+        const int i = i0 + lane;
+        const bool ok = i < i1;
+        const uint32_t c = ok ? hist[code[i]] : 0u;
+        const uint64_t m = match_digit<7>(c, ok);
+        if (ok) {
+            const int r = rank_in(m);
+            const uint32_t at = cnt[w * kClasses + c] + (uint32_t)r;
+            if (n <= kSortLds)
+                reinterpret_cast<uint16_t *>(map)[at] = (uint16_t)i;
+            else
+                map[at] = i;
+            __builtin_amdgcn_wave_barrier();
+            if (r == 0)
+                cnt[w * kClasses + c] = at + (uint32_t)__builtin_popcountll(m);
+        }
+        __builtin_amdgcn_wave_barrier();
+    }
+}
+
+// Ordering, part 2 of 2: workgroup (task, slab) orders one slab (a space of up to kSlabMax points
+// whole) so that its blocks of 64 consecutive points are compact in the target past: sorted by a
+// coordinate and cut into slabs of whole blocks, each slab sorted by the next coordinate and cut,
+// and so on; the last coordinate orders the points of the last slabs.  Level m sorts by (slab,
+// coordinate m) with stable radix passes of 8 bits in LDS: 16 bits of the coordinate, coded as in
+// split_kernel, and the slab.  Points of equal keys keep the order of the level before, so the
+// order is a function of the data alone.  A pass gives each wave a contiguous run of the points;
+// lanes of equal digits find their ranks by ballots, the waves' digit counts are scanned once.
+// Any order is correct (the boxes are taken from the points); this one is the same on every path.
+template <bool LIST>                       // slabs of larger spaces among the tasks: their points listed in LDS
+__global__ void __launch_bounds__(kOrderThreads) order_kernel(CoordSource src, const SortTask *__restrict__ tasks,
+                                                              int32_t *sigma, int nd)
+{
+    __shared__ struct {
+        uint32_t key[kSlabMax];
+        uint32_t cnt[kOrderWaves * 256];
+        uint32_t part[2 * kOrderWaves];
+        uint16_t loc[kSlabMax];
+        uint8_t slab[kSlabMax / kWave];
+    } sh;
+    __shared__ uint32_t list[LIST ? kSlabMax : 1];
+    const SortTask tk = tasks[blockIdx.x];
+    const int slabs = order_slabs(tk.n, nd);
+    if ((int)blockIdx.y >= slabs)          // also: spaces that order_big_kernel orders (no slabs)
+        return;
+    const int t = threadIdx.x, lane = t & (kWave - 1), w = t / kWave;
+    const int nl_all = (tk.n + kWave - 1) / kWave;
+    const int first = slab_first(nl_all, slabs, (int)blockIdx.y);
+    const int base = first * kWave;
+    const int n = min(tk.n, slab_first(nl_all, slabs, (int)blockIdx.y + 1) * kWave) - base;
+    const int nl = (n + kWave - 1) / kWave;
+    int32_t *map = sigma + tk.sig;
+    uint16_t *map16 = reinterpret_cast<uint16_t *>(map);
+    const int level0 = slabs > 1 && nd > 1 ? 1 : 0;       // the slabs were cut along coordinate 0
+    const int each = (n + kOrderThreads - 1) / kOrderThreads;
+    if (nl_all == 1) {                                    // one block: any order will do
+        if (t < n)
+            map16[t] = (uint16_t)t;
+        return;
+    }
+    const bool listed = LIST && slabs > 1;
+    if (listed)
+        for (int i = t; i < n; i += kOrderThreads)
+            list[i] = tk.n <= kSortLds ? (uint32_t)map16[base + i] : (uint32_t)map[base + i];
+    for (int i = t; i < n; i += kOrderThreads)
+        sh.loc[i] = (uint16_t)i;
+    __syncthreads();
+    for (int m = level0; m < nd; ++m) {
+        if (idle_level(nl, nd - level0, m - level0))
+            continue;
+        // keys of this level: wave w holds positions [w each 64, (w + 1) each 64)
+        uint32_t key[kOrderEach];
+        uint16_t loc[kOrderEach];
+        uint32_t lo = ~0u, hi = 0;
+#pragma unroll
+        for (int e = 0; e < kOrderEach; ++e) {
+            const int p = (w * each + e) * kWave + lane;
+            if (e < each && p < n) {
+                loc[e] = sh.loc[p];
+                key[e] = orderable(src.at(tk, listed ? (int)list[loc[e]] : (int)loc[e], m));
+                lo = min(lo, key[e]);
+                hi = max(hi, key[e]);
+            }
+        }
+        if (m > level0 && t < nl)
+            sh.slab[t] = (uint8_t)slab_start(t, nl, nd - level0, m - level0);
+        block_range(lo, hi, sh.part);
+        const int shift = code_shift(lo, hi, 16);
+#pragma unroll
+        for (int e = 0; e < kOrderEach; ++e) {
+            const int p = (w * each + e) * kWave + lane;
+            if (e < each && p < n)
+                key[e] = (key[e] - lo) >> shift | (m > level0 ? (uint32_t)sh.slab[p / kWave] << 16 : 0u);
+        }
+        const int bits = m > level0 ? 24 : 16;
+        for (int bit = 0; bit < bits; bit += 8) {
+            for (int i = t; i < kOrderWaves * 256; i += kOrderThreads)
+                sh.cnt[i] = 0;
+            __syncthreads();
+            uint32_t at[kOrderEach];
+#pragma unroll
+            for (int e = 0; e < kOrderEach; ++e) {
+                if (e >= each)
+                    break;
+                const bool ok = (w * each + e) * kWave + lane < n;
+                const uint32_t d = (key[e] >> bit) & 255u;
+                const uint64_t g = match_digit<8>(d, ok);
+                if (ok) {
+                    const int r = rank_in(g);
+                    at[e] = sh.cnt[w * 256 + d] + (uint32_t)r;
+                    __builtin_amdgcn_wave_barrier();
+                    if (r == 0)
+                        sh.cnt[w * 256 + d] = at[e] + (uint32_t)__builtin_popcountll(g);
+                }
+                __builtin_amdgcn_wave_barrier();
+            }
+            __syncthreads();
+            scan_digits<256>(sh.cnt, sh.part);
+#pragma unroll
+            for (int e = 0; e < kOrderEach; ++e)
+                if (e < each && (w * each + e) * kWave + lane < n) {
+                    const uint32_t p = at[e] + sh.cnt[w * 256 + ((key[e] >> bit) & 255u)];
+                    sh.key[p] = key[e];
+                    sh.loc[p] = loc[e];
+                }
+            __syncthreads();
+            if (bit + 8 < bits)
+#pragma unroll
+                for (int e = 0; e < kOrderEach; ++e) {
+                    const int p = (w * each + e) * kWave + lane;
+                    if (e < each && p < n) {
+                        key[e] = sh.key[p];
+                        loc[e] = sh.loc[p];
+                    }
+                }
+        }
+        __syncthreads();
+    }
+    for (int i = t; i < n; i += kOrderThreads) {
+        const uint32_t o = listed ? list[sh.loc[i]] : (uint32_t)sh.loc[i];
+        if (tk.n <= kSortLds)
+            map16[base + i] = (uint16_t)o;
+        else
+            map[base + i] = (int32_t)o;
+    }
+}
+
+// Spaces above kMaxSlabs x kSlabMax points: one workgroup, a bitonic network per level over
+// npad = 2^k keys (slab, coordinate, index; padding keys sort last) in global scratch.  Every
+// stage's passes with stride below kSortLds only pair elements of the same kSortLds-aligned
+// tile, so each tile is loaded into LDS once per stage for those passes and only the wider
+// strides touch global memory.
+__global__ void __launch_bounds__(kOrderThreads) order_big_kernel(CoordSource src, const SortTask *__restrict__ tasks,
+                                                                  int32_t *sigma, uint64_t *scratch, int nd)
+{
+    __shared__ uint64_t lds[kSortLds];
+    const SortTask tk = tasks[blockIdx.x];
+    const int n = tk.n, np = tk.npad;
+    if (order_slabs(n, nd) > 0)
+        return;
+    const int nl = (n + kWave - 1) / kWave;
+    int32_t *map = sigma + tk.sig;
+    uint64_t *A = scratch + tk.scratch;
+    const int ib = 31 - __builtin_clz(np);                // index bits; slab bits above the coordinate's
+    const int sb = 32 - __builtin_clz(nl);
+    const int drop = max(0, ib + sb + 32 - 64);           // low coordinate bits without room in the key
+    const uint64_t imask = ((uint64_t)1 << ib) - 1;
+    for (int m = 0; m < nd; ++m) {
+        for (int i = threadIdx.x; i < np; i += blockDim.x) {
+            uint64_t key = ~0ull;
+            if (i < n) {
+                const uint64_t o = m == 0 ? (uint64_t)i : (A[i] & imask);
+                key = (uint64_t)slab_start(i / kWave, nl, nd, m) << (ib + 32 - drop) |
+                      (uint64_t)(orderable(src.at(tk, (int)o, m)) >> drop) << ib | o;
+            }
+            A[i] = key;
+        }
+        __syncthreads();
         // stages that fit a tile: sort every tile in LDS
         for (int t0 = 0; t0 < np; t0 += kSortLds) {
             for (int i = threadIdx.x; i < kSortLds; i += blockDim.x)
@@ -1693,20 +938,40 @@ __global__ void __launch_bounds__(1024) sort_kernel(const float *__restrict__ y,
             }
         }
     }
-    for (int i = threadIdx.x; i < tk.n; i += blockDim.x)
-        sigma[tk.sig + i] = (int32_t)(A[i] & 0xffffffffu);
+    for (int i = threadIdx.x; i < n; i += blockDim.x)
+        map[i] = (int32_t)(A[i] & imask);
 }
 
 __global__ void gather_kernel(const float *__restrict__ src, const GatherTask *__restrict__ tasks,
-                              const int32_t *__restrict__ sigma, float *__restrict__ dst, int D)
+                              int32_t *sigma, uint64_t *scratch, float *__restrict__ dst, int D, int d_y)
 {
     const GatherTask tk = tasks[blockIdx.x];
-    for (int q = threadIdx.x; q < tk.n; q += blockDim.x) {
-        int o = sigma[tk.sig + q];
-        if (o < 0 || o >= tk.n)          // maps from sort_kernel are permutations; keep reads in bounds regardless
+    const int n = tk.n;
+    const int lane = threadIdx.x & (kWave - 1);
+    const int nb = (n + kWave - 1) / kWave;
+    float *box = nullptr;
+    if (nb > 1)
+        box = n <= kSortLds ? reinterpret_cast<float *>(sigma + tk.sig + box_words_behind_map(n))
+                            : reinterpret_cast<float *>(scratch + (int64_t)tk.box * kBoxScratchUnit);
+    for (int qb = blockIdx.y * blockDim.x + (threadIdx.x - lane); qb < n; qb += blockDim.x * gridDim.y) {
+        const bool ok = qb + lane < n;
+        const int q = ok ? qb + lane : n - 1;
+        int o = order_at(sigma + tk.sig, n, q);
+        if (o < 0 || o >= n)          // maps from order_kernel are permutations; keep reads in bounds regardless
             o = q;
-        for (int m = 0; m < D; ++m)
-            dst[tk.dst + (int64_t)m * tk.n + q] = src[tk.src + (int64_t)m * tk.ld + o];
+        for (int m = 0; m < D; ++m) {
+            const float v = src[tk.src + (int64_t)m * tk.ld + o];
+            if (ok)
+                dst[tk.dst + (int64_t)m * n + q] = v;
+            if (box != nullptr && m >= 1 && m <= d_y) {
+                float lo, hi;
+                wave_box(v, &lo, &hi);
+                if (lane == 0) {
+                    box[(int64_t)(2 * (m - 1)) * nb + qb / kWave] = lo;
+                    box[(int64_t)(2 * (m - 1) + 1) * nb + qb / kWave] = hi;
+                }
+            }
+        }
     }
 }
 
@@ -1986,23 +1251,11 @@ __global__ void argmax_u_kernel(const double *__restrict__ results, int n_groups
 
 typedef void (*search_fn)(SearchArgs);
 
-template <int DY, int DX, int SLOTS>
-struct Table {
-    static search_fn get(bool generic, bool sorted)
-    {
-        if (sorted)
-            return generic ? search_kernel<DY, DX, kMaxK + 1, true, SLOTS, true>
-                           : search_kernel<DY, DX, 5, false, SLOTS, true>;
-        return generic ? search_kernel<DY, DX, kMaxK + 1, true, SLOTS, false>
-                       : search_kernel<DY, DX, 5, false, SLOTS, false>;
-    }
-};
-
-template <int SLOTS>
-search_fn pick(int d_y, int d_x, bool generic, bool sorted)
+search_fn pick_unordered(int d_y, int d_x, int k)
 {
-#define TE_CASE(A, B) \
-    if (d_y == A && d_x == B) return Table<A, B, SLOTS>::get(generic, sorted);
+#define TE_CASE(A, B)             \
+    if (d_y == A && d_x == B)     \
+        return k != 4 ? search_unordered_kernel<A, B, kMaxK + 1, true> : search_unordered_kernel<A, B, 5, false>;
     TE_CASE(1, 1) TE_CASE(1, 2) TE_CASE(1, 3) TE_CASE(1, 4)
     TE_CASE(2, 1) TE_CASE(2, 2) TE_CASE(2, 3) TE_CASE(2, 4)
     TE_CASE(3, 1) TE_CASE(3, 2) TE_CASE(3, 3) TE_CASE(3, 4)
@@ -2011,47 +1264,12 @@ search_fn pick(int d_y, int d_x, bool generic, bool sorted)
     return nullptr;
 }
 
-search_fn pick_any(int d_y, int d_x, int k, int slots, bool sorted)
+int occupancy(search_fn f, int waves_per_wg, size_t lds)
 {
-    const bool generic = (k != 4);
-    if (k < 1 || k > kMaxK)
-        return nullptr;
-    if (slots == 4)
-        return pick<4>(d_y, d_x, generic, sorted);
-    if (slots == 8)
-        return pick<8>(d_y, d_x, generic, sorted);
-    if (slots == 16)
-        return pick<16>(d_y, d_x, generic, sorted);
-    return nullptr;
-}
-
-// Chunk-set search: V = set_variants(d_y, d_x) chunks per item, k = 4, sorted chunks; two or
-// four candidate slots per lane in the counting pass (the tuned slot count 4 -> 2,
-// 8 or 16 -> 4).
-template <int SLOTS>
-search_fn pick_sets_slots(int d_y, int d_x)
-{
-#define TE_CASE(A, B) \
-    if (d_y == A && d_x == B) return sets_fn<A, B, SLOTS>();
-    TE_CASE(1, 1) TE_CASE(1, 2) TE_CASE(1, 3) TE_CASE(1, 4)
-    TE_CASE(2, 1) TE_CASE(2, 2) TE_CASE(2, 3) TE_CASE(2, 4)
-    TE_CASE(3, 1) TE_CASE(3, 2) TE_CASE(3, 3) TE_CASE(3, 4)
-    TE_CASE(4, 1) TE_CASE(4, 2) TE_CASE(4, 3) TE_CASE(4, 4)
-#undef TE_CASE
-    return nullptr;
-}
-
-search_fn pick_sets(int d_y, int d_x, int slots)
-{
-    return slots <= 4 ? pick_sets_slots<2>(d_y, d_x) : pick_sets_slots<4>(d_y, d_x);
-}
-
-// LDS bytes of the chunk-set search per workgroup (its rows are dynamic shared memory).
-size_t sets_lds_bytes(int d_y, int d_x, int waves_per_wg)
-{
-    const int v = set_variants(d_y, d_x);
-    const int nr = 1 + d_y + v * d_x + v;
-    return (size_t)waves_per_wg * kWave * (size_t)((nr + 3) & ~3) * sizeof(float);
+    int blocks = 0;
+    if (!f || hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, f, kWave * waves_per_wg, lds) != hipSuccess)
+        return 0;
+    return blocks;
 }
 
 }  // namespace
@@ -2069,32 +1287,24 @@ unsigned long long *work_counters()
     return static_cast<unsigned long long *>(p);
 }
 
-bool search_supported(int d_y, int d_x, int k, int slots) { return pick_any(d_y, d_x, k, slots, false) != nullptr; }
+bool search_supported(int d_y, int d_x, int k, int slots)
+{
+    return pick_ordered(d_y, d_x, k, slots, false, 1).fn != nullptr;
+}
 
 // Resident workgroups per compute unit for the chosen search variant (0 if unknown).
 int search_occupancy(int d_y, int d_x, int k, int slots, int waves_per_wg)
 {
-    search_fn f = pick_any(d_y, d_x, k, slots, true);
-    if (!f)
-        return 0;
-    int blocks = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, f, kWave * waves_per_wg, 0) != hipSuccess)
-        return 0;
-    return blocks;
+    const ordered_search s = pick_ordered(d_y, d_x, k, slots, false, waves_per_wg);
+    return occupancy(s.fn, waves_per_wg, s.lds);
 }
 
-bool search_sets_supported(int d_y, int d_x, int k) { return k == 4 && pick_sets(d_y, d_x, 4) != nullptr; }
+bool search_sets_supported(int d_y, int d_x, int k) { return pick_ordered(d_y, d_x, k, 4, true, 1).fn != nullptr; }
 
 int search_sets_occupancy(int d_y, int d_x, int slots, int waves_per_wg)
 {
-    search_fn f = pick_sets(d_y, d_x, slots);
-    if (!f)
-        return 0;
-    int blocks = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, f, kWave * waves_per_wg,
-                                                     sets_lds_bytes(d_y, d_x, waves_per_wg)) != hipSuccess)
-        return 0;
-    return blocks;
+    const ordered_search s = pick_ordered(d_y, d_x, 4, slots, true, waves_per_wg);
+    return occupancy(s.fn, waves_per_wg, s.lds);
 }
 
 hipError_t launch_search(const SearchArgs &a, int d_y, int d_x, const SearchConfig &cfg, int grid_waves,
@@ -2102,17 +1312,14 @@ hipError_t launch_search(const SearchArgs &a, int d_y, int d_x, const SearchConf
 {
     const int wpg = cfg.waves_per_wg;
     const int blocks = (grid_waves + wpg - 1) / wpg;
-    if (a.set_first != nullptr) {
-        search_fn f = (a.k == 4 && a.sorted) ? pick_sets(d_y, d_x, cfg.slots) : nullptr;
-        if (!f)
-            return hipErrorInvalidValue;
-        hipLaunchKernelGGL(f, dim3(blocks), dim3(kWave * wpg), sets_lds_bytes(d_y, d_x, wpg), st, a);
-        return hipGetLastError();
-    }
-    search_fn f = pick_any(d_y, d_x, a.k, cfg.slots, a.sorted != 0);
-    if (!f)
+    ordered_search s{nullptr, 0};
+    if (a.sorted)
+        s = pick_ordered(d_y, d_x, a.k, cfg.slots, a.set_first != nullptr, wpg);
+    else if (a.set_first == nullptr && a.k >= 1 && a.k <= kMaxK)
+        s.fn = pick_unordered(d_y, d_x, a.k);
+    if (!s.fn)
         return hipErrorInvalidValue;
-    hipLaunchKernelGGL(f, dim3(blocks), dim3(kWave * wpg), 0, st, a);
+    hipLaunchKernelGGL(s.fn, dim3(blocks), dim3(kWave * wpg), s.lds, st, a);
     return hipGetLastError();
 }
 
@@ -2132,7 +1339,7 @@ hipError_t launch_fill_i32(int32_t *p, int32_t v, int64_t n, hipStream_t st)
     return hipGetLastError();
 }
 
-hipError_t launch_embed(const float *x, const float *y, const int32_t *perms, const int32_t *sigma,
+hipError_t launch_embed(const float *x, const float *y, const int32_t *perms, int32_t *sigma, uint64_t *scratch,
                         const int32_t *u_dev, const EmbedTask *tasks, int n_tasks, int max_n, float *base, int R,
                         int T, int d_y, int d_x, int tau, int u, int cond, int32_t *err, hipStream_t st)
 {
@@ -2140,7 +1347,7 @@ hipError_t launch_embed(const float *x, const float *y, const int32_t *perms, co
         return hipSuccess;
     // a few hundred to a few thousand points per workgroup, so small batches still fill the GPU
     const int parts = std::max(1, std::min(1024, (max_n + 1023) / 1024));
-    hipLaunchKernelGGL(embed_kernel, dim3(n_tasks, parts), dim3(256), 0, st, x, y, perms, sigma, u_dev, tasks, base,
+    hipLaunchKernelGGL(embed_kernel, dim3(n_tasks, parts), dim3(256), 0, st, x, y, perms, sigma, scratch, u_dev, tasks, base,
                        R, T, d_y, d_x, tau, u, cond, err);
     return hipGetLastError();
 }
@@ -2155,21 +1362,34 @@ hipError_t launch_argmax_u(const double *results, int n_groups, int n_u, const i
     return hipGetLastError();
 }
 
-hipError_t launch_sort(const float *y, const float *pts, const SortTask *tasks, int n_tasks, int32_t *sigma,
-                       uint64_t *scratch, int R, int T, hipStream_t st)
+hipError_t launch_sort(const float *y, const float *pts, int64_t ld, const SortTask *tasks, int n_tasks, int max_n,
+                       int32_t *sigma, uint64_t *scratch, int R, int T, int d_y, int tau, hipStream_t st)
 {
     if (n_tasks <= 0)
         return hipSuccess;
-    hipLaunchKernelGGL(sort_kernel, dim3(n_tasks), dim3(1024), 0, st, y, pts, tasks, sigma, scratch, R, T);
+    const CoordSource src{y, pts, ld, R, T, tau};
+    if (max_n <= kSlabMax) {
+        hipLaunchKernelGGL(order_kernel<false>, dim3(n_tasks), dim3(kOrderThreads), 0, st, src, tasks, sigma, d_y);
+        return hipGetLastError();
+    }
+    // the most slabs of any task: order_slabs grows with n up to kMaxSlabs; above that there are none
+    const int slabs = order_slabs(max_n, d_y);
+    hipLaunchKernelGGL(split_kernel, dim3(n_tasks), dim3(kOrderThreads), 0, st, src, tasks, sigma, scratch, d_y);
+    if (slabs == 0)
+        hipLaunchKernelGGL(order_big_kernel, dim3(n_tasks), dim3(kOrderThreads), 0, st, src, tasks, sigma, scratch,
+                           d_y);
+    hipLaunchKernelGGL(order_kernel<true>, dim3(n_tasks, slabs == 0 ? kMaxSlabs : slabs), dim3(kOrderThreads), 0, st,
+                       src, tasks, sigma, d_y);
     return hipGetLastError();
 }
 
-hipError_t launch_gather(const float *src, const GatherTask *tasks, int n_tasks, const int32_t *sigma, float *dst,
-                         int D, hipStream_t st)
+hipError_t launch_gather(const float *src, const GatherTask *tasks, int n_tasks, int max_n, int32_t *sigma,
+                         uint64_t *scratch, float *dst, int D, int d_y, hipStream_t st)
 {
     if (n_tasks <= 0)
         return hipSuccess;
-    hipLaunchKernelGGL(gather_kernel, dim3(n_tasks), dim3(256), 0, st, src, tasks, sigma, dst, D);
+    const int parts = std::max(1, std::min(1024, (max_n + 1023) / 1024));
+    hipLaunchKernelGGL(gather_kernel, dim3(n_tasks, parts), dim3(256), 0, st, src, tasks, sigma, scratch, dst, D, d_y);
     return hipGetLastError();
 }
 

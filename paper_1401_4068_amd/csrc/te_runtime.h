@@ -33,6 +33,8 @@ size_t align_up(size_t v, size_t a);
 int size_bucket(int64_t n);
 bool sorting_enabled();
 int sort_npad(int n);
+int64_t box_offset(int64_t n, int64_t at, size_t off_sigma, size_t off_scratch, size_t off_base);
+int32_t embed_box(int64_t n, int64_t scratch);
 void queue_bounds(const std::vector<ChunkDesc> &pieces, int64_t n_items, std::vector<int32_t> *part_start);
 te_status knn_counts_run(const float *pts, int64_t dim_stride, const int64_t *offsets, int32_t n_chunks, int32_t d_y,
                          int32_t d_x, int32_t k, char *ws, size_t ws_bytes, hipStream_t st, float *eps,

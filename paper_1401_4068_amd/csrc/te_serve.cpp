@@ -411,6 +411,8 @@ bool Server::admit_one(Job *j)
     for (size_t c = 0; c < b.chunks.size(); ++c) {
         cd[c].tp += fbase;
         cd[c].s += fbase;
+        if (j->plan->impl.sorted)
+            cd[c].geo += fbase;
         cd[c].pbase += pbase;
     }
     j->stage = inject ? nullptr : pool.take(std::max(b.tables_bytes, sizeof(double) * (b.n_results + b.n_groups) + 64));
@@ -436,12 +438,13 @@ bool Server::admit_one(Job *j)
                          P.p.seed, ctr + 1, setup_stream);
     int32_t *sigma = reinterpret_cast<int32_t *>(bat + b.off_sigma);
     if (e == hipSuccess)
-        e = launch_sort(reinterpret_cast<const float *>(reg + j->off_y), nullptr,
-                        reinterpret_cast<const SortTask *>(bat + b.off_sorts), (int)b.sorts.size(), sigma,
-                        reinterpret_cast<uint64_t *>(bat + b.off_scratch), P.p.n_trials, P.p.n_samples, setup_stream);
+        e = launch_sort(reinterpret_cast<const float *>(reg + j->off_y), nullptr, 0,
+                        reinterpret_cast<const SortTask *>(bat + b.off_sorts), (int)b.sorts.size(),
+                        embed_max_n(b), sigma, reinterpret_cast<uint64_t *>(bat + b.off_scratch), P.p.n_trials, P.p.n_samples, P.p.d_y, P.p.tau,
+                        setup_stream);
     if (e == hipSuccess)
         e = launch_embed(reinterpret_cast<const float *>(reg + j->off_x), reinterpret_cast<const float *>(reg + j->off_y),
-                         perm, sigma, nullptr, reinterpret_cast<const EmbedTask *>(bat + b.off_tasks), (int)b.tasks.size(),
+                         perm, sigma, reinterpret_cast<uint64_t *>(bat + b.off_scratch), nullptr, reinterpret_cast<const EmbedTask *>(bat + b.off_tasks), (int)b.tasks.size(),
                          embed_max_n(b), reinterpret_cast<float *>(bat + b.off_coords), P.p.n_trials, P.p.n_samples, P.p.d_y, P.p.d_x,
                          P.p.tau, P.p.u, P.p.cond_source, ctr + 1, setup_stream);
     if (e == hipSuccess)
@@ -516,6 +519,8 @@ bool Server::issue_step(int ci)
                 ChunkDesc d = b.chunks[c0 + v];
                 d.tp += fbase;
                 d.s += fbase;
+                if (kc.sorted)
+                    d.geo += fbase;
                 d.pbase += pb;
                 d.item0 = (int32_t)items;
                 d.block0 = j->next_block[u];

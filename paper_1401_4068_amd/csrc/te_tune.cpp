@@ -142,11 +142,10 @@ te_status te_autotune(int32_t d_y, int32_t d_x, int32_t k, int32_t n_points, int
         if (sorted) {
             d.tp = (int64_t)c * n_points * D;
             d.s = d.tp + (int64_t)(1 + d_y) * n_points;
-            d.ld = n_points;
         } else {
             d.tp = (int64_t)c * n_points;
             d.s = (int64_t)c * n_points + (int64_t)(1 + d_y) * total;
-            d.ld = total;
+            d.geo = total;
         }
         d.out = -1;
         d.perm = -1;
@@ -165,12 +164,15 @@ te_status te_autotune(int32_t d_y, int32_t d_x, int32_t k, int32_t n_points, int
         so.mode = 1;
         so.n = n_points;
         sorts[c] = so;
+        if (sorted)
+            cd[c].geo = box_offset(n_points, so.scratch >= 0 ? so.scratch : so.sig, off_sigma, off_scratch, off_pts);
         GatherTask g{};
         g.src = (int64_t)c * n_points;
         g.ld = total;
         g.dst = (int64_t)c * n_points * D;
         g.sig = (int64_t)c * n_points;
         g.n = n_points;
+        g.box = so.scratch >= 0 ? (int32_t)(so.scratch / kBoxScratchUnit) : 0;
         gathers[c] = g;
     }
     hipError_t e = hipMemcpy(ws + off_chunks, cd.data(), sizeof(ChunkDesc) * n_chunks, hipMemcpyHostToDevice);
@@ -184,13 +186,13 @@ te_status te_autotune(int32_t d_y, int32_t d_x, int32_t k, int32_t n_points, int
     if (e == hipSuccess)
         e = launch_fill_uniform(raw, total * D, 0x7e5eed, st);
     if (e == hipSuccess && sorted)
-        e = launch_sort(nullptr, raw, reinterpret_cast<const SortTask *>(ws + off_sorts), n_chunks,
-                        reinterpret_cast<int32_t *>(ws + off_sigma), reinterpret_cast<uint64_t *>(ws + off_scratch), 0,
-                        0, st);
+        e = launch_sort(nullptr, raw, total, reinterpret_cast<const SortTask *>(ws + off_sorts), n_chunks,
+                        n_points, reinterpret_cast<int32_t *>(ws + off_sigma), reinterpret_cast<uint64_t *>(ws + off_scratch), 0,
+                        0, d_y, 0, st);
     if (e == hipSuccess && sorted)
-        e = launch_gather(raw, reinterpret_cast<const GatherTask *>(ws + off_gathers), n_chunks,
-                          reinterpret_cast<const int32_t *>(ws + off_sigma), reinterpret_cast<float *>(ws + off_pts), D,
-                          st);
+        e = launch_gather(raw, reinterpret_cast<const GatherTask *>(ws + off_gathers), n_chunks, n_points,
+                          reinterpret_cast<int32_t *>(ws + off_sigma), reinterpret_cast<uint64_t *>(ws + off_scratch),
+                          reinterpret_cast<float *>(ws + off_pts), D, d_y, st);
     if (e == hipSuccess)
         e = hipStreamSynchronize(st);
     if (e != hipSuccess)
@@ -210,7 +212,7 @@ te_status te_autotune(int32_t d_y, int32_t d_x, int32_t k, int32_t n_points, int
     hipEventCreate(&e1);
     SearchConfig best{};
     double best_t = 1e30;
-    const int slot_set[] = {4, 8, 16};
+    const int slot_set[] = {4, 8};           // 16 runs as 8
     const int wpg_set[] = {1, 2, 4};
     for (int sl : slot_set)
         for (int wpg : wpg_set) {
@@ -327,12 +329,10 @@ te_status te_plan_autotune(te_plan plan, const float *x, const float *y, const i
     SearchConfig best = saved;
     double best_t = 1e30;
     hipError_t e = hipSuccess;
-    const int slot_set[] = {4, 8, 16};
+    const int slot_set[] = {4, 8};           // 16 runs as 8
     const int wpg_set[] = {1, 2, 4};
     for (int sl : slot_set)
         for (int wpg : wpg_set) {
-            if (b.use_sets && sl == 16)                  // the chunk-set search runs 16 slots as 8
-                continue;
             const int occ = b.use_sets ? search_sets_occupancy(P.dy_eff(), P.p.d_x, sl, wpg)
                                        : search_occupancy(P.dy_eff(), P.p.d_x, P.p.k, sl, wpg);
             if (occ < 1)
