@@ -82,11 +82,13 @@ __device__ __attribute__((noinline)) double psi_of_count(int n)
     return log(x) - 0.5 * r - series + shift;
 }
 
-// Fixed-order butterfly sum over the 64 lanes (same order on every call).
+// Fixed-order butterfly sum over the 64 lanes (same order on every call), neighbouring lanes
+// first: LANES < 64 gives every aligned group of LANES lanes the sum that is its part of the whole.
+template <int LANES = kWave>
 __device__ __forceinline__ double wave_sum(double v)
 {
 #pragma unroll
-    for (int o = 32; o >= 1; o >>= 1)
+    for (int o = 1; o < LANES; o <<= 1)
         v += __shfl_xor(v, o, 64);
     return v;
 }

@@ -1313,6 +1313,14 @@ hipError_t launch_search(const SearchArgs &a, int d_y, int d_x, const SearchConf
     const int wpg = cfg.waves_per_wg;
     const int blocks = (grid_waves + wpg - 1) / wpg;
     ordered_search s{nullptr, 0};
+    const int w = a.sorted ? waves_to_a_block(a.n_items, a.set_first != nullptr, a.k) : 0;
+    if (w > 0) {
+        s = pick_shared(d_y, d_x, a.k, a.set_first != nullptr, w);
+        if (!s.fn)
+            return hipErrorInvalidValue;
+        hipLaunchKernelGGL(s.fn, dim3(a.n_items), dim3(kWave * w), s.lds, st, a);
+        return hipGetLastError();
+    }
     if (a.sorted)
         s = pick_ordered(d_y, d_x, a.k, cfg.slots, a.set_first != nullptr, wpg);
     else if (a.set_first == nullptr && a.k >= 1 && a.k <= kMaxK)

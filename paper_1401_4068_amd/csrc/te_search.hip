@@ -20,8 +20,10 @@
 // Radii, counts and per-item sums do not depend on V: the same float operations
 // decide every comparison, and a block's terms are summed in the same lanes.
 //
-// The kernel is persistent: every wavefront pulls work items (one set of chunks,
-// one block of 64 references) from the queue of its XCD until all queues are empty.
+// A work item is one set of chunks and one block of 64 references.  Large launches are
+// persistent: every wavefront pulls items from the queue of its XCD until all queues are
+// empty.  Small ones give every block a workgroup of W waves, 64 / W references to each
+// (waves_to_a_block).
 
 #include <hip/hip_runtime.h>
 #include <math.h>
@@ -39,13 +41,12 @@ namespace {
 // lane = reference (its insertions run in all lanes at once); below that with
 // lane = candidate against the references that reach it only.
 constexpr int kDense = 44;
-
 // Work item -> chunk run: a set is a run of consecutive chunk descriptors
 // [set_first[c], set_first[c+1]) (single chunks without set_first); its first
 // descriptor supplies tp, box, n, item0 and block0, each descriptor its own s and
 // pbase.  Sets with fewer than V chunks repeat their last chunk in the unused
 // variant slots and do not store those slots' sums.
-template <int DY, int DX, int V, int KP1, bool GENERIC, int SLOTS, bool OUT>
+template <int DY, int DX, int V, int KP1, bool GENERIC, int SLOTS, bool OUT, int W>
 __device__ __forceinline__ void block_search(const SearchArgs &a)
 {
     constexpr int DT = 1 + DY;                 // shared coordinates: y_t' and the target past
@@ -55,8 +56,10 @@ __device__ __forceinline__ void block_search(const SearchArgs &a)
     constexpr int MO = DT > DX ? DT : DX;      // coordinate offsets shared by the target and source blocks
     constexpr int G = (V == 1 && D <= 7) ? 8 : 4;   // candidates per scalar-load group
     extern __shared__ __attribute__((aligned(16))) float rows[];   // waves per workgroup x 64 x RW floats
+    __shared__ double wsum[V][W > 0 ? W : 1];
     const int lane = threadIdx.x & (kWave - 1);
     const int k = GENERIC ? a.k : KP1 - 1;
+    constexpr int RPW = W > 0 ? kWave / W : kWave;   // references per wave
     float *prow = rows + (threadIdx.x / kWave) * (kWave * RW);
 
     const int nq = a.n_parts > 1 ? a.n_parts : 1;
@@ -66,11 +69,13 @@ __device__ __forceinline__ void block_search(const SearchArgs &a)
     unsigned long long work1 = 0, work2 = 0, shared1 = 0, shared2 = 0;
     for (;;) {
         // ---- claim the next work item (wave-uniform)
-        int q = 0;
-        if (lane == 0)
-            q = atomicAdd(a.counter + qp, 1);
-        q = __builtin_amdgcn_readlane(q, 0);
-        if (nq > 1) {
+        int q = (int)blockIdx.x;
+        if (W == 0) {
+            if (lane == 0)
+                q = atomicAdd(a.counter + qp, 1);
+            q = __builtin_amdgcn_readlane(q, 0);
+        }
+        if (W == 0 && nq > 1) {
             q += uload_i(a.part_start + qp);
             if (q >= uload_i(a.part_start + qp + 1)) {
                 if (++drained >= nq)
@@ -116,12 +121,13 @@ __device__ __forceinline__ void block_search(const SearchArgs &a)
         auto row = [&](const float *p, int m) { return V > 1 ? p : p + (int64_t)m * n; };
         const int blk = q - item0 + block0;
         const int nb = (n + kWave - 1) / kWave;
-        const int r0 = blk * kWave;
+        const int r0 = blk * kWave + (W > 0 ? (int)(threadIdx.x / kWave) * RPW : 0);
 
         // ---- pass 1
-        const int i = r0 + lane;
-        const bool valid = i < n;
-        const int ii = valid ? i : n - 1;
+        // (with W waves to a block, every RPW lanes hold the wave's references again, the first ones in use)
+        const int i = r0 + (lane & (RPW - 1));
+        const bool valid = i < n && lane < RPW;
+        const int ii = min(i, n - 1);
         float rt[DT];
         float rs[V][DX];
 #pragma unroll
@@ -244,10 +250,56 @@ __device__ __forceinline__ void block_search(const SearchArgs &a)
 
         // the block's own points first (with a ragged last block, the block before it too, so
         // that every reference starts with a radius)
-        const int ob0 = (blk > 0 && n - r0 < kWave) ? blk - 1 : blk;
-        const int e0 = min(n, r0 + kWave);
-        const int nref = e0 - r0;
-        scan(ob0 * kWave, e0);
+        const int ob0 = (blk > 0 && n - blk * kWave < kWave) ? blk - 1 : blk;
+        const int e0 = min(n, (blk + 1) * kWave);
+        const int nref = max(0, min(RPW, n - r0));
+        if constexpr (W > 0) {
+            // each group of RPW lanes takes every W-th candidate; the groups' lists are merged
+            constexpr int U = 4;                           // candidates in flight per lane
+            for (int j0 = ob0 * kWave; j0 < e0; j0 += U * W) {
+                float dj[U][V];
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int j = j0 + u * W + lane / RPW;
+                    const uint32_t j4 = (uint32_t)min(j, e0 - 1) * 4u;
+                    float dtp = absdiff(rt[0], vload_at(row(tb, 0), moff[0] + j4));
+#pragma unroll
+                    for (int m = 1; m < DT; ++m)
+                        dtp = fmaxf(dtp, absdiff(rt[m], vload_at(row(tb, m), moff[m] + j4)));
+#pragma unroll
+                    for (int v = 0; v < V; ++v) {
+                        float d = absdiff(rs[v][0], vload_at(row(sb[v], 0), moff[0] + j4));
+#pragma unroll
+                        for (int m = 1; m < DX; ++m)
+                            d = fmaxf(d, absdiff(rs[v][m], vload_at(row(sb[v], m), moff[m] + j4)));
+                        dj[u][v] = j < e0 ? fmaxf(dtp, d) : kInf;
+                    }
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+#pragma unroll
+                    for (int v = 0; v < V; ++v)
+                        insert_sorted<KP1>(best[v], dj[u][v]);
+            }
+#pragma unroll
+            for (int o = RPW; o < kWave; o <<= 1)
+#pragma unroll
+                for (int v = 0; v < V; ++v) {
+                    float other[KP1];
+#pragma unroll
+                    for (int s = 0; s < KP1; ++s)
+                        other[s] = __shfl_xor(best[v][s], o, 64);
+#pragma unroll
+                    for (int s = 0; s < KP1; ++s)
+                        insert_sorted<KP1>(best[v], other[s]);
+                }
+            if (GENERIC)
+#pragma unroll
+                for (int v = 0; v < V; ++v)
+                    thr[v] = kth<KP1, GENERIC>(best[v], k);
+        } else {
+            scan(ob0 * kWave, e0);
+        }
         unsigned long long ev = (unsigned long long)(e0 - ob0 * kWave) * (unsigned long long)nref;
 
         // LDS row of a reference: its coordinates, then its current radius per variant
@@ -314,6 +366,19 @@ __device__ __forceinline__ void block_search(const SearchArgs &a)
             for (int m = 0; m < DY; ++m) {
                 blo[m] = uload(bx + (int64_t)(2 * m) * nb + blk);
                 bhi[m] = uload(bx + (int64_t)(2 * m + 1) * nb + blk);
+                if (W > 0) {
+                    // the box of the wave's own references, which every group of RPW lanes holds
+                    float lo = rt[1 + m], hi = rt[1 + m];
+#pragma unroll
+                    for (int o = 1; o < RPW; o <<= 1) {
+                        lo = fminf(lo, __shfl_xor(lo, o, 64));
+                        hi = fmaxf(hi, __shfl_xor(hi, o, 64));
+                    }
+                    if (blo[m] > -kInf && bhi[m] < kInf) {   // else: unbounded, or not numbers
+                        blo[m] = readlane_f(lo, 0);
+                        bhi[m] = readlane_f(hi, 0);
+                    }
+                }
             }
         auto load_boxes = [&](int b0, float (&lo)[DY], float (&hi)[DY]) {
             const uint32_t o = (uint32_t)min(b0 + lane, nb - 1) * 4u;
@@ -325,6 +390,20 @@ __device__ __forceinline__ void block_search(const SearchArgs &a)
                 g = fmaxf(g, fmaxf(lo[m] - bhi[m], blo[m] - hi[m]));
             }
             return g;
+        };
+        // with W waves to a block the first 64 blocks' boxes stay in registers
+        float lo0[DY], hi0[DY], g0 = 0.0f;
+        if (W > 0 && nb > 1)
+            g0 = load_boxes(0, lo0, hi0);
+        auto boxes = [&](int b0, float (&lo)[DY], float (&hi)[DY]) {
+            if (W == 0 || b0 > 0)
+                return load_boxes(b0, lo, hi);
+#pragma unroll
+            for (int m = 0; m < DY; ++m) {
+                lo[m] = lo0[m];
+                hi[m] = hi0[m];
+            }
+            return g0;
         };
         auto box_of = [&](int c, const float (&lo)[DY], const float (&hi)[DY], float (&tlo)[DY], float (&thi)[DY]) {
 #pragma unroll
@@ -424,7 +503,7 @@ __device__ __forceinline__ void block_search(const SearchArgs &a)
                     continue;
                 for (int b0 = 0; b0 < nb; b0 += kWave) {
                     float lo[DY], hi[DY];
-                    const float g = load_boxes(b0, lo, hi);
+                    const float g = boxes(b0, lo, hi);
                     const int b = b0 + lane;
                     uint64_t want = ballot(b < nb && (b < ob0 || b > blk) && g >= lim && g < nlim && !(g >= cm));
                     if (want == 0)
@@ -454,23 +533,12 @@ __device__ __forceinline__ void block_search(const SearchArgs &a)
         for (int v = 0; v < V; ++v)
             accP[v] = accTP[v] = accPS[v] = 0;
         unsigned long long evaluated2 = 0;                // candidate-reference pairs examined in pass 2
-        // the blocks b[0..SLOTS), those from `used` on being none: the references in todo are counted
-        auto count_blocks = [&](uint64_t todo, const int (&b)[SLOTS], int used) {
-            float ct[SLOTS][DT], cs[SLOTS][V][DX];
-#pragma unroll
-            for (int sl = 0; sl < SLOTS; ++sl) {
-                load_block(b[sl], ct[sl], cs[sl]);
-                if (sl > 0 && sl >= used)
-                    ct[sl][1] = kInf;                      // outside every target-past ball
-            }
-            int cands = 0;
-#pragma unroll
-            for (int sl = 0; sl < SLOTS; ++sl)
-                cands += sl < used ? min(kWave, n - b[sl] * kWave) : 0;
-            evaluated2 += (unsigned long long)__builtin_popcountll(todo) * (unsigned long long)cands;
-            // per-block counts of every reference in its lane, as n_P | n_TP << 10 | n_PS << 20 (at most
-            // 64 x SLOTS candidates): one register and one v_writelane per variant
-            static_assert(kWave * SLOTS < 1024, "packed counts take 10 bits each");
+        // counts of the references in todo over NS blocks of candidates
+        auto count = [&](uint64_t todo, auto ns, const float (*ct)[DT], const float (*cs)[V][DX]) {
+            constexpr int NS = decltype(ns)::value;
+            // the counts of every reference in its lane, as n_P | n_TP << 10 | n_PS << 20 (at most
+            // 64 x NS candidates): one register and one v_writelane per variant
+            static_assert(kWave * NS < 1024, "packed counts take 10 bits each");
             uint32_t t[V];
 #pragma unroll
             for (int v = 0; v < V; ++v)
@@ -485,7 +553,7 @@ __device__ __forceinline__ void block_search(const SearchArgs &a)
                 for (int v = 0; v < V; ++v)
                     sP[v] = sTP[v] = sPS[v] = 0;
 #pragma unroll
-                for (int sl = 0; sl < SLOTS; ++sl) {
+                for (int sl = 0; sl < NS; ++sl) {
                     float dp = absdiff(rr[1], ct[sl][1]);
 #pragma unroll
                     for (int m = 2; m < DT; ++m)
@@ -514,43 +582,49 @@ __device__ __forceinline__ void block_search(const SearchArgs &a)
                 accPS[v] += t[v] >> 20;
             }
         };
+        auto evaluate = [&](uint64_t todo, int b) {
+            evaluated2 += (unsigned long long)__builtin_popcountll(todo) * (unsigned long long)min(kWave, n - b * kWave);
+        };
         if (nb > 1) {
             const float emw = wave_max(em);
             for (int b0 = 0; b0 < nb; b0 += kWave) {
                 float lo[DY], hi[DY];
-                const float g = load_boxes(b0, lo, hi);
+                const float g = boxes(b0, lo, hi);
                 uint64_t want = ballot(b0 + lane < nb && !(g >= emw));
                 while (want != 0) {
-                    // the next SLOTS blocks that some reference reaches
-                    int b[SLOTS], used = 0;
+                    // the next SLOTS blocks that some reference reaches, counted together: a
+                    // reference's row is read once for them
+                    float ct[SLOTS][DT], cs[SLOTS][V][DX];
                     uint64_t todo = 0;
+                    int used = 0, b = 0;
 #pragma unroll
                     for (int sl = 0; sl < SLOTS; ++sl) {
-                        b[sl] = sl > 0 ? b[0] : 0;
-                        while (want != 0) {
+                        uint64_t m = 0;
+                        while (want != 0 && m == 0) {
                             const int c = __builtin_ctzll(want);
                             want &= want - 1;
                             float tlo[DY], thi[DY];
                             box_of(c, lo, hi, tlo, thi);
-                            const uint64_t m = ballot(valid && !(box_dist(tlo, thi) >= em));
-                            if (m != 0) {
-                                todo |= m;
-                                b[sl] = b0 + c;
-                                used = sl + 1;
-                                break;
-                            }
+                            m = ballot(valid && !(box_dist(tlo, thi) >= em));
+                            b = b0 + c;
                         }
+                        if (m != 0)
+                            used = sl + 1;
+                        todo |= m;
+                        load_block(b, ct[sl], cs[sl]);
+                        if (m == 0)
+                            ct[sl][1] = kInf;          // outside every target-past ball
+                        evaluate(m, b);
                     }
                     if (used > 0)
-                        count_blocks(todo, b, used);
+                        count(todo, std::integral_constant<int, SLOTS>{}, ct, cs);
                 }
             }
-        } else {
-            int b[SLOTS];
-#pragma unroll
-            for (int sl = 0; sl < SLOTS; ++sl)
-                b[sl] = 0;
-            count_blocks(ballot(valid), b, 1);
+        } else if (nref > 0) {
+            float ct[1][DT], cs[1][V][DX];
+            load_block(0, ct[0], cs[0]);
+            evaluate(ballot(valid), 0);
+            count(ballot(valid), std::integral_constant<int, 1>{}, ct, cs);
         }
 
         if constexpr (OUT) {
@@ -579,9 +653,13 @@ __device__ __forceinline__ void block_search(const SearchArgs &a)
             double term = 0.0;
             if (valid)
                 term = psi_of_count(nP) - psi_of_count(nTP) - psi_of_count(nPS);
-            const double sum = wave_sum(term);
-            if (lane == 0 && v < cnt)
+            const double sum = wave_sum<RPW>(term);
+            if (W > 0) {
+                if (lane == 0)
+                    wsum[v][threadIdx.x / kWave] = sum;
+            } else if (lane == 0 && v < cnt) {
                 a.partial[pb[v] + blk] = sum;
+            }
             if constexpr (OUT) {
                 const int64_t out = uload_l(reinterpret_cast<const int64_t *>(w0 + offsetof(ChunkDesc, out)));
                 const int64_t perm = uload_l(reinterpret_cast<const int64_t *>(w0 + offsetof(ChunkDesc, perm)));
@@ -601,10 +679,30 @@ __device__ __forceinline__ void block_search(const SearchArgs &a)
                 }
             }
         }
+        if (W > 0) {
+            // the waves' sums in the order of the butterfly that a whole wave's lanes go through
+            __syncthreads();
+#pragma unroll
+            for (int v = 0; v < V; ++v)
+                if (threadIdx.x == 0 && v < cnt) {
+                    double s[W > 0 ? W : 1];
+#pragma unroll
+                    for (int x = 0; x < W; ++x)
+                        s[x] = wsum[v][x];
+#pragma unroll
+                    for (int o = 1; o < W; o <<= 1)
+#pragma unroll
+                        for (int x = 0; x < W; x += 2 * o)
+                            s[x] += s[x + o];
+                    a.partial[pb[v] + blk] = s[0];
+                }
+        }
         work1 += ev * (unsigned long long)cnt;
         work2 += evaluated2 * (unsigned long long)cnt;
         shared1 += ev;
         shared2 += evaluated2;
+        if (W > 0)
+            break;
     }
     // measurement: one pair of counter updates per wave, after its last item
     if (a.work != nullptr && lane == 0) {
@@ -615,28 +713,35 @@ __device__ __forceinline__ void block_search(const SearchArgs &a)
     }
 }
 
-template <int DY, int DX, int KP1, bool GENERIC, int SLOTS>
-__global__ void __launch_bounds__(kMaxWavesPerWG * 64) search_kernel(SearchArgs a)
+// W waves to a block (W = 0: persistent waves, a block each).
+template <int DY, int DX, int KP1, bool GENERIC, int SLOTS, int W>
+__global__ void __launch_bounds__((W > 0 ? W : kMaxWavesPerWG) * 64) search_kernel(SearchArgs a)
 {
-    block_search<DY, DX, 1, KP1, GENERIC, SLOTS, true>(a);
+    block_search<DY, DX, 1, KP1, GENERIC, SLOTS, true, W>(a);
 }
 
-template <int DY, int DX, int V, int SLOTS>
-__global__ void __launch_bounds__(kMaxWavesPerWG * 64) search_sets_kernel(SearchArgs a)
+template <int DY, int DX, int V, int SLOTS, int W>
+__global__ void __launch_bounds__((W > 0 ? W : kMaxWavesPerWG) * 64) search_sets_kernel(SearchArgs a)
 {
-    block_search<DY, DX, V, 5, false, SLOTS, false>(a);
+    block_search<DY, DX, V, 5, false, SLOTS, false, W>(a);
 }
 
 typedef void (*search_fn)(SearchArgs);
 
-// Blocks of candidates counted together in pass 2: the tuned slot count 4 -> 1, 8 or 16 -> 2.
-template <int SLOTS>
-search_fn pick(int d_y, int d_x, bool generic, bool sets)
+enum Kind { kSingle, kSets, kAnyK };       // single chunks at k = 4, chunk sets (k = 4), single chunks at any k
+
+template <Kind KIND, int SLOTS, int W>
+search_fn pick(int d_y, int d_x)
 {
-#define TE_CASE(A, B)                                                                   \
-    if (d_y == A && d_x == B)                                                           \
-        return sets ? search_sets_kernel<A, B, set_variants(A, B), SLOTS>               \
-                    : (generic ? search_kernel<A, B, kMaxK + 1, true, SLOTS> : search_kernel<A, B, 5, false, SLOTS>);
+#define TE_CASE(A, B)                                                            \
+    if (d_y == A && d_x == B) {                                                  \
+        if constexpr (KIND == kSets)                                             \
+            return search_sets_kernel<A, B, set_variants(A, B), SLOTS, W>;       \
+        else if constexpr (KIND == kSingle)                                      \
+            return search_kernel<A, B, 5, false, SLOTS, W>;                      \
+        else                                                                     \
+            return search_kernel<A, B, kMaxK + 1, true, SLOTS, W>;               \
+    }
     TE_CASE(1, 1) TE_CASE(1, 2) TE_CASE(1, 3) TE_CASE(1, 4)
     TE_CASE(2, 1) TE_CASE(2, 2) TE_CASE(2, 3) TE_CASE(2, 4)
     TE_CASE(3, 1) TE_CASE(3, 2) TE_CASE(3, 3) TE_CASE(3, 4)
@@ -655,14 +760,60 @@ size_t lds_bytes(int d_y, int d_x, bool sets, int waves_per_wg)
 
 }  // namespace
 
-// The search over ordered chunks, single or in sets (k = 4); nullptr where there is none.
+// The persistent search over ordered chunks, single or in sets (k = 4); no kernel where there is none.
+// Blocks of candidates counted together in pass 2: the tuned slot count 4 -> 1, 8 or 16 -> 2.
 ordered_search pick_ordered(int d_y, int d_x, int k, int slots, bool sets, int waves_per_wg)
 {
     ordered_search s{nullptr, 0};
     if (k < 1 || k > kMaxK || (sets && k != 4) || (slots != 4 && slots != 8 && slots != 16))
         return s;
-    s.fn = slots == 4 ? pick<1>(d_y, d_x, k != 4, sets) : pick<2>(d_y, d_x, k != 4, sets);
+    if (slots == 4)
+        s.fn = sets ? pick<kSets, 1, 0>(d_y, d_x) : k == 4 ? pick<kSingle, 1, 0>(d_y, d_x) : pick<kAnyK, 1, 0>(d_y, d_x);
+    else
+        s.fn = sets ? pick<kSets, 2, 0>(d_y, d_x) : k == 4 ? pick<kSingle, 2, 0>(d_y, d_x) : pick<kAnyK, 2, 0>(d_y, d_x);
     s.lds = lds_bytes(d_y, d_x, sets, waves_per_wg);
+    return s;
+}
+
+// Waves to a block for a launch of n_items blocks; 0: persistent waves, a block each.  With few
+// blocks the chip has more SIMDs than items and a wave, alone on its SIMD, issues an instruction
+// every 6 clocks: the time is one block's chain of instructions.  W waves to a block cut that chain
+// by W, at the price of W walks over the boxes and of insertions for 64 / W references at a time.
+// Measured, us per call of one launch (persistent / W = 2 / 4 / 8):
+//   k = 4, 32 blocks (N = 2 000, D = 5)      181 /  - / 121 / 105
+//   k = 4, 640 blocks                        196 /  - / 134 / 129
+//   k = 4, 790 blocks (N = 5 000, D = 7)     471 / 373 / 335 / 352
+//   k = 4, 3 950 blocks                     1163 / 767 / 809 / 1024
+//   k = 4, 15 800 blocks                    1528 / 1263 / 1415 / 1870
+//   k = 4, 31 600 blocks                    2339 / 2334 / 2697 / 3630
+//   sets of four, 192 blocks (N = 2 000)     577 / 413 / 299 / 241
+//   sets of four, 832 blocks                 612 / 507 / 470 / 577
+//   sets of four, 1 632 blocks               702 / 746 / 677 / 930
+//   sets of four, 3 328 blocks               873 / 1111 / 1090 / 1673
+//   any k, 720 blocks (N = 801 .. 12 007)    952 /  -  / 525 / 499
+//   any k, 940 blocks (N = 3 000, k = 8)     423 / 498 / 479 / 486
+int waves_to_a_block(int64_t n_items, bool sets, int k)
+{
+    if (sets)
+        return n_items <= 512 ? 8 : (n_items <= 1536 ? 4 : 0);
+    if (k != 4)
+        return n_items <= 768 ? 8 : 0;
+    return n_items <= 512 ? 8 : (n_items <= 3072 ? 4 : (n_items <= 24576 ? 2 : 0));
+}
+
+// The search with w waves to a block (w from waves_to_a_block, not 0): one workgroup of w waves per item.
+ordered_search pick_shared(int d_y, int d_x, int k, bool sets, int w)
+{
+    ordered_search s{nullptr, 0};
+    if (k < 1 || k > kMaxK || (sets && k != 4))
+        return s;
+    if (sets)
+        s.fn = w == 4 ? pick<kSets, 1, 4>(d_y, d_x) : pick<kSets, 1, 8>(d_y, d_x);
+    else if (k != 4)
+        s.fn = pick<kAnyK, 1, 8>(d_y, d_x);
+    else
+        s.fn = w == 2 ? pick<kSingle, 1, 2>(d_y, d_x) : w == 4 ? pick<kSingle, 1, 4>(d_y, d_x) : pick<kSingle, 1, 8>(d_y, d_x);
+    s.lds = lds_bytes(d_y, d_x, sets, w);
     return s;
 }
 

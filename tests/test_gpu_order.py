@@ -73,3 +73,31 @@ def test_ordered_equals_unordered_beyond_slabs(te, monkeypatch, N):
     """More points than slabs of one workgroup each hold: the network sort in global scratch."""
     print("beyond slabs", N, flush=True)
     _both(te, monkeypatch, _points("gauss", N, 4, 503), [N], 2, 1, 4)
+
+
+def _repeated(points, S, k):
+    """`points` copies of one window (650 points: 11 blocks, the last ragged)."""
+    wl = synth.generic((6091, S, k), R=50, T=60, d_y=2, d_x=2, k=k, starts=(30,), windows=(13,), n_surrogates=S)
+    wl.window_start = np.full(points, 30, np.int32)
+    wl.window_len = np.full(points, 13, np.int32)
+    wl.trials = np.full(points, 50, np.int32)
+    if S:
+        wl.perms = np.ascontiguousarray(np.repeat(wl.perms, points, axis=1))
+    return wl
+
+
+@pytest.mark.parametrize("S,k,points", [(0, 4, (1, 50, 300, 2300)), (3, 4, (1, 100, 200)), (0, 3, (1, 100))])
+def test_estimates_do_not_depend_on_the_waves_per_block(te, S, k, points):
+    """The same window alone and among copies of itself, in launches of few and of many blocks
+    (8, 4, 2 waves to a block, persistent waves): every estimate has the same bits."""
+    import torch
+    first = None
+    for n in points:
+        wl = _repeated(n, S, k)
+        print("copies", n, "S", S, "k", k, flush=True)
+        x, y = torch.from_numpy(wl.x).cuda(), torch.from_numpy(wl.y).cuda()
+        perms = torch.from_numpy(wl.perms).cuda() if S else None
+        t0, ts, _ = te.Plan.from_workload(wl).surrogates(x, y, perms)
+        first = first or (t0[0, 0], ts[0, 0].copy())
+        np.testing.assert_array_equal(t0, np.full_like(t0, first[0]))
+        np.testing.assert_array_equal(ts[0], np.repeat(first[1][None], n, axis=0))
