@@ -148,6 +148,19 @@ __device__ __forceinline__ uint32_t writelane(uint32_t old, uint32_t v, int lane
     return old;
 }
 
+// One scalar instruction each: the SALU issues one in four clocks per SIMD and is what the
+// counting loop waits for.  m without its bit r; and lo | hi << 16 of values below 2^16.
+__device__ __forceinline__ uint64_t clear_bit(uint64_t m, int r)
+{
+    asm("s_bitset0_b64 %0, %1" : "+s"(m) : "s"(r));
+    return m;
+}
+__device__ __forceinline__ uint32_t pack16(uint32_t lo, uint32_t hi)
+{
+    uint32_t d;
+    asm("s_pack_ll_b32_b16 %0, %1, %2" : "=s"(d) : "s"(lo), "s"(hi));
+    return d;
+}
 __device__ __forceinline__ float readlane_f(float v, int lane)
 {
     return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), lane));

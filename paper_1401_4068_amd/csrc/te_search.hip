@@ -50,11 +50,9 @@ template <int DY, int DX, int V, int KP1, bool GENERIC, int SLOTS, bool OUT, int
 __device__ __forceinline__ void block_search(const SearchArgs &a)
 {
     constexpr int DT = 1 + DY;                 // shared coordinates: y_t' and the target past
-    constexpr int D = DT + DX;
     constexpr int NR = DT + V * DX + V;        // LDS row: shared coordinates, V source blocks, V radii
     constexpr int RW = (NR + 3) & ~3;
     constexpr int MO = DT > DX ? DT : DX;      // coordinate offsets shared by the target and source blocks
-    constexpr int G = (V == 1 && D <= 7) ? 8 : 4;   // candidates per scalar-load group
     extern __shared__ __attribute__((aligned(16))) float rows[];   // waves per workgroup x 64 x RW floats
     __shared__ double wsum[V][W > 0 ? W : 1];
     const int lane = threadIdx.x & (kWave - 1);
@@ -165,87 +163,110 @@ __device__ __forceinline__ void block_search(const SearchArgs &a)
             return valid ? c : 0.0f;
         };
 
-        // lane = reference: NC consecutive candidates from j, wave-uniform (scalar loads).  Their
-        // distances are independent; one wave-wide test of the group's smallest decides whether any
-        // insertion is needed, and a test per candidate skips the insertions that no lane needs.
-        auto visit = [&](auto nc, int j) {
-            constexpr int NC = decltype(nc)::value;
-            const uint32_t off = (uint32_t)j * 4u;
-            float ct[NC][DT], cs[V][NC][DX];
-            auto load = [&](const float *p, uint32_t o, float (&x)[NC]) {
-                if constexpr (NC == 8) {
-                    const f8v t = uload8_at(p, o);
+        // LDS row of a reference: its coordinates, then its current radius per variant
+        auto store_row = [&](const float (&ct)[DT], const float (&cs)[V][DX]) {
+            __builtin_amdgcn_wave_barrier();
 #pragma unroll
-                    for (int u = 0; u < 8; ++u)
-                        x[u] = t[u];
-                } else if constexpr (NC == 4) {
-                    const f4v t = uload4_at(p, o);
-                    x[0] = t.x;
-                    x[1] = t.y;
-                    x[2] = t.z;
-                    x[3] = t.w;
-                } else {
-                    x[0] = uload_at(p, o);
-                }
-            };
+            for (int m = 0; m < DT; ++m)
+                prow[lane * RW + m] = ct[m];
+#pragma unroll
+            for (int v = 0; v < V; ++v) {
+#pragma unroll
+                for (int m = 0; m < DX; ++m)
+                    prow[lane * RW + DT + v * DX + m] = cs[v][m];
+                prow[lane * RW + DT + V * DX + v] = cur(v);
+            }
+            __builtin_amdgcn_wave_barrier();
+        };
+        auto read_row = [&](int r, float (&rr)[RW]) {
+            const f4v *rowv = reinterpret_cast<const f4v *>(prow + r * RW);
+#pragma unroll
+            for (int x = 0; x < RW / 4; ++x) {
+                const f4v q4 = rowv[x];
+                rr[4 * x + 0] = q4.x;
+                rr[4 * x + 1] = q4.y;
+                rr[4 * x + 2] = q4.z;
+                rr[4 * x + 3] = q4.w;
+            }
+        };
+        auto store_radii = [&]() {
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int v = 0; v < V; ++v)
+                prow[lane * RW + DT + V * DX + v] = cur(v);
+            __builtin_amdgcn_wave_barrier();
+        };
+        // block b's candidates, one per lane (coordinates +inf past the chunk's end: outside every ball)
+        auto load_block = [&](int b, float (&ct)[DT], float (&cs)[V][DX]) {
+            const int idx = b * kWave + lane;
+            const bool ok = idx < n;
+            const uint32_t ic4 = (uint32_t)(ok ? idx : n - 1) * 4u;
 #pragma unroll
             for (int m = 0; m < DT; ++m) {
-                float x[NC];
-                load(row(tb, m), moff[m] + off, x);
-#pragma unroll
-                for (int u = 0; u < NC; ++u)
-                    ct[u][m] = x[u];
+                const float x = vload_at(row(tb, m), moff[m] + ic4);
+                ct[m] = ok ? x : kInf;
             }
 #pragma unroll
             for (int v = 0; v < V; ++v)
 #pragma unroll
                 for (int m = 0; m < DX; ++m) {
-                    float x[NC];
-                    load(row(sb[v], m), moff[m] + off, x);
-#pragma unroll
-                    for (int u = 0; u < NC; ++u)
-                        cs[v][u][m] = x[u];
+                    const float x = vload_at(row(sb[v], m), moff[m] + ic4);
+                    cs[v][m] = ok ? x : kInf;
                 }
-            float dtp[NC];
+        };
+        // lane = reference: every lane's reference (lt, ls) against the candidates whose rows are in LDS,
+        // c < c1, read back two at a time as broadcasts.  (From scalar loads the subtractions have an SGPR
+        // operand and issue at half rate; the 15-neighbour lists of 410 chunks of 1 159 points took 1 302 us
+        // that way against 1 044, the four-neighbour sets the same time.)
+        auto scan_rows = [&](int c1, const float (&lt)[DT], const float (&ls)[V][DX]) {
+            for (int c = 0; c < c1; c += 2) {
+                float rr[2][RW], dtp[2];
+                read_row(c, rr[0]);
+                read_row(min(c + 1, kWave - 1), rr[1]);
 #pragma unroll
-            for (int u = 0; u < NC; ++u) {
-                float d = absdiff(rt[0], ct[u][0]);
+                for (int u = 0; u < 2; ++u) {
+                    dtp[u] = absdiff(rr[u][0], lt[0]);
 #pragma unroll
-                for (int m = 1; m < DT; ++m)
-                    d = fmaxf(d, absdiff(rt[m], ct[u][m]));
-                dtp[u] = d;
-            }
-#pragma unroll
-            for (int v = 0; v < V; ++v) {
-                float dj[NC];
-#pragma unroll
-                for (int u = 0; u < NC; ++u) {
-                    float d = absdiff(rs[v][0], cs[v][u][0]);
-#pragma unroll
-                    for (int m = 1; m < DX; ++m)
-                        d = fmaxf(d, absdiff(rs[v][m], cs[v][u][m]));
-                    dj[u] = fmaxf(dtp[u], d);
+                    for (int m = 1; m < DT; ++m)
+                        dtp[u] = fmaxf(dtp[u], absdiff(rr[u][m], lt[m]));
                 }
-                float mn = dj[0];
+                if (c + 1 >= c1)
+                    dtp[1] = kInf;
 #pragma unroll
-                for (int u = 1; u < NC; ++u)
-                    mn = fminf(mn, dj[u]);
-                if (ballot(mn < cur(v))) {
-                    keep_branch();
+                for (int v = 0; v < V; ++v) {
+                    float dj[2];
 #pragma unroll
-                    for (int u = 0; u < NC; ++u)
-                        if (NC == 1 || ballot(dj[u] < cur(v))) {
-                            keep_branch();
-                            insert(v, dj[u]);
-                        }
+                    for (int u = 0; u < 2; ++u) {
+                        float d = absdiff(rr[u][DT + v * DX], ls[v][0]);
+#pragma unroll
+                        for (int m = 1; m < DX; ++m)
+                            d = fmaxf(d, absdiff(rr[u][DT + v * DX + m], ls[v][m]));
+                        dj[u] = fmaxf(dtp[u], d);
+                    }
+                    if (ballot(fminf(dj[0], dj[1]) < cur(v))) {
+                        keep_branch();
+                        insert(v, dj[0]);
+                        insert(v, dj[1]);
+                    }
                 }
             }
         };
-        auto scan = [&](int j, int j1) {
-            for (; j + G <= j1; j += G)
-                visit(std::integral_constant<int, G>{}, j);
-            for (; j < j1; ++j)
-                visit(std::integral_constant<int, 1>{}, j);
+        // the same for block b, whose candidates take the place of the references' rows meanwhile
+        auto scan_block = [&](int b) {
+            float ct[DT], cs[V][DX], own[RW], lt[DT], ls[V][DX];
+            load_block(b, ct, cs);
+            read_row(lane, own);
+#pragma unroll
+            for (int m = 0; m < DT; ++m)
+                lt[m] = own[m];
+#pragma unroll
+            for (int v = 0; v < V; ++v)
+#pragma unroll
+                for (int m = 0; m < DX; ++m)
+                    ls[v][m] = own[DT + v * DX + m];
+            store_row(ct, cs);
+            scan_rows(min(kWave, n - b * kWave), lt, ls);
+            store_row(lt, ls);
         };
 
         // the block's own points first (with a ragged last block, the block before it too, so
@@ -297,60 +318,17 @@ __device__ __forceinline__ void block_search(const SearchArgs &a)
 #pragma unroll
                 for (int v = 0; v < V; ++v)
                     thr[v] = kth<KP1, GENERIC>(best[v], k);
+            store_row(rt, rs);
         } else {
-            scan(ob0 * kWave, e0);
+            store_row(rt, rs);
+            scan_rows(nref, rt, rs);
+            if (ob0 < blk)
+                scan_block(ob0);
+            else
+                store_radii();
         }
         unsigned long long ev = (unsigned long long)(e0 - ob0 * kWave) * (unsigned long long)nref;
 
-        // LDS row of a reference: its coordinates, then its current radius per variant
-        __builtin_amdgcn_wave_barrier();
-#pragma unroll
-        for (int m = 0; m < DT; ++m)
-            prow[lane * RW + m] = rt[m];
-#pragma unroll
-        for (int v = 0; v < V; ++v) {
-#pragma unroll
-            for (int m = 0; m < DX; ++m)
-                prow[lane * RW + DT + v * DX + m] = rs[v][m];
-            prow[lane * RW + DT + V * DX + v] = cur(v);
-        }
-        __builtin_amdgcn_wave_barrier();
-        auto read_row = [&](int r, float (&rr)[RW]) {
-            const f4v *rowv = reinterpret_cast<const f4v *>(prow + r * RW);
-#pragma unroll
-            for (int x = 0; x < RW / 4; ++x) {
-                const f4v q4 = rowv[x];
-                rr[4 * x + 0] = q4.x;
-                rr[4 * x + 1] = q4.y;
-                rr[4 * x + 2] = q4.z;
-                rr[4 * x + 3] = q4.w;
-            }
-        };
-        auto store_radii = [&]() {
-            __builtin_amdgcn_wave_barrier();
-#pragma unroll
-            for (int v = 0; v < V; ++v)
-                prow[lane * RW + DT + V * DX + v] = cur(v);
-            __builtin_amdgcn_wave_barrier();
-        };
-        // block b's candidates, one per lane (coordinates +inf past the chunk's end: outside every ball)
-        auto load_block = [&](int b, float (&ct)[DT], float (&cs)[V][DX]) {
-            const int idx = b * kWave + lane;
-            const bool ok = idx < n;
-            const uint32_t ic4 = (uint32_t)(ok ? idx : n - 1) * 4u;
-#pragma unroll
-            for (int m = 0; m < DT; ++m) {
-                const float x = vload_at(row(tb, m), moff[m] + ic4);
-                ct[m] = ok ? x : kInf;
-            }
-#pragma unroll
-            for (int v = 0; v < V; ++v)
-#pragma unroll
-                for (int m = 0; m < DX; ++m) {
-                    const float x = vload_at(row(sb[v], m), moff[m] + ic4);
-                    cs[v][m] = ok ? x : kInf;
-                }
-        };
         // distance of the lane's reference from a box (-inf: inside, or not a number)
         auto box_dist = [&](const float (&lo)[DY], const float (&hi)[DY]) {
             float g = -kInf;
@@ -420,8 +398,7 @@ __device__ __forceinline__ void block_search(const SearchArgs &a)
             const int reach = __builtin_popcountll(todo);
             if (reach >= kDense) {
                 ev += (unsigned long long)nref * (unsigned long long)(t1 - t0);
-                scan(t0, t1);
-                store_radii();
+                scan_block(b);
                 return;
             }
             if (reach == 0)
@@ -438,7 +415,7 @@ __device__ __forceinline__ void block_search(const SearchArgs &a)
             bool dirty = false;
             do {
                 const int r = __builtin_ctzll(todo);
-                todo &= todo - 1;
+                todo = clear_bit(todo, r);
                 float rr[RW];
                 read_row(r, rr);
                 float dtp = absdiff(rr[0], ct[0]);
@@ -527,25 +504,45 @@ __device__ __forceinline__ void block_search(const SearchArgs &a)
         const float em = curmax();
 
         // ---- pass 2: lane = candidate, references uniform from this wave's LDS rows (which hold the
-        // final radii); the three strict comparisons are wave ballots, counted on the SALU
+        // final radii); the three strict comparisons are wave ballots, counted on the SALU.  Bound by
+        // issue: at (3, 3, four chunks) a step of 64 candidates is 45 VALU (28 of them at half rate), 28 SALU
+        // and five LDS reads, 171 clocks per SIMD; the two-to-a-register counts took 11 SALU off it
+        // (30 windows x 101 chunks of 1 000 to 50 000 points: 119.0 -> 110.6 ms).
+        constexpr int NC = V + (V + 1) / 2;
         uint32_t accP[V], accTP[V], accPS[V];
+        uint32_t packed[NC];                              // counts since the last unpack(), 16 bits each
+        int counted = 0;                                  // candidates counted since then, at most 65 535
 #pragma unroll
         for (int v = 0; v < V; ++v)
             accP[v] = accTP[v] = accPS[v] = 0;
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+            packed[c] = 0;
+        auto unpack = [&]() {
+#pragma unroll
+            for (int v = 0; v < V; ++v) {
+                accP[v] += packed[v] & 0xffffu;
+                accTP[v] += packed[v] >> 16;
+                accPS[v] += v % 2 == 0 ? packed[V + v / 2] & 0xffffu : packed[V + v / 2] >> 16;
+            }
+#pragma unroll
+            for (int c = 0; c < NC; ++c)
+                packed[c] = 0;
+            counted = 0;
+        };
         unsigned long long evaluated2 = 0;                // candidate-reference pairs examined in pass 2
         // counts of the references in todo over NS blocks of candidates
         auto count = [&](uint64_t todo, auto ns, const float (*ct)[DT], const float (*cs)[V][DX]) {
             constexpr int NS = decltype(ns)::value;
-            // the counts of every reference in its lane, as n_P | n_TP << 10 | n_PS << 20 (at most
-            // 64 x NS candidates): one register and one v_writelane per variant
-            static_assert(kWave * NS < 1024, "packed counts take 10 bits each");
-            uint32_t t[V];
+            // the counts of every reference in its lane, two to a register: n_P | n_TP << 16 of each
+            // variant, then the variants' n_PS in pairs
+            uint32_t t[NC];
 #pragma unroll
-            for (int v = 0; v < V; ++v)
-                t[v] = 0;
+            for (int c = 0; c < NC; ++c)
+                t[c] = 0;
             while (todo != 0) {
                 const int r = __builtin_ctzll(todo);
-                todo &= todo - 1;
+                todo = clear_bit(todo, r);
                 float rr[RW];
                 read_row(r, rr);
                 uint32_t sP[V], sTP[V], sPS[V];
@@ -573,14 +570,17 @@ __device__ __forceinline__ void block_search(const SearchArgs &a)
                 }
 #pragma unroll
                 for (int v = 0; v < V; ++v)
-                    t[v] = writelane(t[v], sP[v] | (sTP[v] << 10) | (sPS[v] << 20), r);
+                    t[v] = writelane(t[v], pack16(sP[v], sTP[v]), r);
+#pragma unroll
+                for (int v = 0; v < V; v += 2)
+                    t[V + v / 2] = writelane(t[V + v / 2], v + 1 < V ? pack16(sPS[v], sPS[v + 1]) : sPS[v], r);
             }
 #pragma unroll
-            for (int v = 0; v < V; ++v) {
-                accP[v] += t[v] & 1023u;
-                accTP[v] += (t[v] >> 10) & 1023u;
-                accPS[v] += t[v] >> 20;
-            }
+            for (int c = 0; c < NC; ++c)
+                packed[c] += t[c];
+            counted += kWave * NS;
+            if (counted > 65535 - kWave * SLOTS)
+                unpack();
         };
         auto evaluate = [&](uint64_t todo, int b) {
             evaluated2 += (unsigned long long)__builtin_popcountll(todo) * (unsigned long long)min(kWave, n - b * kWave);
@@ -627,18 +627,21 @@ __device__ __forceinline__ void block_search(const SearchArgs &a)
             count(ballot(valid), std::integral_constant<int, 1>{}, ct, cs);
         }
 
+        unpack();
         if constexpr (OUT) {
             // Pre-embedded points may be infinite: a difference of equal infinities is no number and
             // lies in no ball, but a maximum passes it over.  It takes an infinite reference.
             auto unbounded = [](float x, float z) { return fmaxf(z, absdiff(x, x)); };
-            float p = rt[1] - rt[1], s = rs[0][0] - rs[0][0];
+            float own[RW];
+            read_row(lane, own);
+            float p = rt[1] - rt[1], s = own[DT] - own[DT];
 #pragma unroll
             for (int m = 1; m < DY; ++m)
                 p = unbounded(rt[1 + m], p);
 #pragma unroll
             for (int m = 1; m < DX; ++m)
-                s = unbounded(rs[0][m], s);
-            if (p != p || rt[0] - rt[0] != 0.0f)
+                s = unbounded(own[DT + m], s);
+            if (p != p || own[0] - own[0] != 0.0f)
                 accTP[0] = 0;
             if (p != p || s != s)
                 accPS[0] = 0;
@@ -720,8 +723,14 @@ __global__ void __launch_bounds__((W > 0 ? W : kMaxWavesPerWG) * 64) search_kern
     block_search<DY, DX, 1, KP1, GENERIC, SLOTS, true, W>(a);
 }
 
+// A set whose pairs have many coordinates is held to five waves per SIMD: at (3, 3, four chunks) 96
+// VGPRs with a few spills beat 105 and four waves, 111 to 103 ms on 30 windows x 101 chunks of 1 000 to
+// 50 000 points; the narrower sets have five or six waves as they are and lose by it.
+constexpr int sets_waves(int d_y, int d_x, int v, int w) { return w == 0 && 1 + d_y + v * d_x >= 16 ? 5 : 1; }
+
 template <int DY, int DX, int V, int SLOTS, int W>
-__global__ void __launch_bounds__((W > 0 ? W : kMaxWavesPerWG) * 64) search_sets_kernel(SearchArgs a)
+__global__ void __launch_bounds__((W > 0 ? W : kMaxWavesPerWG) * 64)
+    __attribute__((amdgpu_waves_per_eu(sets_waves(DY, DX, V, W), 8))) search_sets_kernel(SearchArgs a)
 {
     block_search<DY, DX, V, 5, false, SLOTS, false, W>(a);
 }
