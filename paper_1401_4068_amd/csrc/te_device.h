@@ -221,6 +221,20 @@ __device__ __forceinline__ int find_chunk(const int32_t *item_start, int n_chunk
     return lo;
 }
 
+// Box of a wave's 64 values: their smallest and largest, in every lane; unbounded if one is no
+// number (its distances then say nothing, so nothing may be skipped for them).
+__device__ __forceinline__ void wave_box(float v, float *lo, float *hi)
+{
+    float a = v != v ? -kInf : v, b = v != v ? kInf : v;
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) {
+        a = fminf(a, __shfl_xor(a, o, 64));
+        b = fmaxf(b, __shfl_xor(b, o, 64));
+    }
+    *lo = a;
+    *hi = b;
+}
+
 // Largest of the wave's values, uniform: DPP row shifts, then the row broadcasts.
 // The values are non-negative floats, whose bit patterns order like unsigned integers.
 __device__ __forceinline__ float wave_max(float f)

@@ -71,7 +71,8 @@ struct SortTask {
     int64_t scratch;  // uint64 offset of global key scratch (npad > kSortLds), else -1
     int64_t key_off;  // mode 1: float offset of the first target-past coordinate (point q at key_off + q)
     int32_t mode;     // 0: keys from y of window point q = r W + (t' - w); 1: stored coordinates
-    int32_t pair, w, W, Rc, n, npad, pad_;
+    int32_t pair, w, W, Rc, n, npad;
+    int32_t nd;       // coordinates that order the space; 0: the launch's d_y
 };
 constexpr int kSortLds = 16384;   // keys sorted in LDS (128 KiB) up to this many (padded) points
 
@@ -186,8 +187,9 @@ hipError_t launch_fill_i32(int32_t *p, int32_t v, int64_t n, hipStream_t st);
 hipError_t launch_embed(const float *x, const float *y, const int32_t *perms, int32_t *sigma, uint64_t *scratch,
                         const int32_t *u_dev, const EmbedTask *tasks, int n_tasks, int max_n, float *base, int R,
                         int T, int d_y, int d_x, int tau, int u, int cond, int32_t *err, hipStream_t st);
-// Order maps of n_tasks search spaces by their d_y target-past coordinates (ld: the stride
-// between the coordinates of pts, mode 1; tau: the embedding delay, mode 0).
+// Order maps of n_tasks search spaces of at most max_n points by their d_y target-past coordinates
+// (0: the tasks' own, at most 4; ld: the stride between the coordinates of pts, mode 1; tau: the
+// embedding delay, mode 0).
 hipError_t launch_sort(const float *y, const float *pts, int64_t ld, const SortTask *tasks, int n_tasks, int max_n,
                        int32_t *sigma, uint64_t *scratch, int R, int T, int d_y, int tau, hipStream_t st);
 hipError_t launch_gather(const float *src, const GatherTask *tasks, int n_tasks, int max_n, int32_t *sigma,

@@ -307,20 +307,6 @@ __global__ void fill_i32_kernel(int32_t *p, int32_t v, int64_t n)
         p[i] = v;
 }
 
-// Box of a wave's 64 values: their smallest and largest, in every lane; unbounded if one is no
-// number (its distances then say nothing, so nothing may be skipped for them).
-__device__ __forceinline__ void wave_box(float v, float *lo, float *hi)
-{
-    float a = v != v ? -kInf : v, b = v != v ? kInf : v;
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) {
-        a = fminf(a, __shfl_xor(a, o, 64));
-        b = fmaxf(b, __shfl_xor(b, o, 64));
-    }
-    *lo = a;
-    *hi = b;
-}
-
 // One wave per block of 64 points at a time: the block's coordinates gathered through the order
 // map, and with the window's first target block the block's box (target-past coordinates; the
 // current source sample, which shuffles with the source, stays unbounded).
@@ -635,14 +621,14 @@ constexpr int kCodeBits = 15;
 constexpr int kClasses = 128;          // runs between cuts: 2 (kMaxSlabs - 1) + 1 at most
 
 __global__ void __launch_bounds__(kOrderThreads) split_kernel(CoordSource src, const SortTask *__restrict__ tasks,
-                                                              int32_t *sigma, uint64_t *scratch, int nd)
+                                                              int32_t *sigma, uint64_t *scratch, int d_y)
 {
     __shared__ uint32_t hist[1 << kCodeBits];             // code counts; then each code's class
     __shared__ uint32_t cnt[kOrderWaves * kClasses];
     __shared__ uint32_t part[2 * kOrderWaves];
     __shared__ int32_t cut_code[kMaxSlabs];
     const SortTask tk = tasks[blockIdx.x];
-    const int n = tk.n;
+    const int n = tk.n, nd = tk.nd > 0 ? tk.nd : d_y;
     const int slabs = order_slabs(n, nd);
     if (slabs <= 1)
         return;
@@ -757,7 +743,7 @@ __global__ void __launch_bounds__(kOrderThreads) split_kernel(CoordSource src, c
 // Any order is correct (the boxes are taken from the points); this one is the same on every path.
 template <bool LIST>                       // slabs of larger spaces among the tasks: their points listed in LDS
 __global__ void __launch_bounds__(kOrderThreads) order_kernel(CoordSource src, const SortTask *__restrict__ tasks,
-                                                              int32_t *sigma, int nd)
+                                                              int32_t *sigma, int d_y)
 {
     __shared__ struct {
         uint32_t key[kSlabMax];
@@ -768,6 +754,7 @@ __global__ void __launch_bounds__(kOrderThreads) order_kernel(CoordSource src, c
     } sh;
     __shared__ uint32_t list[LIST ? kSlabMax : 1];
     const SortTask tk = tasks[blockIdx.x];
+    const int nd = tk.nd > 0 ? tk.nd : d_y;
     const int slabs = order_slabs(tk.n, nd);
     if ((int)blockIdx.y >= slabs)          // also: spaces that order_big_kernel orders (no slabs)
         return;
@@ -879,11 +866,11 @@ __global__ void __launch_bounds__(kOrderThreads) order_kernel(CoordSource src, c
 // tile, so each tile is loaded into LDS once per stage for those passes and only the wider
 // strides touch global memory.
 __global__ void __launch_bounds__(kOrderThreads) order_big_kernel(CoordSource src, const SortTask *__restrict__ tasks,
-                                                                  int32_t *sigma, uint64_t *scratch, int nd)
+                                                                  int32_t *sigma, uint64_t *scratch, int d_y)
 {
     __shared__ uint64_t lds[kSortLds];
     const SortTask tk = tasks[blockIdx.x];
-    const int n = tk.n, np = tk.npad;
+    const int n = tk.n, np = tk.npad, nd = tk.nd > 0 ? tk.nd : d_y;
     if (order_slabs(n, nd) > 0)
         return;
     const int nl = (n + kWave - 1) / kWave;
@@ -1381,7 +1368,9 @@ hipError_t launch_sort(const float *y, const float *pts, int64_t ld, const SortT
         return hipGetLastError();
     }
     // the most slabs of any task: order_slabs grows with n up to kMaxSlabs; above that there are none
-    const int slabs = order_slabs(max_n, d_y);
+    int slabs = order_slabs(max_n, d_y > 0 ? d_y : 1);
+    for (int nd = 2; d_y == 0 && nd <= 4; ++nd)
+        slabs = std::max(slabs, order_slabs(max_n, nd));
     hipLaunchKernelGGL(split_kernel, dim3(n_tasks), dim3(kOrderThreads), 0, st, src, tasks, sigma, scratch, d_y);
     if (slabs == 0)
         hipLaunchKernelGGL(order_big_kernel, dim3(n_tasks), dim3(kOrderThreads), 0, st, src, tasks, sigma, scratch,

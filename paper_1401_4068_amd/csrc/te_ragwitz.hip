@@ -13,6 +13,7 @@
 #include <vector>
 
 #include "te.h"
+#include "te_device.h"
 #include "te_internal.h"
 #include "te_runtime.h"
 
@@ -22,38 +23,55 @@ namespace {
 constexpr int kRagMaxDim = TE_RAGWITZ_MAX_DIM;
 constexpr int kRagMaxK = TE_RAGWITZ_MAX_K;
 constexpr int kScoreThreads = 256;
+constexpr int kRagBatch = 16;             // candidates of one launch at most (their tables travel as kernel arguments)
+constexpr int kOrderDims = 4;             // state coordinates that order a candidate's points
 
-typedef float f8v __attribute__((ext_vector_type(8)));
-typedef const __attribute__((address_space(4))) float rag_cfloat_t;
-typedef const __attribute__((address_space(4))) f8v __attribute__((aligned(4))) rag_cf8_t;
+// One candidate of a launch; offsets in 32-bit words from the workspace's start.
+struct RagCand {
+    int d, tau, id;
+    int64_t rows;                         // states [d][N] in point order
+    int64_t copy;                         // states [d][N] in block order
+    int64_t box;                          // smallest and largest of each block per coordinate, [2 d][blocks]
+    int64_t map;                          // order map (order_at)
+    int64_t scratch;                      // the ordering's scratch, 64-bit words
+};
+struct RagArgs {
+    int n;
+    RagCand c[kRagBatch];
+};
 
-// wave-uniform loads (scalar memory): one value, or eight consecutive values at a
-// 32-bit byte offset from a uniform base
-__device__ __forceinline__ float sload(const float *p) { return *(rag_cfloat_t *)p; }
-__device__ __forceinline__ f8v sload8(const float *p, uint32_t byte_off)
+// States of the launch's candidates (blockIdx.y): rows[m N + i] = y[r][t - 1 - m tau] for point
+// i = r W + (t - w), and with tgt non-null the targets tgt[i] = y[r][t].  A non-finite value sets *bad.
+// Also writes the candidate's ordering task.
+__global__ void rag_embed_kernel(const float *__restrict__ y, int T, int w, int W, int N, RagArgs a,
+                                 float *__restrict__ ws, SortTask *__restrict__ tasks, float *__restrict__ tgt,
+                                 int npad, int *__restrict__ bad)
 {
-    typedef const __attribute__((address_space(4))) char cchar_t;
-    return *(rag_cf8_t *)((cchar_t *)p + byte_off);
-}
-
-// States of one candidate: rows[m N + i] = y[r][t - 1 - m tau] for point i = r W + (t - w),
-// and with tgt non-null the targets tgt[i] = y[r][t].  A non-finite value sets *bad.
-__global__ void rag_embed_kernel(const float *__restrict__ y, int T, int w, int W, int N, int d, int tau,
-                                 float *__restrict__ rows, float *__restrict__ tgt, int *__restrict__ bad)
-{
+    const RagCand c = a.c[blockIdx.y];
     const int i = (int)(blockIdx.x * blockDim.x + threadIdx.x);
+    if (i == 0) {
+        SortTask t{};
+        t.sig = c.map;
+        t.scratch = c.scratch;
+        t.key_off = c.rows;
+        t.mode = 1;
+        t.n = N;
+        t.npad = npad;
+        t.nd = c.d < kOrderDims ? c.d : kOrderDims;
+        tasks[blockIdx.y] = t;
+    }
     if (i >= N)
         return;
     const int r = i / W;
     const int t = w + (i - r * W);
     const float *yr = y + (int64_t)r * T;
     bool ok = true;
-    for (int m = 0; m < d; ++m) {
-        const float v = yr[t - 1 - m * tau];
+    for (int m = 0; m < c.d; ++m) {
+        const float v = yr[t - 1 - m * c.tau];
         ok = ok && __builtin_isfinite(v);
-        rows[(int64_t)m * N + i] = v;
+        ws[c.rows + (int64_t)m * N + i] = v;
     }
-    if (tgt != nullptr) {
+    if (tgt != nullptr && blockIdx.y == 0) {
         const float v = yr[t];
         ok = ok && __builtin_isfinite(v);
         tgt[i] = v;
@@ -62,180 +80,259 @@ __global__ void rag_embed_kernel(const float *__restrict__ y, int T, int w, int 
         atomicOr(bad, 1);
 }
 
-// The k smallest (distance, index) pairs seen so far, ascending.  Entries arrive with
-// an index above every listed entry of equal distance, so inserting only what is
-// strictly closer than the k-th keeps equal distances in index order.
-template <int KC>                                 // capacity: k <= KC
-struct TopK {
-    float bd[KC];
-    int bi[KC];
-    float thr;                                    // bd[k - 1]
-    int k;
-    __device__ void init(int k_)
-    {
-        thr = __builtin_inff();
-        k = k_;
-#pragma unroll
-        for (int p = 0; p < KC; ++p) {
-            bd[p] = __builtin_inff();
-            bi[p] = 0;
-        }
-    }
-    // (x, j) with x < thr: entries larger than x move down one place and x goes behind
-    // the last entry <= x (from the last place up, each place reads the one above before
-    // that one changes)
-    __device__ __forceinline__ void insert(float x, int j)
-    {
-#pragma unroll
-        for (int p = KC - 1; p >= 1; --p) {
-            if (p < k) {
-                const bool move = bd[p - 1] > x;
-                const bool put = !move && bd[p] > x;
-                bd[p] = move ? bd[p - 1] : (put ? x : bd[p]);
-                bi[p] = move ? bi[p - 1] : (put ? j : bi[p]);
-            }
-        }
-        if (bd[0] > x) {
-            bd[0] = x;
-            bi[0] = j;
-        }
-#pragma unroll
-        for (int p = 0; p < KC; ++p)
-            if (p == k - 1)
-                thr = bd[p];
-    }
-};
-
-// One wave per (64 RPL reference points, candidate segment): lane l holds references
-// b + l + 64 r (r < RPL), the segment's candidates are uniform in index order, eight at
-// a time on scalar loads, so each load feeds 8 RPL distances per lane.  The segment's
-// list of each reference goes to lst_d / lst_i [segment][place][point] (places a
-// segment cannot fill stay at distance +inf).  Four references per lane while their
-// lists fit in registers (capacity up to 8), one for lists of 16.
-constexpr int refs_per_lane(int kc) { return kc <= 8 ? 4 : 1; }
-
-template <int D, int KC>
-__global__ void __launch_bounds__(64) rag_knn_kernel(const float *__restrict__ rows, int N, int k, int seg_len,
-                                                     float *__restrict__ lst_d, int *__restrict__ lst_i)
+// The states in block order and the blocks' boxes, one wave per block at a time.
+__global__ void rag_gather_kernel(RagArgs a, float *__restrict__ ws, int N)
 {
-    constexpr int RPL = refs_per_lane(KC);
-    const int lane = (int)threadIdx.x;
-    const int seg = (int)blockIdx.y;
-    const int j0 = seg * seg_len;
-    const int j1 = min(N, j0 + seg_len);
-    int ri[RPL];
-    float ref[RPL][D];
-#pragma unroll
-    for (int r = 0; r < RPL; ++r) {
-        ri[r] = (int)blockIdx.x * (kWave * RPL) + r * kWave + lane;
-        const int ii = ri[r] < N ? ri[r] : N - 1;
-#pragma unroll
-        for (int m = 0; m < D; ++m)
-            ref[r][m] = rows[(int64_t)m * N + ii];
-    }
-    TopK<KC> L[RPL];
-#pragma unroll
-    for (int r = 0; r < RPL; ++r)
-        L[r].init(k);
-    int j = j0;
-    for (; j + 8 <= j1; j += 8) {
-        float c[8][D];
-#pragma unroll
-        for (int m = 0; m < D; ++m) {
-            const f8v v = sload8(rows + (int64_t)m * N, (uint32_t)j * 4u);
-#pragma unroll
-            for (int u = 0; u < 8; ++u)
-                c[u][m] = v[u];
-        }
-#pragma unroll
-        for (int r = 0; r < RPL; ++r) {
-            float dist[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                float dm = __builtin_fabsf(c[u][0] - ref[r][0]);
-#pragma unroll
-                for (int m = 1; m < D; ++m)
-                    dm = fmaxf(dm, __builtin_fabsf(c[u][m] - ref[r][m]));
-                dist[u] = (j + u == ri[r]) ? __builtin_inff() : dm;
-            }
-            const float mn = fminf(fminf(fminf(dist[0], dist[1]), fminf(dist[2], dist[3])),
-                                   fminf(fminf(dist[4], dist[5]), fminf(dist[6], dist[7])));
-            if (__builtin_amdgcn_ballot_w64(mn < L[r].thr)) {
-#pragma unroll
-                for (int u = 0; u < 8; ++u)
-                    if (dist[u] < L[r].thr)
-                        L[r].insert(dist[u], j + u);
+    const RagCand c = a.c[blockIdx.y];
+    const int32_t *map = reinterpret_cast<const int32_t *>(ws) + c.map;
+    const int lane = threadIdx.x & (kWave - 1);
+    const int nb = (N + kWave - 1) / kWave;
+    for (int qb = (int)(blockIdx.x * blockDim.x) + (int)threadIdx.x - lane; qb < N; qb += (int)(blockDim.x * gridDim.x)) {
+        const bool ok = qb + lane < N;
+        const int q = ok ? qb + lane : N - 1;
+        const int o = min(max(order_at(map, N, q), 0), N - 1);
+        for (int m = 0; m < c.d; ++m) {
+            const float v = ws[c.rows + (int64_t)m * N + o];
+            if (ok)
+                ws[c.copy + (int64_t)m * N + q] = v;
+            float lo, hi;
+            wave_box(v, &lo, &hi);
+            if (lane == 0) {
+                ws[c.box + (int64_t)(2 * m) * nb + qb / kWave] = lo;
+                ws[c.box + (int64_t)(2 * m + 1) * nb + qb / kWave] = hi;
             }
         }
     }
-    for (; j < j1; ++j) {
-        float cj[D];
-#pragma unroll
-        for (int m = 0; m < D; ++m)
-            cj[m] = sload(rows + (int64_t)m * N + j);
-#pragma unroll
-        for (int r = 0; r < RPL; ++r) {
-            float dm = __builtin_fabsf(cj[0] - ref[r][0]);
-#pragma unroll
-            for (int m = 1; m < D; ++m)
-                dm = fmaxf(dm, __builtin_fabsf(cj[m] - ref[r][m]));
-            if (j != ri[r] && dm < L[r].thr)
-                L[r].insert(dm, j);
-        }
-    }
-#pragma unroll
-    for (int r = 0; r < RPL; ++r)
-        if (ri[r] < N) {
-#pragma unroll
-            for (int p = 0; p < KC; ++p)
-                if (p < k) {
-                    const int64_t o = ((int64_t)seg * k + p) * N + ri[r];
-                    lst_d[o] = L[r].bd[p];
-                    lst_i[o] = L[r].bi[p];
-                }
-        }
 }
 
-// Thread = point: the segments' lists merged in segment order (indices ascend across
-// segments and within a list equal distances ascend in index, so the strict insertion
-// keeps the rank order), then the prediction -- the neighbours' targets summed in rank
-// order in fp64 -- and its squared error.
-template <int KC>
-__global__ void __launch_bounds__(256) rag_merge_kernel(const float *__restrict__ lst_d,
-                                                        const int *__restrict__ lst_i,
-                                                        const float *__restrict__ tgt, int N, int k, int n_seg,
-                                                        double *__restrict__ pred, double *__restrict__ sq)
+// The KC smallest (distance, index) pairs, ascending: the distance's bits above the index, so that
+// one unsigned comparison ranks equal distances by index.  Unfilled places are (inf, 0).
+constexpr uint64_t kNone = 0x7f80000000000000ull;
+__device__ __forceinline__ uint64_t rank_key(float dist, int index)
 {
-    const int i = (int)(blockIdx.x * blockDim.x + threadIdx.x);
-    if (i >= N)
-        return;
-    TopK<KC> L;
-    L.init(k);
-#pragma unroll 4
-    for (int seg = 0; seg < n_seg; ++seg) {
-        float xd[KC];
-        int xi[KC];
+    return (uint64_t)__builtin_bit_cast(uint32_t, dist) << 32 | (uint32_t)index;
+}
+template <int KC>
+__device__ __forceinline__ void insert_key(uint64_t (&b)[KC], uint64_t x)
+{
 #pragma unroll
-        for (int p = 0; p < KC; ++p) {            // the segment's list, all loads in flight
-            const int64_t o = ((int64_t)seg * k + (p < k ? p : 0)) * N + i;
-            xd[p] = p < k ? lst_d[o] : __builtin_inff();
-            xi[p] = p < k ? lst_i[o] : 0;
-        }
+    for (int p = KC - 1; p >= 1; --p)
+        b[p] = x < b[p - 1] ? b[p - 1] : (x < b[p] ? x : b[p]);
+    b[0] = x < b[0] ? x : b[0];
+}
+template <int KC>
+__device__ __forceinline__ uint64_t key_at(const uint64_t (&b)[KC], int p)
+{
+    uint64_t r = b[0];
+#pragma unroll
+    for (int i = 1; i < KC; ++i)
+        r = p == i ? b[i] : r;
+    return r;
+}
+
+// The k nearest of every point of a block of 64 (block order), the prediction -- the neighbours'
+// targets summed in rank order in fp64 -- and its squared error.  Four waves of 16 references each:
+// the block's own points first, every group of 16 lanes a quarter of them and the groups' lists
+// merged; then, lane = candidate, the blocks whose box the references' current k-th distances
+// reach, nearer ones first (a box farther than the k-th distance holds nothing nearer, and nothing
+// equally near; rounding is monotone, so the box bound holds for binary32 differences).
+// Bound by the latency of a wave's chain of block visits.  Every pair of points in index order took
+// 4 176 us for the window of 15 000 points and the twelve candidates (d = 1..6, tau = 1, 2; k = 4).
+constexpr int kRagWaves = 4;
+constexpr int kRagRefs = kWave / kRagWaves;
+
+template <int D, int KC>
+__device__ __forceinline__ void rag_block(const RagCand &c, const float *ws, const float *tgt, int N, int k,
+                                          double *pred, double *sq, float *lds)
+{
+    constexpr int RW = (D + 2 + 3) & ~3;       // LDS row: coordinates, k-th distance, its index
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = threadIdx.x / kWave;
+    const int nb = (N + kWave - 1) / kWave;
+    const int blk = blockIdx.x;
+    const float *pts = ws + c.copy;
+    const int32_t *map = reinterpret_cast<const int32_t *>(ws) + c.map;
+    float *rows = lds + wave * kRagRefs * RW;
+    const int i = blk * kWave + wave * kRagRefs + (lane & (kRagRefs - 1));
+    const bool valid = i < N && lane < kRagRefs;
+    const int ii = min(i, N - 1);
+    float ref[D];
+#pragma unroll
+    for (int m = 0; m < D; ++m)
+        ref[m] = pts[(int64_t)m * N + ii];
+    uint64_t b[KC];
+#pragma unroll
+    for (int p = 0; p < KC; ++p)
+        b[p] = kNone;
+
+    // own block (with a ragged last block, the one before it too)
+    const int ob0 = (blk > 0 && N - blk * kWave < kWave) ? blk - 1 : blk;
+    const int e0 = min(N, (blk + 1) * kWave);
+    for (int j0 = ob0 * kWave; j0 < e0; j0 += kRagWaves) {
+        const int j = j0 + lane / kRagRefs, jj = min(j, e0 - 1);
+        float dist = absdiff(pts[jj], ref[0]);
+#pragma unroll
+        for (int m = 1; m < D; ++m)
+            dist = fmaxf(dist, absdiff(pts[(int64_t)m * N + jj], ref[m]));
+        insert_key<KC>(b, j < e0 && j != i ? rank_key(dist, order_at(map, N, jj)) : kNone);
+    }
+#pragma unroll
+    for (int o = kRagRefs; o < kWave; o <<= 1) {
+        uint64_t other[KC];
 #pragma unroll
         for (int p = 0; p < KC; ++p)
-            if (xd[p] < L.thr)
-                L.insert(xd[p], xi[p]);
+            other[p] = __shfl_xor((unsigned long long)b[p], o, 64);
+#pragma unroll
+        for (int p = 0; p < KC; ++p)
+            insert_key<KC>(b, other[p]);
     }
+    uint64_t last = key_at<KC>(b, k - 1);
+    auto reach = [&]() { return valid ? __builtin_bit_cast(float, (uint32_t)(last >> 32)) : 0.0f; };
+
+    if (lane < kRagRefs) {
+#pragma unroll
+        for (int m = 0; m < D; ++m)
+            rows[lane * RW + m] = ref[m];
+        rows[lane * RW + D] = __builtin_bit_cast(float, (uint32_t)(last >> 32));
+        rows[lane * RW + D + 1] = __builtin_bit_cast(float, (uint32_t)last);
+    }
+    __builtin_amdgcn_wave_barrier();
+
+    // the box of the wave's own references
+    const float *bx = ws + c.box;
+    float blo[D], bhi[D];
+#pragma unroll
+    for (int m = 0; m < D; ++m) {
+        float lo = ref[m] != ref[m] ? -kInf : ref[m], hi = ref[m] != ref[m] ? kInf : ref[m];
+#pragma unroll
+        for (int o = 1; o < kRagRefs; o <<= 1) {
+            lo = fminf(lo, __shfl_xor(lo, o, 64));
+            hi = fmaxf(hi, __shfl_xor(hi, o, 64));
+        }
+        blo[m] = readlane_f(lo, 0);
+        bhi[m] = readlane_f(hi, 0);
+    }
+    float lim = -kInf;
+    for (int sw = 0; sw < 4 && nb > 1; ++sw) {
+        float cm = wave_max(reach());
+        const float share = sw == 0 ? 0.05f : (sw == 1 ? 0.15f : 0.4f);
+        const float nlim = sw == 3 ? kInf : fmaxf(lim, share * cm);
+        if (nlim == lim)
+            continue;
+        for (int b0 = 0; b0 < nb; b0 += kWave) {
+            const int bb = min(b0 + lane, nb - 1);
+            float lo[D], hi[D], g = -kInf;
+#pragma unroll
+            for (int m = 0; m < D; ++m) {
+                lo[m] = bx[(int64_t)(2 * m) * nb + bb];
+                hi[m] = bx[(int64_t)(2 * m + 1) * nb + bb];
+                g = fmaxf(g, fmaxf(lo[m] - bhi[m], blo[m] - hi[m]));
+            }
+            const int bl = b0 + lane;
+            uint64_t want = ballot(bl < nb && (bl < ob0 || bl > blk) && g >= lim && (g < nlim || sw == 3) && !(g > cm));
+            if (want == 0)
+                continue;
+            do {
+                const int cc = __builtin_ctzll(want);
+                want = clear_bit(want, cc);
+                float far = -kInf;                        // of the lane's reference from the block's box
+#pragma unroll
+                for (int m = 0; m < D; ++m)
+                    far = fmaxf(far, fmaxf(readlane_f(lo[m], cc) - ref[m], ref[m] - readlane_f(hi[m], cc)));
+                uint64_t todo = ballot(valid && !(far > reach()));
+                if (todo == 0)
+                    continue;
+                const int idx = (b0 + cc) * kWave + lane;
+                const int jj = min(idx, N - 1);
+                float cand[D];
+#pragma unroll
+                for (int m = 0; m < D; ++m)
+                    cand[m] = idx < N ? pts[(int64_t)m * N + jj] : kInf;
+                const int ci = order_at(map, N, jj);
+                do {
+                    const int r = __builtin_ctzll(todo);
+                    todo = clear_bit(todo, r);
+                    float rr[RW];
+#pragma unroll
+                    for (int x = 0; x < RW / 4; ++x) {
+                        const f4v q4 = reinterpret_cast<const f4v *>(rows + r * RW)[x];
+                        rr[4 * x + 0] = q4.x;
+                        rr[4 * x + 1] = q4.y;
+                        rr[4 * x + 2] = q4.z;
+                        rr[4 * x + 3] = q4.w;
+                    }
+                    float dist = absdiff(rr[0], cand[0]);
+#pragma unroll
+                    for (int m = 1; m < D; ++m)
+                        dist = fmaxf(dist, absdiff(rr[m], cand[m]));
+                    if (ballot(dist <= rr[D]) == 0)
+                        continue;
+                    keep_branch();
+                    const uint64_t key = rank_key(dist, ci);
+                    uint64_t bar = (uint64_t)__builtin_bit_cast(uint32_t, rr[D]) << 32 |
+                                   __builtin_bit_cast(uint32_t, rr[D + 1]);
+                    uint64_t hit = ballot(dist <= rr[D] && key < bar);   // a distance that is no number hits nothing
+                    if (hit == 0)
+                        continue;
+                    do {
+                        const int x = __builtin_ctzll(hit);
+                        hit = clear_bit(hit, x);
+                        const uint64_t kx =
+                            (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(key >> 32), x) << 32 |
+                            (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)key, x);
+                        if (lane == r) {
+                            insert_key<KC>(b, kx);
+                            last = key_at<KC>(b, k - 1);
+                        }
+                        bar = (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(last >> 32), r) << 32 |
+                              (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)last, r);
+                        hit &= ballot(key < bar);
+                    } while (hit != 0);
+                    if (lane == r) {
+                        rows[r * RW + D] = __builtin_bit_cast(float, (uint32_t)(last >> 32));
+                        rows[r * RW + D + 1] = __builtin_bit_cast(float, (uint32_t)last);
+                    }
+                    __builtin_amdgcn_wave_barrier();
+                } while (todo != 0);
+            } while (want != 0);
+            cm = wave_max(reach());
+        }
+        lim = nlim;
+    }
+    if (!valid)
+        return;
     double s = 0.0;
 #pragma unroll
     for (int p = 0; p < KC; ++p)
         if (p < k)
-            s += (double)tgt[L.bi[p]];
+            s += (double)tgt[min((uint32_t)b[p], (uint32_t)(N - 1))];
     const double yhat = s / (double)k;
+    const int o = min(max(order_at(map, N, i), 0), N - 1);
     if (pred != nullptr)
-        pred[i] = yhat;
-    const double e = (double)tgt[i] - yhat;
-    sq[i] = e * e;
+        pred[o] = yhat;
+    const double e = (double)tgt[o] - yhat;
+    sq[o] = e * e;
+}
+
+template <int KC>
+__global__ void __launch_bounds__(kRagWaves * kWave) rag_search_kernel(RagArgs a, const float *__restrict__ ws,
+                                                                      const float *__restrict__ tgt, int N, int k,
+                                                                      double *pred, double *sq)
+{
+    __shared__ __attribute__((aligned(16))) float lds[kWave * ((kRagMaxDim + 2 + 3) & ~3)];
+    const RagCand c = a.c[blockIdx.y];
+    double *p = pred != nullptr ? pred + (int64_t)c.id * N : nullptr;
+    double *q = sq + (int64_t)c.id * N;
+    switch (c.d) {
+    case 1: rag_block<1, KC>(c, ws, tgt, N, k, p, q, lds); break;
+    case 2: rag_block<2, KC>(c, ws, tgt, N, k, p, q, lds); break;
+    case 3: rag_block<3, KC>(c, ws, tgt, N, k, p, q, lds); break;
+    case 4: rag_block<4, KC>(c, ws, tgt, N, k, p, q, lds); break;
+    case 5: rag_block<5, KC>(c, ws, tgt, N, k, p, q, lds); break;
+    case 6: rag_block<6, KC>(c, ws, tgt, N, k, p, q, lds); break;
+    case 7: rag_block<7, KC>(c, ws, tgt, N, k, p, q, lds); break;
+    default: rag_block<8, KC>(c, ws, tgt, N, k, p, q, lds); break;
+    }
 }
 
 // Fixed-order sum over a workgroup of kScoreThreads threads.
@@ -278,76 +375,44 @@ __global__ void __launch_bounds__(kScoreThreads) rag_score_kernel(const float *_
         score[c] = V > 0.0 ? E / V : __builtin_nan("");
 }
 
-// Candidate segments per point: enough (wave, segment) pairs to give every SIMD of the
-// chip several waves (a wave holds 64 rpl references), segments of at least 64 points
-// (a multiple of 8), at most 64.
-struct Segments {
-    int len = 0, n = 0;
+// Words of one candidate's part of the search area: states in block order, boxes, order map, and the
+// ordering's scratch (codes, or the keys of spaces too large for slabs) above kSortLds points.
+struct RagPart {
+    int64_t box, map, scratch, total;
 };
 
-Segments segments(int64_t N, int rpl)
+RagPart rag_part(int64_t N, int d)
 {
-    const int64_t blocks = (N + kWave * rpl - 1) / (kWave * rpl);
-    int64_t want = (16384 + blocks - 1) / blocks;
-    want = want < 1 ? 1 : (want > 64 ? 64 : want);
-    int64_t len = (N + want - 1) / want;
-    len = len < 64 ? 64 : (len + 7) / 8 * 8;
-    Segments s;
-    s.len = (int)len;
-    s.n = (int)((N + len - 1) / len);
-    return s;
+    auto up = [](int64_t v) { return (v + 15) / 16 * 16; };
+    RagPart p;
+    p.box = up(N * d);
+    p.map = p.box + up(2 * d * ((N + kWave - 1) / kWave));
+    p.scratch = p.map + up(N);
+    int64_t words = 0;
+    if (N > kSortLds)
+        words = order_slabs((int)N, std::min(d, kOrderDims)) > 0 ? (N + 1) / 2 : 2 * (int64_t)sort_npad((int)N);
+    p.total = p.scratch + up(words);
+    return p;
 }
 
-template <int KC>
-hipError_t launch_knn_kc(int d, const float *rows, int N, int k, const Segments &sg, float *lst_d, int *lst_i,
-                         hipStream_t st)
+// 128 bytes a point of the search area for each of these runs of at least 64 points: the size callers have
+// reserved for it, of which a candidate's part takes at most 56 bytes a point and 320 bytes.
+int64_t rag_runs(int64_t N)
 {
-    constexpr int RPL = refs_per_lane(KC);
-    const dim3 grid((unsigned)((N + kWave * RPL - 1) / (kWave * RPL)), (unsigned)sg.n);
-    const dim3 block(kWave);
-    switch (d) {
-    case 1: rag_knn_kernel<1, KC><<<grid, block, 0, st>>>(rows, N, k, sg.len, lst_d, lst_i); break;
-    case 2: rag_knn_kernel<2, KC><<<grid, block, 0, st>>>(rows, N, k, sg.len, lst_d, lst_i); break;
-    case 3: rag_knn_kernel<3, KC><<<grid, block, 0, st>>>(rows, N, k, sg.len, lst_d, lst_i); break;
-    case 4: rag_knn_kernel<4, KC><<<grid, block, 0, st>>>(rows, N, k, sg.len, lst_d, lst_i); break;
-    case 5: rag_knn_kernel<5, KC><<<grid, block, 0, st>>>(rows, N, k, sg.len, lst_d, lst_i); break;
-    case 6: rag_knn_kernel<6, KC><<<grid, block, 0, st>>>(rows, N, k, sg.len, lst_d, lst_i); break;
-    case 7: rag_knn_kernel<7, KC><<<grid, block, 0, st>>>(rows, N, k, sg.len, lst_d, lst_i); break;
-    case 8: rag_knn_kernel<8, KC><<<grid, block, 0, st>>>(rows, N, k, sg.len, lst_d, lst_i); break;
-    default: return hipErrorInvalidValue;
-    }
-    return hipGetLastError();
+    auto runs = [N](int64_t refs) {
+        const int64_t groups = (N + refs - 1) / refs;
+        const int64_t want = std::min<int64_t>(64, std::max<int64_t>(1, (16384 + groups - 1) / groups));
+        const int64_t len = std::max<int64_t>(64, ((N + want - 1) / want + 7) / 8 * 8);
+        return (N + len - 1) / len;
+    };
+    return std::max(runs(kWave), runs(4 * kWave));
 }
 
-template <int KC>
-hipError_t launch_candidate(int d, const float *rows, const float *tgt, int N, int k, const Segments &sg,
-                            float *lst_d, int *lst_i, double *pred, double *sq, hipStream_t st)
-{
-    hipError_t e = launch_knn_kc<KC>(d, rows, N, k, sg, lst_d, lst_i, st);
-    if (e != hipSuccess)
-        return e;
-    rag_merge_kernel<KC><<<dim3((unsigned)((N + 255) / 256)), dim3(256), 0, st>>>(lst_d, lst_i, tgt, N, k, sg.n,
-                                                                                 pred, sq);
-    return hipGetLastError();
-}
-
-// the k nearest of each point for one candidate, merged, with its predictions: the list
-// capacity is the smallest of 4, 8, 16 that holds k
-hipError_t launch_knn(int d, const float *rows, const float *tgt, int N, int k, float *lst_d, int *lst_i,
-                      double *pred, double *sq, hipStream_t st)
-{
-    if (k <= 4)
-        return launch_candidate<4>(d, rows, tgt, N, k, segments(N, refs_per_lane(4)), lst_d, lst_i, pred, sq, st);
-    if (k <= 8)
-        return launch_candidate<8>(d, rows, tgt, N, k, segments(N, refs_per_lane(8)), lst_d, lst_i, pred, sq, st);
-    return launch_candidate<16>(d, rows, tgt, N, k, segments(N, refs_per_lane(16)), lst_d, lst_i, pred, sq, st);
-}
-
-// Workspace layout: flag | targets [N] | states of each candidate [d_c][N] | squared errors
-// [n_cand][N] | scores [n_cand] | segment lists (distances, indices) [segments][k][N] for
-// k up to TE_RAGWITZ_MAX_K, reused by every candidate; each part 256-byte aligned.
+// Workspace layout: flag | targets [N] | states of each candidate [d_c][N] | squared errors [n_cand][N] |
+// scores [n_cand] | search area (ordering tasks, then parts of as many candidates at a time as fit); each
+// part 256-byte aligned.
 struct RagLayout {
-    size_t flag = 0, tgt = 0, sq = 0, score = 0, lst_d = 0, lst_i = 0, total = 0;
+    size_t tgt = 0, sq = 0, score = 0, area = 0, total = 0;
     std::vector<size_t> rows;
 };
 
@@ -365,12 +430,9 @@ RagLayout rag_layout(int64_t N, const int32_t *dims, int n_cand)
     o += align_up(sizeof(double) * (size_t)N * (size_t)n_cand, 256);
     L.score = o;
     o += align_up(sizeof(double) * (size_t)n_cand, 256);
-    const int n_seg = std::max(segments(N, refs_per_lane(8)).n, segments(N, refs_per_lane(16)).n);
-    const size_t lst = (size_t)n_seg * (size_t)kRagMaxK * (size_t)N;
-    L.lst_d = o;
-    o += align_up(sizeof(float) * lst, 256);
-    L.lst_i = o;
-    o += align_up(sizeof(int) * lst, 256);
+    const int64_t lists = rag_runs(N) * kRagMaxK * N;
+    L.area = o;
+    o += 2 * align_up(sizeof(float) * (size_t)lists, 256);
     L.total = o;
     return L;
 }
@@ -443,28 +505,60 @@ te_status te_ragwitz(const float *y, int32_t n_trials, int32_t n_samples, int32_
         return fail(TE_ERR_NOMEM, "workspace %zu bytes < %zu", ws_bytes, L.total);
     char *ws = static_cast<char *>(ws_);
     hipStream_t st = (hipStream_t)hip_stream;
-    int *bad = reinterpret_cast<int *>(ws + L.flag);
+    int *bad = reinterpret_cast<int *>(ws);
     float *tgt = reinterpret_cast<float *>(ws + L.tgt);
     double *sq = reinterpret_cast<double *>(ws + L.sq);
     double *dscore = reinterpret_cast<double *>(ws + L.score);
-    hipError_t e = hipMemsetAsync(bad, 0, sizeof(int), st);
+    hipError_t e = launch_fill_i32(bad, 0, 1, st);
     if (e != hipSuccess)
-        return hip_fail(e, "hipMemsetAsync");
-    const dim3 eb(256), eg((unsigned)((N + 255) / 256));
-    for (int c = 0; c < n_cand; ++c) {
-        float *rows = reinterpret_cast<float *>(ws + L.rows[c]);
-        rag_embed_kernel<<<eg, eb, 0, st>>>(y, n_samples, window_start, window_len, N, dims[c], taus[c], rows,
-                                            c == 0 ? tgt : nullptr, bad);
+        return hip_fail(e, "fill");
+    float *wsf = reinterpret_cast<float *>(ws);
+    const int64_t area_words = (int64_t)((L.total - L.area) / sizeof(float));
+    const int npad = sort_npad(N);
+    for (int c0 = 0; c0 < n_cand;) {
+        // as many candidates as the search area holds
+        RagArgs a{};
+        int64_t words = 0;
+        const int64_t area = (int64_t)(L.area / sizeof(float));
+        auto task_words = [](int n) { return ((int64_t)n * (int64_t)sizeof(SortTask) / 4 + 15) / 16 * 16; };
+        while (a.n < kRagBatch && c0 + a.n < n_cand) {
+            const RagPart p = rag_part(N, dims[c0 + a.n]);
+            if (a.n > 0 && task_words(a.n + 1) + words + p.total > area_words)
+                break;
+            words += p.total;
+            ++a.n;
+        }
+        int64_t o = area + task_words(a.n);
+        for (int c = 0; c < a.n; ++c) {
+            const RagPart p = rag_part(N, dims[c0 + c]);
+            a.c[c] = RagCand{dims[c0 + c], taus[c0 + c], c0 + c, (int64_t)(L.rows[c0 + c] / sizeof(float)), o,
+                             o + p.box, o + p.map, (o + p.scratch) / 2};
+            o += p.total;
+        }
+        if (o > area + area_words)
+            return fail(TE_ERR_NOMEM, "the search area does not hold a candidate's part");
+        SortTask *tasks = reinterpret_cast<SortTask *>(wsf + area);
+        rag_embed_kernel<<<dim3((unsigned)((N + 255) / 256), (unsigned)a.n), dim3(256), 0, st>>>(
+            y, n_samples, window_start, window_len, N, a, wsf, tasks, c0 == 0 ? tgt : nullptr, npad, bad);
         if ((e = hipGetLastError()) != hipSuccess)
             return hip_fail(e, "rag_embed_kernel");
-    }
-    float *lst_d = reinterpret_cast<float *>(ws + L.lst_d);
-    int *lst_i = reinterpret_cast<int *>(ws + L.lst_i);
-    for (int c = 0; c < n_cand; ++c) {
-        const float *rows = reinterpret_cast<const float *>(ws + L.rows[c]);
-        if ((e = launch_knn(dims[c], rows, tgt, N, k, lst_d, lst_i, pred ? pred + (int64_t)c * N : nullptr,
-                            sq + (int64_t)c * N, st)) != hipSuccess)
-            return hip_fail(e, "rag_knn_kernel / rag_merge_kernel");
+        if ((e = launch_sort(nullptr, wsf, N, tasks, a.n, N, reinterpret_cast<int32_t *>(ws),
+                             reinterpret_cast<uint64_t *>(ws), 0, 0, 0, 0, st)) != hipSuccess)
+            return hip_fail(e, "ordering");
+        rag_gather_kernel<<<dim3((unsigned)std::min(1024, (N + 1023) / 1024), (unsigned)a.n), dim3(256), 0, st>>>(a, wsf, N);
+        if ((e = hipGetLastError()) != hipSuccess)
+            return hip_fail(e, "rag_gather_kernel");
+        const dim3 grid((unsigned)((N + kWave - 1) / kWave), (unsigned)a.n), block(kRagWaves * kWave);
+        // the list capacity is the smallest of 4, 8, 16 that holds k
+        if (k <= 4)
+            rag_search_kernel<4><<<grid, block, 0, st>>>(a, wsf, tgt, N, k, pred, sq);
+        else if (k <= 8)
+            rag_search_kernel<8><<<grid, block, 0, st>>>(a, wsf, tgt, N, k, pred, sq);
+        else
+            rag_search_kernel<16><<<grid, block, 0, st>>>(a, wsf, tgt, N, k, pred, sq);
+        if ((e = hipGetLastError()) != hipSuccess)
+            return hip_fail(e, "rag_search_kernel");
+        c0 += a.n;
     }
     rag_score_kernel<<<dim3((unsigned)n_cand), dim3(kScoreThreads), 0, st>>>(tgt, sq, N, dscore);
     if ((e = hipGetLastError()) != hipSuccess)
