@@ -355,6 +355,7 @@ te_status Plan::build_group_batch(const std::vector<int> &groups, int n_surr, Ba
                 pt.point = c;
                 pt.surr = s - 1;
                 b->perm_tasks.push_back(pt);
+                b->max_rc = std::max(b->max_rc, trials[c]);
                 b->n_perm += trials[c];
                 t.perm = pt.dst;
             }
@@ -485,7 +486,7 @@ te_status Plan::enqueue_batch(const Batch &b, const float *x, const float *y, co
     if (!b.perm_tasks.empty()) {
         // the caller's permutations (copied and checked) or ones drawn from the seed
         e = launch_perms(perms, reinterpret_cast<const PermTask *>(ws + b.off_ptasks), (int)b.perm_tasks.size(),
-                         parea, p.seed, ctr + 1, st);
+                         b.max_rc, parea, p.seed, ctr + 1, st);
         if (e != hipSuccess)
             return hip_fail(e, "permutation launch");
     }
@@ -785,7 +786,8 @@ te_status te_plan_permutations(te_plan plan, void *ws, size_t ws_bytes, void *hi
     if (e == hipSuccess)
         e = launch_fill_i32(err, 0, 1, st);
     if (e == hipSuccess)
-        e = launch_perms(nullptr, reinterpret_cast<const PermTask *>(d), (int)rows.size(), perms, P.p.seed, err, st);
+        e = launch_perms(nullptr, reinterpret_cast<const PermTask *>(d), (int)rows.size(), P.full.max_rc, perms,
+                         P.p.seed, err, st);
     int32_t *herr = reinterpret_cast<int32_t *>(stg + tbytes);
     if (e == hipSuccess)
         e = hipMemcpyAsync(herr, err, sizeof(int32_t), hipMemcpyDeviceToHost, st);

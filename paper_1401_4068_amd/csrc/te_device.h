@@ -221,27 +221,10 @@ __device__ __forceinline__ int find_chunk(const int32_t *item_start, int n_chunk
     return lo;
 }
 
-// Box of a wave's 64 values: their smallest and largest, in every lane; unbounded if one is no
-// number (its distances then say nothing, so nothing may be skipped for them).
-__device__ __forceinline__ void wave_box(float v, float *lo, float *hi)
+// Largest of the wave's values, uniform: DPP row shifts, then the row broadcasts (no LDS).
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t x)
 {
-    float a = v != v ? -kInf : v, b = v != v ? kInf : v;
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) {
-        a = fminf(a, __shfl_xor(a, o, 64));
-        b = fmaxf(b, __shfl_xor(b, o, 64));
-    }
-    *lo = a;
-    *hi = b;
-}
-
-// Largest of the wave's values, uniform: DPP row shifts, then the row broadcasts.
-// The values are non-negative floats, whose bit patterns order like unsigned integers.
-__device__ __forceinline__ float wave_max(float f)
-{
-    int x = __builtin_bit_cast(int, f);
-#define TE_STEP(ctrl, rows) \
-    x = (int)max((uint32_t)x, (uint32_t)__builtin_amdgcn_update_dpp(0, x, ctrl, rows, 0xf, false))
+#define TE_STEP(ctrl, rows) x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, ctrl, rows, 0xf, false))
     TE_STEP(0x111, 0xf);   // row_shr:1, 2, 4, 8: the row's largest in its last lane
     TE_STEP(0x112, 0xf);
     TE_STEP(0x114, 0xf);
@@ -249,7 +232,44 @@ __device__ __forceinline__ float wave_max(float f)
     TE_STEP(0x142, 0xa);   // row_bcast:15
     TE_STEP(0x143, 0xc);   // row_bcast:31
 #undef TE_STEP
-    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(x, kWave - 1));
+    return (uint32_t)__builtin_amdgcn_readlane((int)x, kWave - 1);
+}
+// The same for non-negative floats, whose bit patterns order like unsigned integers.
+__device__ __forceinline__ float wave_max(float f)
+{
+    return __builtin_bit_cast(float, wave_max_u32(__builtin_bit_cast(uint32_t, f)));
+}
+// Inclusive sum over the lanes up to this one.
+__device__ __forceinline__ uint32_t wave_scan(uint32_t x)
+{
+#define TE_STEP(ctrl, rows) x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, ctrl, rows, 0xf, false)
+    TE_STEP(0x111, 0xf);   // row_shr:1, 2, 4, 8
+    TE_STEP(0x112, 0xf);
+    TE_STEP(0x114, 0xf);
+    TE_STEP(0x118, 0xf);
+    TE_STEP(0x142, 0xa);   // row_bcast:15
+    TE_STEP(0x143, 0xc);   // row_bcast:31
+#undef TE_STEP
+    return x;
+}
+
+// Order-preserving unsigned image of a float (negative values reversed), and back.
+__device__ __forceinline__ uint32_t orderable(float f)
+{
+    const uint32_t u = __builtin_bit_cast(uint32_t, f);
+    return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+}
+__device__ __forceinline__ float from_orderable(uint32_t u)
+{
+    return __builtin_bit_cast(float, (u & 0x80000000u) ? (u & 0x7fffffffu) : ~u);
+}
+
+// Box of a wave's 64 values: their smallest and largest, uniform; unbounded if one is no
+// number (its distances then say nothing, so nothing may be skipped for them).
+__device__ __forceinline__ void wave_box(float v, float *lo, float *hi)
+{
+    *lo = from_orderable(~wave_max_u32(~orderable(v != v ? -kInf : v)));
+    *hi = from_orderable(wave_max_u32(orderable(v != v ? kInf : v)));
 }
 
 }  // namespace

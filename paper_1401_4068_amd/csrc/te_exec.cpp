@@ -414,7 +414,7 @@ te_status Plan::estimate_each(const float *x, const float *y, const int32_t *per
                           hipSuccess)
             break;
         if (n_surr > 0 &&
-            (e = launch_perms(perms, dp + (int64_t)g * n_surr, n_surr, parea, p.seed, gerr, st)) != hipSuccess)
+            (e = launch_perms(perms, dp + (int64_t)g * n_surr, n_surr, trials[c], parea, p.seed, gerr, st)) != hipSuccess)
             break;
         for (int s = 0; s < S1 && e == hipSuccess; ++s) {
             const int64_t ci = (int64_t)g * S1 + s;

@@ -195,8 +195,8 @@ hipError_t launch_sort(const float *y, const float *pts, int64_t ld, const SortT
 hipError_t launch_gather(const float *src, const GatherTask *tasks, int n_tasks, int max_n, int32_t *sigma,
                          uint64_t *scratch, float *dst, int D, int d_y, hipStream_t st);
 // Fill a batch's permutation area: copy (and check) the caller's rows when src is
-// given, else draw every row from `seed`.  Sets bit 2 of *err for an invalid row.
-hipError_t launch_perms(const int32_t *src, const PermTask *tasks, int n_tasks, int32_t *dst,
+// given, else draw every row (of at most max_rc trials) from `seed`.  Sets bit 2 of *err for an invalid row.
+hipError_t launch_perms(const int32_t *src, const PermTask *tasks, int n_tasks, int max_rc, int32_t *dst,
                         uint64_t seed, int32_t *err, hipStream_t st);
 hipError_t launch_search(const SearchArgs &a, int d_y, int d_x, const SearchConfig &cfg, int grid_waves,
                          hipStream_t st);

@@ -402,13 +402,6 @@ __global__ void embed_kernel(const float *__restrict__ x, const float *__restric
         atomicOr(err, 1);
 }
 
-// Order-preserving unsigned image of a float (negative values reversed).
-__device__ __forceinline__ uint32_t orderable(float f)
-{
-    const uint32_t u = __builtin_bit_cast(uint32_t, f);
-    return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
-}
-
 // One bitonic compare-exchange pass with stride jj inside stage kk over the
 // len elements of A (LDS tile or global array).  offset: global index of A[0],
 // so the sort direction is that of the full network.  Workgroup-wide: every
@@ -527,24 +520,15 @@ constexpr int kOrderEach = kSlabMax / kOrderThreads;   // points per thread at m
 // Smallest and largest of the workgroup's values (red: 2 x kOrderWaves words of LDS).
 __device__ __forceinline__ void block_range(uint32_t &lo, uint32_t &hi, uint32_t *red)
 {
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) {
-        lo = min(lo, (uint32_t)__shfl_xor((int)lo, o, 64));
-        hi = max(hi, (uint32_t)__shfl_xor((int)hi, o, 64));
-    }
     const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
+    uint32_t a = ~wave_max_u32(~lo), b = wave_max_u32(hi);
     if (lane == 0) {
-        red[w] = lo;
-        red[kOrderWaves + w] = hi;
+        red[w] = a;
+        red[kOrderWaves + w] = b;
     }
     __syncthreads();
-    lo = red[lane & (kOrderWaves - 1)];
-    hi = red[kOrderWaves + (lane & (kOrderWaves - 1))];
-#pragma unroll
-    for (int o = kOrderWaves / 2; o >= 1; o >>= 1) {
-        lo = min(lo, (uint32_t)__shfl_xor((int)lo, o, 64));
-        hi = max(hi, (uint32_t)__shfl_xor((int)hi, o, 64));
-    }
+    lo = ~wave_max_u32(~red[lane & (kOrderWaves - 1)]);
+    hi = wave_max_u32(red[kOrderWaves + (lane & (kOrderWaves - 1))]);
     __syncthreads();
 }
 
@@ -558,14 +542,16 @@ __device__ __forceinline__ int code_shift(uint32_t lo, uint32_t hi, int bits)
 template <int BITS>
 __device__ __forceinline__ uint64_t match_digit(uint32_t d, bool active)
 {
-    uint64_t m = ballot(active);
+    const uint64_t act = ballot(active);
+    uint32_t lo = (uint32_t)act, hi = (uint32_t)(act >> 32);
 #pragma unroll
     for (int b = 0; b < BITS; ++b) {
-        const bool one = (d >> b) & 1u;
-        const uint64_t mb = ballot(one);
-        m &= one ? mb : ~mb;
+        const uint32_t one = (uint32_t)((int32_t)(d << (31 - b)) >> 31);   // all ones where the bit is set
+        const uint64_t mb = ballot(one != 0);
+        lo &= ~((uint32_t)mb ^ one);
+        hi &= ~((uint32_t)(mb >> 32) ^ one);
     }
-    return m;
+    return (uint64_t)hi << 32 | lo;
 }
 
 __device__ __forceinline__ int rank_in(uint64_t m)
@@ -586,13 +572,7 @@ __device__ __forceinline__ void scan_digits(uint32_t *cnt, uint32_t *part)
             c[v] = cnt[v * DIGITS + t];
             own += c[v];
         }
-    uint32_t inc = own;
-#pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) {
-        const uint32_t v = (uint32_t)__shfl_up((int)inc, o, 64);
-        if (lane >= o)
-            inc += v;
-    }
+    const uint32_t inc = wave_scan(own);                  // inclusive
     if (lane == kWave - 1)
         part[w] = inc;
     __syncthreads();
@@ -641,18 +621,36 @@ __global__ void __launch_bounds__(kOrderThreads) split_kernel(CoordSource src, c
         hist[i] = 0;
     for (int i = t; i < kOrderWaves * kClasses; i += kOrderThreads)
         cnt[i] = 0;
+    // eight loads in flight per thread: a workgroup alone on its CU waits for each round of them
+    constexpr int U = 8;
     uint32_t lo = ~0u, hi = 0;
-    for (int i = t; i < n; i += kOrderThreads) {
-        const uint32_t o = orderable(src.at(tk, i, 0));
-        lo = min(lo, o);
-        hi = max(hi, o);
+    for (int i0 = t; i0 < n; i0 += U * kOrderThreads) {
+        uint32_t o[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            o[u] = orderable(src.at(tk, min(i0 + u * kOrderThreads, n - 1), 0));
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            lo = min(lo, o[u]);
+            hi = max(hi, o[u]);
+        }
     }
     block_range(lo, hi, part);
     const int shift = code_shift(lo, hi, kCodeBits);
-    for (int i = t; i < n; i += kOrderThreads) {
-        const uint32_t c = (orderable(src.at(tk, i, 0)) - lo) >> shift;
-        code[i] = (uint16_t)c;
-        atomicAdd(&hist[c], 1u);
+    for (int i0 = t; i0 < n; i0 += U * kOrderThreads) {
+        uint32_t o[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            o[u] = orderable(src.at(tk, min(i0 + u * kOrderThreads, n - 1), 0));
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int i = i0 + u * kOrderThreads;
+            if (i < n) {
+                const uint32_t c = (o[u] - lo) >> shift;
+                code[i] = (uint16_t)c;
+                atomicAdd(&hist[c], 1u);
+            }
+        }
     }
     __syncthreads();
     // thread t owns 32 consecutive codes: the code of each cut, then the class of every code
@@ -660,13 +658,7 @@ __global__ void __launch_bounds__(kOrderThreads) split_kernel(CoordSource src, c
     uint32_t own = 0;
     for (int e = 0; e < kOwn; ++e)
         own += hist[t * kOwn + e];
-    uint32_t inc = own;
-#pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) {
-        const uint32_t v = (uint32_t)__shfl_up((int)inc, o, 64);
-        if (lane >= o)
-            inc += v;
-    }
+    const uint32_t inc = wave_scan(own);                  // inclusive
     if (lane == kWave - 1)
         part[w] = inc;
     __syncthreads();
@@ -708,14 +700,28 @@ __global__ void __launch_bounds__(kOrderThreads) split_kernel(CoordSource src, c
     // stable counting sort by class: wave w takes a contiguous run of points
     const int run = ((n + kOrderThreads - 1) / kOrderThreads) * kWave;
     const int i1 = min(n, (w + 1) * run);
-    for (int i = w * run + lane; i < i1; i += kWave)
-        atomicAdd(&cnt[w * kClasses + hist[code[i]]], 1u);
+    for (int i0 = w * run + lane; i0 < i1; i0 += U * kWave) {
+        uint32_t c[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            c[u] = code[min(i0 + u * kWave, n - 1)];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (i0 + u * kWave < i1)
+                atomicAdd(&cnt[w * kClasses + hist[c[u]]], 1u);
+    }
     __syncthreads();
     scan_digits<kClasses>(cnt, part);
-    for (int i0 = w * run; i0 < i1; i0 += kWave) {
-        const int i = i0 + lane;
+    for (int j0 = w * run; j0 < i1; j0 += U * kWave) {
+      uint32_t cc[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+          cc[u] = code[min(j0 + u * kWave + lane, n - 1)];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int i = j0 + u * kWave + lane;
         const bool ok = i < i1;
-        const uint32_t c = ok ? hist[code[i]] : 0u;
+        const uint32_t c = ok ? hist[cc[u]] : 0u;
         const uint64_t m = match_digit<7>(c, ok);
         if (ok) {
             const int r = rank_in(m);
@@ -729,6 +735,7 @@ __global__ void __launch_bounds__(kOrderThreads) split_kernel(CoordSource src, c
                 cnt[w * kClasses + c] = at + (uint32_t)__builtin_popcountll(m);
         }
         __builtin_amdgcn_wave_barrier();
+      }
     }
 }
 
@@ -1011,10 +1018,12 @@ __global__ void take_perms_kernel(const int32_t *__restrict__ src, const PermTas
 // output: m = w (i + 1), j_i = m >> 32, rejected when (m mod 2^32) < 2^32 mod (i+1).
 // Draws are made in rounds: in round one draw t takes output t; each later round
 // gives the draws rejected so far, in draw order, the next unused outputs.
-// One wave per row: the rounds run across lanes, the swaps on one lane in LDS
-// (rows of up to kDrawLds trials) or in the destination row itself (longer rows).
+// The swaps are resolved in parallel (draw_perms_kernel); rows of more than kDrawShared trials, and
+// rows with a rejected draw (about one in two thousand of 2 000 trials), by one wave: the rounds
+// across lanes, the swaps in order on one lane (draw_row).
 constexpr uint64_t kGolden = 0x9E3779B97F4A7C15ull;
-constexpr int kDrawLds = 8192;
+constexpr int kDrawShared = 6144;         // 10 bytes of LDS per trial
+constexpr int kDrawThreads = 256;
 constexpr int kMaxRejects = 256;
 
 __device__ __forceinline__ uint64_t mix64(uint64_t z)
@@ -1037,29 +1046,23 @@ __device__ __forceinline__ int lemire_draw(uint64_t key, uint64_t q, uint32_t s)
     return (int)(m >> 32);
 }
 
-__global__ void __launch_bounds__(64) draw_perms_kernel(const PermTask *__restrict__ tasks, int32_t *__restrict__ dst,
-                                                        uint64_t seed, int32_t *err)
+__device__ __forceinline__ uint64_t row_key(uint64_t seed, const PermTask &tk)
 {
-    __shared__ int32_t lds_perm[kDrawLds];
-    __shared__ int32_t pend[2][kMaxRejects];
-    __shared__ int32_t fix_t[kMaxRejects], fix_j[kMaxRejects];
-    const PermTask tk = tasks[blockIdx.x];
-    const int lane = threadIdx.x;
-    const int n = tk.rc;
-    int32_t *row = dst + tk.dst;
-    if (n < 1 || n > kMaxPermTrials) {
-        for (int r = lane; r < tk.len; r += kWave)
-            row[r] = r;
-        if (lane == 0)
-            atomicOr(err, 2);
-        return;
-    }
     uint64_t key = 0x5EED5EED5EED5EEDull;
     key = fold_key(key, seed);
     key = fold_key(key, 77ull);
     key = fold_key(key, (uint64_t)(int64_t)tk.pair);
     key = fold_key(key, (uint64_t)(int64_t)tk.point);
-    key = fold_key(key, (uint64_t)(int64_t)tk.surr);
+    return fold_key(key, (uint64_t)(int64_t)tk.surr);
+}
+
+// One wave draws a row and makes its swaps in order, in the row itself.
+__device__ void draw_row(const PermTask &tk, int32_t *row, uint64_t key, int32_t *err)
+{
+    __shared__ int32_t pend[2][kMaxRejects];
+    __shared__ int32_t fix_t[kMaxRejects], fix_j[kMaxRejects];
+    const int lane = threadIdx.x & (kWave - 1);
+    const int n = tk.rc;
     const int draws = n - 1;
     const uint64_t lanes_below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
 
@@ -1114,7 +1117,7 @@ __global__ void __launch_bounds__(64) draw_perms_kernel(const PermTask *__restri
         overflow = nfix > kMaxRejects || npend > kMaxRejects;
     }
     if (overflow) {
-        for (int r = lane; r < tk.len; r += kWave)
+        for (int r = lane; r < n; r += kWave)
             row[r] = r;
         if (lane == 0)
             atomicOr(err, 2);
@@ -1122,9 +1125,8 @@ __global__ void __launch_bounds__(64) draw_perms_kernel(const PermTask *__restri
     }
     __builtin_amdgcn_wave_barrier();
     // the swaps, in order, on one lane
-    int32_t *a = n <= kDrawLds ? lds_perm : row;
     for (int r = lane; r < n; r += kWave)
-        a[r] = r;
+        row[r] = r;
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -1138,19 +1140,88 @@ __global__ void __launch_bounds__(64) draw_perms_kernel(const PermTask *__restri
                         j = fix_j[f];
             if (j < 0 || j > i)              // cannot happen: every rejected draw has a fix
                 j = i;
-            const int32_t vi = a[i], vj = a[j];
-            a[i] = vj;
-            a[j] = vi;
+            const int32_t vi = row[i], vj = row[j];
+            row[i] = vj;
+            row[j] = vi;
         }
     }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    if (n <= kDrawLds)
-        for (int r = lane; r < n; r += kWave)
-            row[r] = lds_perm[r];
-    for (int r = n + lane; r < tk.len; r += kWave)
+}
+
+// One workgroup per row.  What position i holds in the end is what position j_i held when step i
+// swapped them (steps run from i = n-1 down): the entry that the last earlier step i' > i with
+// j_i' = j_i had put there, or j_i itself; step i' had put there what position i' held then, and so
+// on.  With next(p) = the smallest step i > p with j_i = p, that is
+//   a[i] = end(s) for s = the smallest step above i with j_s = j_i, or j_i if there is none,
+// end(p) following next() to its end; a[0] = end(0).  The steps of equal j are chained by exchanges in
+// LDS (in any order: only minima are taken from a chain), chains and paths being a few steps long.
+// Bound by LDS latency.  One lane making the swaps in order took 1 240 us for 30 windows x 100 rows of
+// up to 5 000 trials.
+__global__ void __launch_bounds__(kDrawThreads) draw_perms_kernel(const PermTask *__restrict__ tasks,
+                                                                  int32_t *__restrict__ dst, uint64_t seed, int32_t *err)
+{
+    extern __shared__ __attribute__((aligned(16))) char draw_lds[];
+    __shared__ int32_t rejected;
+    constexpr uint16_t kEnd = 0xffff;
+    const PermTask tk = tasks[blockIdx.x];
+    const int n = tk.rc, tid = threadIdx.x;
+    int32_t *row = dst + tk.dst;
+    const bool too_big = n < 1 || n > kMaxPermTrials;
+    for (int r = too_big ? tid : n + tid; r < tk.len; r += kDrawThreads)
         row[r] = r;
+    if (too_big) {
+        if (tid == 0)
+            atomicOr(err, 2);
+        return;
+    }
+    const uint64_t key = row_key(seed, tk);
+    if (n > kDrawShared) {
+        if (tid < kWave)
+            draw_row(tk, row, key, err);
+        return;
+    }
+    int32_t *head = reinterpret_cast<int32_t *>(draw_lds);
+    uint16_t *j = reinterpret_cast<uint16_t *>(head + n), *chain = j + n, *next = chain + n;
+    if (tid == 0)
+        rejected = 0;
+    __syncthreads();
+    bool rej = false;
+    for (int i = tid; i < n; i += kDrawThreads) {
+        head[i] = kEnd;
+        const int d = i > 0 ? lemire_draw(key, (uint64_t)(n - 1 - i), (uint32_t)(i + 1)) : 0;
+        rej |= d < 0;
+        j[i] = (uint16_t)max(d, 0);
+    }
+    if (rej)
+        rejected = 1;
+    __syncthreads();
+    if (rejected) {
+        if (tid < kWave)
+            draw_row(tk, row, key, err);
+        return;
+    }
+    for (int i = tid; i < n; i += kDrawThreads)
+        if (i > 0)
+            chain[i] = (uint16_t)atomicExch(&head[j[i]], i);
+    __syncthreads();
+    // the smallest step above i in the chain of position p
+    auto above = [&](int p, int i) {
+        int best = kEnd;
+        for (int s = head[p]; s != kEnd; s = chain[s])
+            best = s > i ? min(best, s) : best;
+        return best;
+    };
+    for (int p = tid; p < n; p += kDrawThreads)
+        next[p] = (uint16_t)above(p, p);
+    __syncthreads();
+    for (int i = tid; i < n; i += kDrawThreads) {
+        const int p = i > 0 ? (int)j[i] : 0;
+        int s = above(p, i), v = p;
+        while (s != kEnd) {
+            v = s;
+            s = next[s];
+        }
+        row[i] = v;
+    }
 }
 
 // p-value of window group g (eq. 10 test): the fraction of its n_surr surrogate
@@ -1334,14 +1405,21 @@ hipError_t launch_fill_i32(int32_t *p, int32_t v, int64_t n, hipStream_t st)
     return hipGetLastError();
 }
 
+// Workgroups per task of the kernels that take a task's points 256 at a time: one round each while that
+// leaves the launch small (its time is then one round's latency), else four or more.
+static int point_parts(int n_tasks, int max_n)
+{
+    const int rounds = (max_n + 255) / 256;
+    return std::max(1, std::min(1024, (int64_t)n_tasks * rounds <= 4096 ? rounds : (rounds + 3) / 4));
+}
+
 hipError_t launch_embed(const float *x, const float *y, const int32_t *perms, int32_t *sigma, uint64_t *scratch,
                         const int32_t *u_dev, const EmbedTask *tasks, int n_tasks, int max_n, float *base, int R,
                         int T, int d_y, int d_x, int tau, int u, int cond, int32_t *err, hipStream_t st)
 {
     if (n_tasks <= 0)
         return hipSuccess;
-    // a few hundred to a few thousand points per workgroup, so small batches still fill the GPU
-    const int parts = std::max(1, std::min(1024, (max_n + 1023) / 1024));
+    const int parts = point_parts(n_tasks, max_n);
     hipLaunchKernelGGL(embed_kernel, dim3(n_tasks, parts), dim3(256), 0, st, x, y, perms, sigma, scratch, u_dev, tasks, base,
                        R, T, d_y, d_x, tau, u, cond, err);
     return hipGetLastError();
@@ -1385,12 +1463,12 @@ hipError_t launch_gather(const float *src, const GatherTask *tasks, int n_tasks,
 {
     if (n_tasks <= 0)
         return hipSuccess;
-    const int parts = std::max(1, std::min(1024, (max_n + 1023) / 1024));
+    const int parts = point_parts(n_tasks, max_n);
     hipLaunchKernelGGL(gather_kernel, dim3(n_tasks, parts), dim3(256), 0, st, src, tasks, sigma, scratch, dst, D, d_y);
     return hipGetLastError();
 }
 
-hipError_t launch_perms(const int32_t *src, const PermTask *tasks, int n_tasks, int32_t *dst,
+hipError_t launch_perms(const int32_t *src, const PermTask *tasks, int n_tasks, int max_rc, int32_t *dst,
                         uint64_t seed, int32_t *err, hipStream_t st)
 {
     if (n_tasks <= 0)
@@ -1398,7 +1476,8 @@ hipError_t launch_perms(const int32_t *src, const PermTask *tasks, int n_tasks, 
     if (src != nullptr)
         hipLaunchKernelGGL(take_perms_kernel, dim3(n_tasks), dim3(256), 0, st, src, tasks, dst, err);
     else
-        hipLaunchKernelGGL(draw_perms_kernel, dim3(n_tasks), dim3(kWave), 0, st, tasks, dst, seed, err);
+        hipLaunchKernelGGL(draw_perms_kernel, dim3(n_tasks), dim3(kDrawThreads),
+                           (size_t)10 * std::max(0, std::min(max_rc, kDrawShared)) + 16, st, tasks, dst, seed, err);
     return hipGetLastError();
 }
 

@@ -53,6 +53,7 @@ struct Batch {
     std::vector<int32_t> item_start;
     std::vector<EmbedTask> tasks;
     std::vector<PermTask> perm_tasks;     // one per surrogate chunk: its trial permutation
+    int max_rc = 0;                       // trials of the longest of them
     int64_t n_perm = 0;                   // int32 entries of the batch's permutation area
     std::vector<SortTask> sorts;          // one per window group (empty when chunks are not sorted)
     int64_t n_sigma = 0;                  // int32 entries of the sorted-to-original maps

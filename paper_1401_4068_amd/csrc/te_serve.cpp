@@ -434,7 +434,7 @@ bool Server::admit_one(Job *j)
     int32_t *perm = reinterpret_cast<int32_t *>(bat + b.off_perm);
     if (e == hipSuccess && !b.perm_tasks.empty())
         e = launch_perms(j->n_perm ? reinterpret_cast<const int32_t *>(reg + j->off_perm) : nullptr,
-                         reinterpret_cast<const PermTask *>(bat + b.off_ptasks), (int)b.perm_tasks.size(), perm,
+                         reinterpret_cast<const PermTask *>(bat + b.off_ptasks), (int)b.perm_tasks.size(), b.max_rc, perm,
                          P.p.seed, ctr + 1, setup_stream);
     int32_t *sigma = reinterpret_cast<int32_t *>(bat + b.off_sigma);
     if (e == hipSuccess)
