@@ -120,16 +120,6 @@ __device__ __forceinline__ void insert_key(uint64_t (&b)[KC], uint64_t x)
         b[p] = x < b[p - 1] ? b[p - 1] : (x < b[p] ? x : b[p]);
     b[0] = x < b[0] ? x : b[0];
 }
-template <int KC>
-__device__ __forceinline__ uint64_t key_at(const uint64_t (&b)[KC], int p)
-{
-    uint64_t r = b[0];
-#pragma unroll
-    for (int i = 1; i < KC; ++i)
-        r = p == i ? b[i] : r;
-    return r;
-}
-
 // The k nearest of every point of a block of 64 (block order), the prediction -- the neighbours'
 // targets summed in rank order in fp64 -- and its squared error.  Four waves of 16 references each:
 // the block's own points first, every group of 16 lanes a quarter of them and the groups' lists
@@ -161,9 +151,11 @@ __device__ __forceinline__ void rag_block(const RagCand &c, const float *ws, con
     for (int m = 0; m < D; ++m)
         ref[m] = pts[(int64_t)m * N + ii];
     uint64_t b[KC];
+    // a list longer than k starts with zeros, which nothing displaces: its last entry is the k-th
+    const int fill = KC - k;
 #pragma unroll
     for (int p = 0; p < KC; ++p)
-        b[p] = kNone;
+        b[p] = p < fill ? 0 : kNone;
 
     // own block (with a ragged last block, the one before it too)
     const int ob0 = (blk > 0 && N - blk * kWave < kWave) ? blk - 1 : blk;
@@ -184,9 +176,10 @@ __device__ __forceinline__ void rag_block(const RagCand &c, const float *ws, con
             other[p] = __shfl_xor((unsigned long long)b[p], o, 64);
 #pragma unroll
         for (int p = 0; p < KC; ++p)
-            insert_key<KC>(b, other[p]);
+            if (p >= fill)
+                insert_key<KC>(b, other[p]);
     }
-    uint64_t last = key_at<KC>(b, k - 1);
+    uint64_t &last = b[KC - 1];
     auto reach = [&]() { return valid ? __builtin_bit_cast(float, (uint32_t)(last >> 32)) : 0.0f; };
 
     if (lane < kRagRefs) {
@@ -247,7 +240,8 @@ __device__ __forceinline__ void rag_block(const RagCand &c, const float *ws, con
                 float cand[D];
 #pragma unroll
                 for (int m = 0; m < D; ++m)
-                    cand[m] = idx < N ? pts[(int64_t)m * N + jj] : kInf;
+                    cand[m] = pts[(int64_t)m * N + jj];
+                cand[0] = idx < N ? cand[0] : kInf;
                 const int ci = order_at(map, N, jj);
                 do {
                     const int r = __builtin_ctzll(todo);
@@ -280,10 +274,8 @@ __device__ __forceinline__ void rag_block(const RagCand &c, const float *ws, con
                         const uint64_t kx =
                             (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(key >> 32), x) << 32 |
                             (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)key, x);
-                        if (lane == r) {
+                        if (lane == r)
                             insert_key<KC>(b, kx);
-                            last = key_at<KC>(b, k - 1);
-                        }
                         bar = (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(last >> 32), r) << 32 |
                               (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)last, r);
                         hit &= ballot(key < bar);
@@ -304,7 +296,7 @@ __device__ __forceinline__ void rag_block(const RagCand &c, const float *ws, con
     double s = 0.0;
 #pragma unroll
     for (int p = 0; p < KC; ++p)
-        if (p < k)
+        if (p >= fill)
             s += (double)tgt[min((uint32_t)b[p], (uint32_t)(N - 1))];
     const double yhat = s / (double)k;
     const int o = min(max(order_at(map, N, i), 0), N - 1);

@@ -140,21 +140,17 @@ __device__ __forceinline__ void block_search(const SearchArgs &a)
                 rs[v][m] = vload_at(row(sb[v], m), moff[m] + (uint32_t)ii * 4u);
         // The k+1 smallest joint distances of the lane's reference per variant, itself
         // included (distance 0): the radius is the (k+1)-th, the k-th neighbour without self.
+        // A list longer than that starts with zeros, which nothing displaces, so the radius is
+        // always its last entry.
+        const int fill = GENERIC ? KP1 - 1 - k : 0;
         float best[V][KP1];
-        float thr[V];                                  // GENERIC: the current (k+1)-th
 #pragma unroll
-        for (int v = 0; v < V; ++v) {
-            thr[v] = kInf;
+        for (int v = 0; v < V; ++v)
 #pragma unroll
             for (int s = 0; s < KP1; ++s)
-                best[v][s] = kInf;
-        }
-        auto cur = [&](int v) { return GENERIC ? thr[v] : best[v][KP1 - 1]; };
-        auto insert = [&](int v, float x) {
-            insert_sorted<KP1>(best[v], x);
-            if (GENERIC)
-                thr[v] = kth<KP1, GENERIC>(best[v], k);
-        };
+                best[v][s] = s < fill ? 0.0f : kInf;
+        auto cur = [&](int v) { return best[v][KP1 - 1]; };
+        auto insert = [&](int v, float x) { insert_sorted<KP1>(best[v], x); };
         // largest current radius over the variants (0 in lanes past the chunk's end): a
         // candidate at least that far away is of no use to any variant
         auto curmax = [&]() {
@@ -198,22 +194,25 @@ __device__ __forceinline__ void block_search(const SearchArgs &a)
                 prow[lane * RW + DT + V * DX + v] = cur(v);
             __builtin_amdgcn_wave_barrier();
         };
-        // block b's candidates, one per lane (coordinates +inf past the chunk's end: outside every ball)
+        // Block b's candidates, one per lane; past the chunk's end the last point moved to +inf, outside
+        // every ball: in all coordinates where a reference may be infinite itself (pre-embedded points),
+        // else in one.  (Added, not selected: back to back, selects on VCC issue one in 23 clocks.)
         auto load_block = [&](int b, float (&ct)[DT], float (&cs)[V][DX]) {
             const int idx = b * kWave + lane;
             const bool ok = idx < n;
             const uint32_t ic4 = (uint32_t)(ok ? idx : n - 1) * 4u;
+            const float away = ok ? 0.0f : kInf;
 #pragma unroll
             for (int m = 0; m < DT; ++m) {
                 const float x = vload_at(row(tb, m), moff[m] + ic4);
-                ct[m] = ok ? x : kInf;
+                ct[m] = OUT || m == 1 ? x + away : x;
             }
 #pragma unroll
             for (int v = 0; v < V; ++v)
 #pragma unroll
                 for (int m = 0; m < DX; ++m) {
                     const float x = vload_at(row(sb[v], m), moff[m] + ic4);
-                    cs[v][m] = ok ? x : kInf;
+                    cs[v][m] = OUT ? x + away : x;
                 }
         };
         // lane = reference: every lane's reference (lt, ls) against the candidates whose rows are in LDS,
@@ -289,13 +288,14 @@ __device__ __forceinline__ void block_search(const SearchArgs &a)
 #pragma unroll
                     for (int m = 1; m < DT; ++m)
                         dtp = fmaxf(dtp, absdiff(rt[m], vload_at(row(tb, m), moff[m] + j4)));
+                    dtp = j < e0 ? dtp : kInf;
 #pragma unroll
                     for (int v = 0; v < V; ++v) {
                         float d = absdiff(rs[v][0], vload_at(row(sb[v], 0), moff[0] + j4));
 #pragma unroll
                         for (int m = 1; m < DX; ++m)
                             d = fmaxf(d, absdiff(rs[v][m], vload_at(row(sb[v], m), moff[m] + j4)));
-                        dj[u][v] = j < e0 ? fmaxf(dtp, d) : kInf;
+                        dj[u][v] = fmaxf(dtp, d);
                     }
                 }
 #pragma unroll
@@ -314,12 +314,9 @@ __device__ __forceinline__ void block_search(const SearchArgs &a)
                         other[s] = __shfl_xor(best[v][s], o, 64);
 #pragma unroll
                     for (int s = 0; s < KP1; ++s)
-                        insert_sorted<KP1>(best[v], other[s]);
+                        if (s >= fill)
+                            insert_sorted<KP1>(best[v], other[s]);
                 }
-            if (GENERIC)
-#pragma unroll
-                for (int v = 0; v < V; ++v)
-                    thr[v] = kth<KP1, GENERIC>(best[v], k);
             store_row(rt, rs);
         } else {
             store_row(rt, rs);
