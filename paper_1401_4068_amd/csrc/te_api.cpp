@@ -185,6 +185,11 @@ void Batch::finish_layout()
     o = align_up(o + sizeof(int32_t) * part_start.size(), 16);
     off_sets = o;
     o = align_up(o + sizeof(int32_t) * set_first.size(), 16);
+    // error word and reduce counter, then the XCD queue counters: zeros that travel with the tables
+    off_ctr = align_up(o, 16);
+    o = off_ctr + sizeof(int32_t) * 4;
+    off_qctr = o;
+    o = align_up(o + sizeof(int32_t) * kQueues, 16);
     tables_bytes = o - off_tables;
     off_partial = align_up(o, 256);
     o = off_partial + sizeof(double) * (size_t)std::max<int64_t>(n_partials, 1);
@@ -195,11 +200,6 @@ void Batch::finish_layout()
     o = off_pv + sizeof(double) * (size_t)std::max(n_groups, 1);
     off_errout = o;
     o = off_errout + sizeof(double);
-    // error word and reduce counter, then the XCD queue counters: one fill
-    off_ctr = align_up(o, 256);
-    o = off_ctr + sizeof(int32_t) * 4;
-    off_qctr = o;
-    o = off_qctr + sizeof(int32_t) * kQueues;
     off_sigma = align_up(o, 256);
     o = off_sigma + sizeof(int32_t) * (size_t)n_sigma;
     off_perm = align_up(o, 256);
@@ -476,11 +476,9 @@ te_status Plan::enqueue_batch(const Batch &b, const float *x, const float *y, co
     e = hipMemcpyAsync(ws + b.off_tables, tables_src, b.tables_bytes, hipMemcpyHostToDevice, st);
     if (e != hipSuccess)
         return hip_fail(e, "upload tables");
-    // ctr: [1] error word, [2] finished reduce workgroups; the queue counters follow
+    // ctr: [1] error word, [2] finished reduce workgroups; the queue counters follow (zero in the upload)
     int32_t *ctr = reinterpret_cast<int32_t *>(ws + b.off_ctr);
     int32_t *qctr = reinterpret_cast<int32_t *>(ws + b.off_qctr);
-    if ((e = launch_fill_i32(ctr, 0, 4 + kQueues, st)) != hipSuccess)
-        return hip_fail(e, "fill");
     float *base = reinterpret_cast<float *>(ws + b.off_coords);
     int32_t *parea = reinterpret_cast<int32_t *>(ws + b.off_perm);
     if (!b.perm_tasks.empty()) {

@@ -15,8 +15,6 @@ typedef const __attribute__((address_space(4))) float cfloat_t;
 typedef const __attribute__((address_space(4))) int32_t cint_t;
 typedef const __attribute__((address_space(4))) int64_t cint64_t;
 typedef const __attribute__((address_space(4))) f4v __attribute__((aligned(4))) cf4_t;
-typedef float f8v __attribute__((ext_vector_type(8)));
-typedef const __attribute__((address_space(4))) f8v __attribute__((aligned(4))) cf8_t;
 
 // Wave-uniform loads through the constant address space: the address is the
 // same in every lane, so these become scalar (SMEM) loads into SGPRs.  Only
@@ -24,22 +22,12 @@ typedef const __attribute__((address_space(4))) f8v __attribute__((aligned(4))) 
 // be lowered to vector-memory loads).
 __device__ __forceinline__ float uload(const float *p) { return *(cfloat_t *)p; }
 __device__ __forceinline__ f4v uload4(const float *p) { return *(cf4_t *)p; }
-__device__ __forceinline__ f8v uload8_at(const float *p, uint32_t byte_off)
-{
-    typedef const __attribute__((address_space(4))) char cchar_t;
-    return *(cf8_t *)((cchar_t *)p + byte_off);
-}
 // the same at a 32-bit byte offset from a wave-uniform base: one SGPR offset shared
 // by several bases, so the loads need no 64-bit address arithmetic
 __device__ __forceinline__ f4v uload4_at(const float *p, uint32_t byte_off)
 {
     typedef const __attribute__((address_space(4))) char cchar_t;
     return *(cf4_t *)((cchar_t *)p + byte_off);
-}
-__device__ __forceinline__ float uload_at(const float *p, uint32_t byte_off)
-{
-    typedef const __attribute__((address_space(4))) char cchar_t;
-    return *(cfloat_t *)((cchar_t *)p + byte_off);
 }
 // per-lane load at a 32-bit byte offset from a wave-uniform base: the base stays in
 // SGPRs and the offset in one VGPR (no 64-bit address per lane)

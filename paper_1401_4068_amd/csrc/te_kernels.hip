@@ -713,29 +713,29 @@ __global__ void __launch_bounds__(kOrderThreads) split_kernel(CoordSource src, c
     __syncthreads();
     scan_digits<kClasses>(cnt, part);
     for (int j0 = w * run; j0 < i1; j0 += U * kWave) {
-      uint32_t cc[U];
+        uint32_t cc[U];
 #pragma unroll
-      for (int u = 0; u < U; ++u)
-          cc[u] = code[min(j0 + u * kWave + lane, n - 1)];
+        for (int u = 0; u < U; ++u)
+            cc[u] = code[min(j0 + u * kWave + lane, n - 1)];
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int i = j0 + u * kWave + lane;
-        const bool ok = i < i1;
-        const uint32_t c = ok ? hist[cc[u]] : 0u;
-        const uint64_t m = match_digit<7>(c, ok);
-        if (ok) {
-            const int r = rank_in(m);
-            const uint32_t at = cnt[w * kClasses + c] + (uint32_t)r;
-            if (n <= kSortLds)
-                reinterpret_cast<uint16_t *>(map)[at] = (uint16_t)i;
-            else
-                map[at] = i;
+        for (int u = 0; u < U; ++u) {
+            const int i = j0 + u * kWave + lane;
+            const bool ok = i < i1;
+            const uint32_t c = ok ? hist[cc[u]] : 0u;
+            const uint64_t m = match_digit<7>(c, ok);
+            if (ok) {
+                const int r = rank_in(m);
+                const uint32_t at = cnt[w * kClasses + c] + (uint32_t)r;
+                if (n <= kSortLds)
+                    reinterpret_cast<uint16_t *>(map)[at] = (uint16_t)i;
+                else
+                    map[at] = i;
+                __builtin_amdgcn_wave_barrier();
+                if (r == 0)
+                    cnt[w * kClasses + c] = at + (uint32_t)__builtin_popcountll(m);
+            }
             __builtin_amdgcn_wave_barrier();
-            if (r == 0)
-                cnt[w * kClasses + c] = at + (uint32_t)__builtin_popcountll(m);
         }
-        __builtin_amdgcn_wave_barrier();
-      }
     }
 }
 

@@ -53,32 +53,26 @@ ordered_search pick_ordered(int d_y, int d_x, int k, int slots, bool sets, int w
 // every 6 clocks: the time is one block's chain of instructions.  W waves to a block cut that chain
 // by W, at the price of W walks over the boxes and of insertions for 64 / W references at a time.
 // Measured, us per call of one launch (persistent / W = 2 / 4 / 8):
-//   k = 4, 32 blocks (N = 2 000, D = 5)      181 /  - / 121 / 105
-//   k = 4, 640 blocks                        196 /  - / 134 / 129
-//   k = 4, 790 blocks (N = 5 000, D = 7)     471 / 373 / 335 / 352
-//   k = 4, 3 950 blocks                     1163 / 767 / 809 / 1024
-//   k = 4, 15 800 blocks                    1528 / 1263 / 1415 / 1870
-//   k = 4, 31 600 blocks                    2339 / 2334 / 2697 / 3630
+//   k = 4, 32 blocks (N = 2 000, D = 5)      174 /  - / 103 /  92
+//   k = 4, 750 blocks (N = 48 000, D = 7)    1152 / 804 / 624 / 575
+//   k = 4, 7 900 blocks (N = 5 000, D = 7)   1136 / 720 / 775 / 969
+//   k = 4, 31 600 blocks                     2339 / 2334 / 2697 / 3630
+//   k = 1, 940 / 3 760 / 24 400 blocks       224 / 159 / 134 / 140, 551 / 221 / 221 / 276, 1241 / 711 / 867 / 1201
+//   k = 6, 940 / 8 200 / 24 400 blocks       282 / 214 / 174 / 185, 890 / 521 / 549 / 765, 1306 / 1216 / 1366 / 2047
+//   k = 8, 940 / 8 200 / 24 400 blocks       299 / 234 / 188 / 189, 897 / 588 / 608 / 834, 1333 / 1392 / 1532 / 2254
+//   k = 12, 940 / 8 200 / 24 400 blocks      332 /  - / 238 /  - , 855 /  - / 823 /  - , 1425 /  - / 2124 /  -
 //   sets of four, 192 blocks (N = 2 000)     577 / 413 / 299 / 241
-//   sets of four, 832 blocks                 612 / 507 / 470 / 577
-//   sets of four, 1 632 blocks               702 / 746 / 677 / 930
+//   sets of four, 832 / 1 632 blocks         612 / 507 / 470 / 577, 702 / 746 / 677 / 930
 //   sets of four, 3 328 blocks               873 / 1111 / 1090 / 1673
-//   k = 1, 940 / 3 760 / 24 400 blocks       243 / 181 / 153 / 161, 579 / 249 / 252 / 302, 1328 / 835 / 1008 / 1589
-//   k = 6, 192 / 1 880 / 8 200 blocks        262 / 231 / 175 / 156, 416 / 434 / 406 / 421, 1111 / 1036 / 1044 / 1243
-//   k = 8, 192 / 940 / 1 880 blocks          276 / 272 / 192 / 169, 353 / 367 / 352 / 344, 436 / 550 / 531 / 527
-//   k = 12, 192 / 940 blocks                 343 / 398 / 283 / 282, 435 / 788 / 761 / 780
-// Longer lists make the W own-block scans and merges dearer, so their line lies lower.
 int waves_to_a_block(int64_t n_items, bool sets, int k)
 {
     if (sets)
         return n_items <= 512 ? 8 : (n_items <= 1536 ? 4 : 0);
-    if (k <= 4)
-        return n_items <= 512 ? 8 : (n_items <= (k == 4 ? 3072 : 1536) ? 4 : (n_items <= 24576 ? 2 : 0));
-    if (k <= 6)
-        return n_items <= 960 ? 8 : (n_items <= 4096 ? 4 : (n_items <= 8192 ? 2 : 0));
-    if (k <= 8)
-        return n_items <= 960 ? 8 : 0;
-    return n_items <= 384 ? 4 : 0;
+    if (k > 8)
+        return n_items <= 8192 ? 4 : 0;
+    if (n_items <= 832)
+        return 8;
+    return n_items <= 4096 ? 4 : (n_items <= (k <= 6 ? 24576 : 16384) ? 2 : 0);
 }
 
 // The search with w waves to a block (w from waves_to_a_block, not 0): one workgroup of w waves per item.

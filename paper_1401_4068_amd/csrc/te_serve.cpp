@@ -427,9 +427,7 @@ bool Server::admit_one(Job *j)
     std::memcpy(j->stage, tables.data(), b.tables_bytes);
     if (e == hipSuccess)
         e = hipMemcpyAsync(bat + b.off_tables, j->stage, b.tables_bytes, hipMemcpyHostToDevice, setup_stream);
-    int32_t *ctr = reinterpret_cast<int32_t *>(bat + b.off_ctr);
-    if (e == hipSuccess)
-        e = launch_fill_i32(ctr, 0, 4, setup_stream);
+    int32_t *ctr = reinterpret_cast<int32_t *>(bat + b.off_ctr);       // zero in the uploaded tables
     // the job's permutations: copied (and checked) from the uploaded ones, or drawn from its seed
     int32_t *perm = reinterpret_cast<int32_t *>(bat + b.off_perm);
     if (e == hipSuccess && !b.perm_tasks.empty())

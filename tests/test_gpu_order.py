@@ -87,7 +87,8 @@ def _repeated(points, S, k):
 
 
 @pytest.mark.parametrize("S,k,points", [(0, 4, (1, 50, 300, 2300)), (3, 4, (1, 100, 200)), (0, 3, (1, 100, 300, 2300)),
-                                        (0, 6, (1, 200, 500, 800)), (0, 8, (1, 100)), (0, 15, (1, 50))])
+                                        (0, 6, (1, 200, 500, 800)), (0, 8, (1, 100)), (0, 15, (1, 50)), (0, 4, (1, 600)),
+                                        (0, 8, (1, 1500, 1800))])
 def test_estimates_do_not_depend_on_the_waves_per_block(te, S, k, points):
     """The same window alone and among copies of itself, in launches of few and of many blocks
     (8, 4, 2 waves to a block, persistent waves): every estimate has the same bits."""
@@ -102,3 +103,19 @@ def test_estimates_do_not_depend_on_the_waves_per_block(te, S, k, points):
         first = first or (t0[0, 0], ts[0, 0].copy())
         np.testing.assert_array_equal(t0, np.full_like(t0, first[0]))
         np.testing.assert_array_equal(ts[0], np.repeat(first[1][None], n, axis=0))
+
+
+@pytest.mark.parametrize("R,trials,S,seed", [(1, (1,), 3, 5), (2, (2, 1), 5, 6), (3, (3, 2), 5, 7),
+                                             (257, (63, 64, 65, 256, 257), 9, 8), (2000, (1999, 2000), 6, 9),
+                                             (6145, (6143, 6144, 6145), 4, 10), (6144, (6144,), 600, 11)])
+def test_drawn_permutations_at_the_edges(te, R, trials, S, seed):
+    """Rows of one trial up to the longest drawn across lanes and the next one; 600 rows of 6 144
+    trials hold rejected draws (a row has one with probability 0.0022)."""
+    C = len(trials)
+    print("permutations", R, trials, S, flush=True)
+    wl = synth.configs.Workload(name="perm", x=np.zeros((1, R, 12), np.float32), y=np.zeros((1, R, 12), np.float32),
+                                d_y=1, d_x=1, tau=1, u=1, k=4, window_start=np.ones(C, np.int32),
+                                window_len=np.full(C, 8, np.int32), trials=np.array(trials, np.int32), n_surrogates=S)
+    wl.perm_seed = seed
+    want = synth.configs.make_perms(seed, 1, wl.trials, S, R)
+    np.testing.assert_array_equal(te.Plan.from_workload(wl).permutations().cpu().numpy(), want)
