@@ -150,12 +150,16 @@ struct SearchArgs {
 };
 
 // Chunks of one window searched together by the chunk-set search (they share the
-// (y_t', Y_past) block and its order and differ in the source block): as many as
-// keep a group of four candidates' coordinates, 4 (1 + d_y + V d_x) values, within
-// 64 scalar registers, two to four.
+// (y_t', Y_past) block and its order and differ in the source block).  More of them share a pair's
+// target differences, but a block of candidates has to be examined for the chunk with the largest
+// radius.  Measured, us, two / three / four to a set (8 windows of 20 000 points x 61 chunks):
+// (1, 3) 19 939 / 20 189 / 23 806, (2, 2) 7 978 / 7 601 / 8 073, (3, 3) 12 530 / 12 873 / 13 109,
+// (4, 4) 19 773 / 19 796 / -; 40 windows of 2 400 points x 101: (3, 3) 4 704 / 4 434 / 4 386,
+// (4, 4) 5 995 / 5 738 / 6 247; with one source coordinate: (1, 1) 2 592 / 2 497 / 2 367,
+// (2, 1) 2 738 / 2 573 / 2 399.
 constexpr int set_variants(int d_y, int d_x)
 {
-    return (15 - d_y) / d_x >= 4 ? 4 : ((15 - d_y) / d_x <= 2 ? 2 : (15 - d_y) / d_x);
+    return d_x == 1 ? 4 : 3;
 }
 constexpr int kMaxSetVariants = 4;
 
@@ -206,7 +210,7 @@ struct ordered_search {
     size_t lds;
 };
 ordered_search pick_ordered(int d_y, int d_x, int k, int slots, bool sets, int waves_per_wg);
-int waves_to_a_block(int64_t n_items, bool sets, int k);
+int waves_to_a_block(int64_t n_items, int set_coords, int k);
 ordered_search pick_shared(int d_y, int d_x, int k, bool sets, int w);
 // With pv != nullptr the launch also computes the n_groups p-values (results laid
 // out [group][original, surrogates...]; NaN when *err is set) and copies *err to

@@ -504,9 +504,10 @@ __device__ __forceinline__ void block_search(const SearchArgs &a)
 
         // ---- pass 2: lane = candidate, references uniform from this wave's LDS rows (which hold the
         // final radii); the three strict comparisons are wave ballots, counted on the SALU.  Bound by
-        // issue: at (3, 3, four chunks) a step of 64 candidates is 45 VALU (28 of them at half rate), 28 SALU
+        // issue: with four chunks at (3, 3) a step of 64 candidates is 45 VALU (28 of them at half rate), 28 SALU
         // and five LDS reads, 171 clocks per SIMD; the two-to-a-register counts took 11 SALU off it
-        // (30 windows x 101 chunks of 1 000 to 50 000 points: 119.0 -> 110.6 ms).
+        // (30 windows x 101 chunks of 1 000 to 50 000 points: 119.0 -> 110.6 ms; 94.1 with three chunks
+        // and six waves).
         constexpr int NC = V + (V + 1) / 2;
         uint32_t accP[V], accTP[V], accPS[V];
         uint32_t packed[NC];                              // counts since the last unpack(), 16 bits each
@@ -722,10 +723,15 @@ __global__ void __launch_bounds__((W > 0 ? W : kMaxWavesPerWG) * 64) search_kern
     block_search<DY, DX, 1, KP1, GENERIC, SLOTS, true, W>(a);
 }
 
-// A set whose pairs have many coordinates is held to five waves per SIMD: at (3, 3, four chunks) 96
-// VGPRs with a few spills beat 105 and four waves, 111 to 103 ms on 30 windows x 101 chunks of 1 000 to
-// 50 000 points; the narrower sets have five or six waves as they are and lose by it.
-constexpr int sets_waves(int d_y, int d_x, int v, int w) { return w == 0 && 1 + d_y + v * d_x >= 16 ? 5 : 1; }
+// Waves per SIMD that a set's kernel is held to: the passes wait for LDS rows and issue slots of other
+// pipes, and another wave fills them.  Six waves (85 VGPRs) where they cost a few spills at most: at
+// (3, 3), three chunks, against five 100.4 to 94.1 ms on 30 windows x 101 chunks of 1 000 to 50 000
+// points, seven 108 ms; at (3, 2) 8.49 to 8.08 ms on 8 windows x 61 chunks of 20 000 points.  With 14
+// coordinates and more six cost more spills than they hide: (4, 3) 15.5 ms at five, 16.9 ms at six.
+constexpr int sets_waves(int d_y, int d_x, int v, int w)
+{
+    return w > 0 ? 1 : (1 + d_y + v * d_x >= 14 ? 5 : 6);
+}
 
 template <int DY, int DX, int V, int SLOTS, int W>
 __global__ void __launch_bounds__((W > 0 ? W : kMaxWavesPerWG) * 64)

@@ -61,13 +61,15 @@ ordered_search pick_ordered(int d_y, int d_x, int k, int slots, bool sets, int w
 //   k = 6, 940 / 8 200 / 24 400 blocks       282 / 214 / 174 / 185, 890 / 521 / 549 / 765, 1306 / 1216 / 1366 / 2047
 //   k = 8, 940 / 8 200 / 24 400 blocks       299 / 234 / 188 / 189, 897 / 588 / 608 / 834, 1333 / 1392 / 1532 / 2254
 //   k = 12, 940 / 8 200 / 24 400 blocks      332 /  - / 238 /  - , 855 /  - / 823 /  - , 1425 /  - / 2124 /  -
-//   sets of four, 192 blocks (N = 2 000)     577 / 413 / 299 / 241
-//   sets of four, 832 / 1 632 blocks         612 / 507 / 470 / 577, 702 / 746 / 677 / 930
-//   sets of four, 3 328 blocks               873 / 1111 / 1090 / 1673
-int waves_to_a_block(int64_t n_items, bool sets, int k)
+//   sets (3, 3), 224 / 1 088 / 2 688 / 8 704 blocks (N = 2 000)   442 / 311 / 212 / 169, 478 / 368 / 355 / 366,
+//                                            615 / 619 / 588 / 688, 1243 / 1498 / 1581 / 1967
+//   sets (2, 2), 224 / 1 088 / 2 688 / 8 704 / 17 408 blocks      287 / 235 / 167 / 136, 321 / 281 / 235 / 284,
+//                                            468 / 426 / 400 / 514, 1033 / 921 / 1002 / 1395, 1397 / 1675 / 1869 / 2673
+// A set's pairs of up to nine coordinates leave the persistent waves idle up to 9 000 blocks, wider ones do not.
+int waves_to_a_block(int64_t n_items, int set_coords, int k)
 {
-    if (sets)
-        return n_items <= 512 ? 8 : (n_items <= 1536 ? 4 : 0);
+    if (set_coords > 0)
+        return n_items <= 512 ? 8 : (n_items <= 3072 ? 4 : (set_coords <= 9 && n_items <= 9216 ? 2 : 0));
     if (k > 8)
         return n_items <= 8192 ? 4 : 0;
     if (n_items <= 832)

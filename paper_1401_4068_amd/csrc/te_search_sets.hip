@@ -20,6 +20,7 @@ search_fn pick_search_sets(int d_y, int d_x, int slots, int w)
 {
     switch (w) {
     case 0: return slots == 1 ? pick_sets<1, 0>(d_y, d_x) : pick_sets<2, 0>(d_y, d_x);
+    case 2: return pick_sets<1, 2>(d_y, d_x);
     case 4: return pick_sets<1, 4>(d_y, d_x);
     case 8: return pick_sets<1, 8>(d_y, d_x);
     default: return nullptr;

@@ -88,7 +88,7 @@ def _repeated(points, S, k):
 
 @pytest.mark.parametrize("S,k,points", [(0, 4, (1, 50, 300, 2300)), (3, 4, (1, 100, 200)), (0, 3, (1, 100, 300, 2300)),
                                         (0, 6, (1, 200, 500, 800)), (0, 8, (1, 100)), (0, 15, (1, 50)), (0, 4, (1, 600)),
-                                        (0, 8, (1, 1500, 1800))])
+                                        (0, 8, (1, 1500, 1800)), (3, 4, (1, 500))])
 def test_estimates_do_not_depend_on_the_waves_per_block(te, S, k, points):
     """The same window alone and among copies of itself, in launches of few and of many blocks
     (8, 4, 2 waves to a block, persistent waves): every estimate has the same bits."""
