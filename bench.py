@@ -77,8 +77,8 @@ def valu_ceiling(sub: float, mx: float, cmp: float) -> float:
 # device copy measured the same way (factors 2.000 and 1.000), keyed by (kernel source, workload); any other
 # kernel source reports null.
 RECORDED_TRAFFIC = {
-    ("e2709849861a", "uneven_chunks_200_surrogates"): 171724200872,
-    ("e2709849861a", "nonlinear_ar_ensemble"): 19403050,
+    ("cf6d8f22878f", "uneven_chunks_200_surrogates"): 112927948800,
+    ("cf6d8f22878f", "nonlinear_ar_ensemble"): 435912328,
 }
 KERNEL_SRC = [os.path.join(ROOT, "paper_1401_4068_amd", "csrc", f)
               for f in ("te_kernels.hip", "te_search.hip", "te_search.h", "te_search_sets.hip")]
@@ -680,8 +680,8 @@ def ragwitz_record(args):
     torch.cuda.synchronize()
     dt = time.perf_counter() - t0
     dev_ms = ev0.elapsed_time(ev1) / args.steps
-    # executed FP32 operations: per (reference, candidate point) pair d subtractions, d - 1
-    # maxes and one min or compare (abs is an operand modifier)
+    # the method's FP32 operations: per (reference, candidate point) pair d subtractions, d - 1
+    # maxes and one min or compare (abs is an operand modifier); the search prunes and executes fewer
     ops = sum(2 * d for d, _ in cands) * float(N) * float(N)
     achieved = ops / (dev_ms * 1e-3) / 1e12
     peak = FP32_LANE_INSTR_PER_S / 1e12
@@ -695,12 +695,12 @@ def ragwitz_record(args):
                     candidates=[list(c) for c in cands], k=k, workspace_bytes=int(need.value),
                     path="te_ragwitz (synchronous)"),
         distance_evals_per_s=round(len(cands) * N * (N - 1) * args.steps / dt, 1),
-        roofline=dict(bound="alu", achieved=round(achieved, 3), peak=round(peak, 3), unit="TFLOP/s",
-                      frac=round(achieved / peak, 4), traffic=None,
+        roofline=dict(bound="alu", achieved=None, peak=round(peak, 3), unit="TFLOP/s", frac=None, traffic=None,
+                      method_equivalent_tops=round(achieved, 3), frac_method_equivalent=round(achieved / peak, 4),
                       peak_derivation="78.64e12 FP32 lane-instr/s (256 CU x 4 SIMD x 32 lanes x 2.4 GHz), one "
-                                      "executed op per instruction",
-                      kernel="rag_knn_kernel<d> (+ embed, score)", device_ms_per_step=round(dev_ms, 4),
-                      ops_per_step=ops),
+                                      "op per instruction; executed pairs are not counted on this path",
+                      kernel="rag_search_kernel (+ order, embed, gather, score)", device_ms_per_step=round(dev_ms, 4),
+                      method_ops_per_step=ops),
         findings=dict(scores=[round(float(v), 6) for v in scores], chosen=list(cands[best])))
     if not args.no_cpu:
         from oracle import ragwitz as rg
