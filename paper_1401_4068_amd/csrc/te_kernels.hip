@@ -599,10 +599,15 @@ __device__ __forceinline__ void scan_digits(uint32_t *cnt, uint32_t *part)
 // sort by the runs between those codes then puts every point on its side of every cut (points of
 // a cut's own code by index), and leaves the point indices of each slab in index order in the map.
 // The codes live behind the 16-bit map or in the key scratch, where the boxes will be written later.
-// Bound by the latency of one workgroup's passes.  With order_kernel 122 us for one window of 48 000
-// points and 63 us for five of 10 500; a bitonic sort by the first coordinate alone took 1 156 and 215 us.
+// Bound by the latency of one workgroup's passes.  With order_kernel 113 us for one window of 48 000
+// points and 53 us for five of 10 500; a bitonic sort by the first coordinate alone took 1 156 and 215 us.
 constexpr int kCodeBits = 15;
 constexpr int kClasses = 128;          // runs between cuts: 2 (kMaxSlabs - 1) + 1 at most
+
+// Where a code's count is kept: rotated within its group of 32, so that threads which walk a group
+// each read different banks (in code order a wave's reads all fall in one: 42 instead of 32 us for five
+// windows of 10 500 points).
+__device__ __forceinline__ uint32_t code_slot(uint32_t c) { return (c & ~31u) | ((c + (c >> 5)) & 31u); }
 
 __global__ void __launch_bounds__(kOrderThreads) split_kernel(CoordSource src, const SortTask *__restrict__ tasks,
                                                               int32_t *sigma, uint64_t *scratch, int d_y)
@@ -650,7 +655,7 @@ __global__ void __launch_bounds__(kOrderThreads) split_kernel(CoordSource src, c
         for (int u = 0; u < U; ++u) {
             const int i = i0 + u * kOrderThreads;
             if (i < n) {
-                const uint32_t c = (o[u] - lo) >> shift;
+                const uint32_t c = code_slot((o[u] - lo) >> shift);
                 code[i] = (uint16_t)c;
                 atomicAdd(&hist[c], 1u);
             }
@@ -661,7 +666,7 @@ __global__ void __launch_bounds__(kOrderThreads) split_kernel(CoordSource src, c
     constexpr int kOwn = (1 << kCodeBits) / kOrderThreads;
     uint32_t own = 0;
     for (int e = 0; e < kOwn; ++e)
-        own += hist[t * kOwn + e];
+        own += hist[code_slot(t * kOwn + e)];
     const uint32_t inc = wave_scan(own);                  // inclusive
     if (lane == kWave - 1)
         part[w] = inc;
@@ -677,8 +682,8 @@ __global__ void __launch_bounds__(kOrderThreads) split_kernel(CoordSource src, c
             const uint32_t rank = (uint32_t)slab_first(nl, slabs, s) * kWave;
             if (rank < before || rank >= before + own)
                 continue;
-            while (cum + hist[t * kOwn + e] <= rank)
-                cum += hist[t * kOwn + e++];
+            while (cum + hist[code_slot(t * kOwn + e)] <= rank)
+                cum += hist[code_slot(t * kOwn + e++)];
             cut_code[s] = t * kOwn + e;
         }
     }
@@ -692,7 +697,7 @@ __global__ void __launch_bounds__(kOrderThreads) split_kernel(CoordSource src, c
         for (int e = 0; e < kOwn; ++e) {
             const int c = t * kOwn + e;
             const bool cut = s < slabs && cut_code[s] == c;
-            hist[c] = (uint32_t)(2 * below + (cut ? 1 : 0));
+            hist[code_slot(c)] = (uint32_t)(2 * below + (cut ? 1 : 0));
             if (cut) {
                 ++below;
                 while (s < slabs && cut_code[s] == c)

