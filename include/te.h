@@ -231,7 +231,9 @@ te_status te_delay_scan(te_plan plan, const float *x, const float *y, const int3
  * searched in one launch.
  *   pts        device float32, coordinate-major: coordinate m of global point
  *              i is pts[m * dim_stride + i]; coordinates ordered
- *              (y_t | Y_past (d_y) | X_past (d_x))
+ *              (y_t | Y_past (d_y) | X_past (d_x)).  A coordinate whose
+ *              difference is no number (NaN, equal infinities) says nothing about
+ *              its pair; a pair without any in a space is in no ball of it
  *   offsets    host int64 [n_chunks + 1]: chunk c holds points
  *              [offsets[c], offsets[c+1]); each chunk needs more than k points
  *   ws         device workspace of te_knn_counts_workspace_bytes(n_chunks) bytes

@@ -150,7 +150,8 @@ __device__ __forceinline__ void block_search(const SearchArgs &a)
             for (int s = 0; s < KP1; ++s)
                 best[v][s] = s < fill ? 0.0f : kInf;
         auto cur = [&](int v) { return best[v][KP1 - 1]; };
-        auto insert = [&](int v, float x) { insert_sorted<KP1>(best[v], x); };
+        // (pre-embedded points: a distance that is no number is beyond every other one)
+        auto insert = [&](int v, float x) { insert_sorted<KP1>(best[v], OUT ? fminf(x, kInf) : x); };
         // largest current radius over the variants (0 in lanes past the chunk's end): a
         // candidate at least that far away is of no use to any variant
         auto curmax = [&]() {
@@ -302,7 +303,7 @@ __device__ __forceinline__ void block_search(const SearchArgs &a)
                 for (int u = 0; u < U; ++u)
 #pragma unroll
                     for (int v = 0; v < V; ++v)
-                        insert_sorted<KP1>(best[v], dj[u][v]);
+                        insert(v, dj[u][v]);
             }
 #pragma unroll
             for (int o = RPW; o < kWave; o <<= 1)
@@ -531,6 +532,10 @@ __device__ __forceinline__ void block_search(const SearchArgs &a)
             counted = 0;
         };
         unsigned long long evaluated2 = 0;                // candidate-reference pairs examined in pass 2
+        // Pre-embedded points may be infinite or no numbers: a coordinate without a difference says nothing
+        // about its pair (fmaxf passes it over), but a pair without any in one space is outside the balls of
+        // both, so there the larger of two distances is no number if one of them is none.
+        auto larger = [](float d, float e) { return OUT ? __builtin_elementwise_maximum(d, e) : fmaxf(d, e); };
         // counts of the references in todo over NS blocks of candidates
         auto count = [&](uint64_t todo, auto ns, const float (*ct)[DT], const float (*cs)[V][DX]) {
             constexpr int NS = decltype(ns)::value;
@@ -555,7 +560,7 @@ __device__ __forceinline__ void block_search(const SearchArgs &a)
 #pragma unroll
                     for (int m = 2; m < DT; ++m)
                         dp = fmaxf(dp, absdiff(rr[m], ct[sl][m]));
-                    const float dtp = fmaxf(absdiff(rr[0], ct[sl][0]), dp);
+                    const float dtp = larger(absdiff(rr[0], ct[sl][0]), dp);
 #pragma unroll
                     for (int v = 0; v < V; ++v) {
                         float ds = absdiff(rr[DT + v * DX], cs[sl][v][0]);
@@ -565,7 +570,7 @@ __device__ __forceinline__ void block_search(const SearchArgs &a)
                         const float er = rr[DT + V * DX + v];
                         sP[v] += (uint32_t)__builtin_popcountll(ballot(dp < er));
                         sTP[v] += (uint32_t)__builtin_popcountll(ballot(dtp < er));
-                        sPS[v] += (uint32_t)__builtin_popcountll(ballot(fmaxf(dp, ds) < er));
+                        sPS[v] += (uint32_t)__builtin_popcountll(ballot(larger(dp, ds) < er));
                     }
                 }
 #pragma unroll
@@ -628,24 +633,6 @@ __device__ __forceinline__ void block_search(const SearchArgs &a)
         }
 
         unpack();
-        if constexpr (OUT) {
-            // Pre-embedded points may be infinite: a difference of equal infinities is no number and
-            // lies in no ball, but a maximum passes it over.  It takes an infinite reference.
-            auto unbounded = [](float x, float z) { return fmaxf(z, absdiff(x, x)); };
-            float own[RW];
-            read_row(lane, own);
-            float p = rt[1] - rt[1], s = own[DT] - own[DT];
-#pragma unroll
-            for (int m = 1; m < DY; ++m)
-                p = unbounded(rt[1 + m], p);
-#pragma unroll
-            for (int m = 1; m < DX; ++m)
-                s = unbounded(own[DT + m], s);
-            if (p != p || own[0] - own[0] != 0.0f)
-                accTP[0] = 0;
-            if (p != p || s != s)
-                accPS[0] = 0;
-        }
 
         // ---- per-point digamma terms of eq. 9, summed over the block in fixed order; self is at
         // distance 0 in every space and was counted iff its radius is positive

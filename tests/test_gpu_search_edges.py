@@ -1,0 +1,74 @@
+"""GPU tests of the searches where their inputs or launch shapes are unusual."""
+import numpy as np
+import pytest
+
+from synth.rng import derive_key, normal64
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def te():
+    import paper_1401_4068_amd as te
+    return te
+
+
+def _offsets(sizes):
+    return np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+
+
+def _statistics(te, pts, sizes, d_y, d_x, k):
+    import torch
+    got = te.knn_counts(torch.from_numpy(np.ascontiguousarray(pts)).cuda(), _offsets(sizes), d_y, d_x, k)
+    return got[0].cpu().numpy(), got[1].cpu().numpy(), got[2]
+
+
+def _brute_force(p, d_y, k):
+    """Radii and counts of one chunk: a coordinate difference that is no number says nothing about
+    its pair, and a pair without any in a space lies in no ball of that space."""
+    eps = np.empty(p.shape[1], np.float32)
+    cnt = np.empty((3, p.shape[1]), np.int32)
+    with np.errstate(invalid="ignore"):
+        for i in range(p.shape[1]):
+            d = np.abs(p - p[:, i:i + 1])
+            dt, dp = d[0], np.fmax.reduce(d[1:1 + d_y])
+            ds = np.fmax.reduce(d[1 + d_y:])
+            dj = np.fmax(np.fmax(dt, dp), ds)
+            e = np.sort(np.where(np.isnan(dj), np.float32(np.inf), dj))[k]
+            in_p = dp < e
+            own = int(e > 0)
+            eps[i] = e
+            cnt[:, i] = in_p.sum() - own, (in_p & (dt < e)).sum() - own, (in_p & (ds < e)).sum() - own
+    return eps, cnt
+
+
+def _with_nan(kind, N, D, d_y, seed):
+    p = normal64(derive_key(seed, N, D), N * D).reshape(D, N)
+    if kind == "future":
+        p[0, 1::7] = np.nan
+    elif kind == "past":
+        p[1:1 + d_y, 3::11] = np.nan
+    elif kind == "source":
+        p[1 + d_y:, 2::9] = np.nan
+    elif kind == "points":                   # whole points, as a marker of missing values
+        p[:, 5::13] = np.nan
+    elif kind == "single":                   # every coordinate somewhere, alone and together, beside infinities
+        for m in range(D):
+            p[m, m::5 + m] = np.nan
+        p[1, 4::17] = np.inf
+        p[D - 1, 6::19] = -np.inf
+    return p.astype(np.float32)
+
+
+@pytest.mark.parametrize("d_y,d_x,k", [(1, 1, 4), (3, 3, 4), (2, 1, 7), (4, 2, 12)])
+@pytest.mark.parametrize("kind", ["future", "past", "source", "points", "single"])
+def test_points_that_are_no_numbers(te, monkeypatch, kind, d_y, d_x, k):
+    sizes = [40, 64, 65, 1100]
+    pts = _with_nan(kind, sum(sizes), 1 + d_y + d_x, d_y, 601)
+    print("nan", kind, d_y, d_x, k, flush=True)
+    want = [_brute_force(pts[:, a:b], d_y, k) for a, b in zip(_offsets(sizes)[:-1], _offsets(sizes)[1:])]
+    for no_sort in ("0", "1"):
+        monkeypatch.setenv("TE_NO_SORT", no_sort)
+        eps, cnt, _ = _statistics(te, pts, sizes, d_y, d_x, k)
+        np.testing.assert_array_equal(eps, np.concatenate([w[0] for w in want]))
+        np.testing.assert_array_equal(cnt, np.concatenate([w[1] for w in want], axis=1))
