@@ -617,8 +617,12 @@ __device__ __forceinline__ void block_search(const SearchArgs &a)
                             used = sl + 1;
                         todo |= m;
                         load_block(b, ct[sl], cs[sl]);
+                        // unused: outside every target-past ball; with one infinite coordinate only, an
+                        // infinite reference would pass it over and take the block's points again
                         if (m == 0)
-                            ct[sl][1] = kInf;          // outside every target-past ball
+#pragma unroll
+                            for (int x = 1; x < (OUT ? DT : 2); ++x)
+                                ct[sl][x] = kInf;
                         evaluate(m, b);
                     }
                     if (used > 0)

@@ -72,3 +72,37 @@ def test_points_that_are_no_numbers(te, monkeypatch, kind, d_y, d_x, k):
         eps, cnt, _ = _statistics(te, pts, sizes, d_y, d_x, k)
         np.testing.assert_array_equal(eps, np.concatenate([w[0] for w in want]))
         np.testing.assert_array_equal(cnt, np.concatenate([w[1] for w in want], axis=1))
+
+
+def _many(kind, d_y, D):
+    """30 000 blocks of chunks of one to eighteen blocks: searched by persistent waves, a block each."""
+    sizes = [65, 190, 1100, 700, 511] * 714
+    pts = _with_nan(kind, sum(sizes[:50]), D, d_y, 602).astype(np.float32)
+    if kind == "infinite":
+        pts[0, 1::13] = np.inf
+        pts[-1, 2::9] = -np.inf
+        pts[1, ::7] = np.inf
+        pts[1, ::11] = -np.inf
+    elif kind == "grid":
+        pts = np.round(pts * 2) / 2
+    out = np.tile(pts, (1, -(-sum(sizes) // pts.shape[1])))[:, :sum(sizes)]
+    return out, sizes
+
+
+@pytest.mark.parametrize("slots", [4, 8])
+@pytest.mark.parametrize("kind,d_y,d_x,k", [("gauss", 2, 2, 4), ("grid", 3, 3, 4), ("grid", 1, 1, 6), ("infinite", 2, 2, 4),
+                                            ("infinite", 4, 1, 4), ("points", 2, 2, 4), ("single", 3, 1, 4),
+                                            ("single", 1, 2, 9)])
+def test_persistent_waves_equal_the_unordered_search(te, monkeypatch, kind, d_y, d_x, k, slots):
+    """Single chunks in launches too large for several waves to a block, one and two blocks of
+    candidates counted together: radii and counts of the every-pair search."""
+    pts, sizes = _many(kind, d_y, 1 + d_y + d_x)
+    print("persistent", kind, d_y, d_x, k, slots, flush=True)
+    monkeypatch.setenv("TE_SLOTS", str(slots))
+    got = _statistics(te, pts, sizes, d_y, d_x, k)
+    monkeypatch.setenv("TE_NO_SORT", "1")
+    want = _statistics(te, pts, sizes, d_y, d_x, k)
+    np.testing.assert_array_equal(got[0], want[0])
+    np.testing.assert_array_equal(got[1], want[1])
+    # eq. 9 sums N terms below 14 in another order: N rounding errors of 2^-53 * 14 N at most, over N
+    np.testing.assert_allclose(got[2], want[2], rtol=0, atol=14 * max(sizes) * 2.0 ** -53, equal_nan=True)
