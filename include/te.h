@@ -363,7 +363,9 @@ te_status te_serve_close(te_server srv);
  * The search kernel's launch shape -- candidate slots in the counting pass (4:
  * one block of 64 candidates at a time; 8 and 16: two), waves per workgroup (1, 2 or 4) and resident workgroups per
  * compute unit (every whole number of waves per SIMD from full occupancy down to
- * half) -- is chosen per (d_y, d_x, k, chunk-size bucket floor(log2 N)).
+ * half) -- is chosen per (d_y, d_x, k, chunk-size bucket floor(log2 N)).  It is
+ * the shape of large launches; small ones, which give a block several waves, do
+ * not use it, and the tuners time the large form whatever their problem's size.
  * te_autotune times every shape on n_chunks synthetic chunks of n_points points
  * (uniform random coordinates generated in ws) and records the fastest in a
  * process-wide table that plans and servers created afterwards use (the nearest

@@ -178,6 +178,7 @@ struct SearchConfig {
     int slots;        // candidate blocks counted together in pass 2: 4 -> one, 8 and 16 -> two
     int waves_per_wg; // independent wavefronts per workgroup
     int wg_per_cu;    // persistent workgroups per compute unit
+    bool timed = false;   // the tuners: persistent waves however small the launch is, so that a shape is what is timed
 };
 
 struct DeviceInfo {

@@ -1,7 +1,9 @@
 // te_tune.cpp -- autotuner for the search kernel's launch shape.
 //
-// A shape is (candidate slots per lane in the counting pass, waves per
-// workgroup, resident workgroups per CU).  te_autotune times every shape on
+// A shape is (candidate slots in the counting pass, waves per workgroup, resident
+// workgroups per CU) of the persistent waves; launches small enough for several
+// waves to a block (waves_to_a_block) do not use it, and both tuners time persistent
+// waves however few blocks they are given.  te_autotune times every shape on
 // synthetic chunks of the requested (d_y, d_x, k, N) generated on the device,
 // keeps the fastest in a process-wide table keyed by (d_y, d_x, k, N bucket),
 // and default_config() consults that table.  te_tune_save / te_tune_load keep
@@ -229,7 +231,7 @@ te_status te_autotune(int32_t d_y, int32_t d_x, int32_t k, int32_t n_points, int
                 if (std::find(wgs.begin(), wgs.end(), w * per_level) == wgs.end())
                     wgs.push_back(w * per_level);
             for (int wg : wgs) {
-                SearchConfig c{sl, wpg, wg};
+                SearchConfig c{sl, wpg, wg, true};
                 double tmin = 1e30;
                 for (int rep = 0; rep < 5 && e == hipSuccess; ++rep) {
                     e = launch_fill_i32(a.counter, 0, 1, st);
@@ -259,6 +261,7 @@ te_status te_autotune(int32_t d_y, int32_t d_x, int32_t k, int32_t n_points, int
     hipEventDestroy(e1);
     if (e != hipSuccess)
         return hip_fail(e, "tuning run");
+    best.timed = false;
     {
         std::lock_guard<std::mutex> lk(g_mu);
         g_table[TuneKey{d_y, d_x, k, size_bucket(n_points)}] = TuneVal{best, best_t};
@@ -347,7 +350,7 @@ te_status te_plan_autotune(te_plan plan, const float *x, const float *y, const i
                 if (std::find(wgs.begin(), wgs.end(), w * per_level) == wgs.end())
                     wgs.push_back(w * per_level);
             for (int wg : wgs) {
-                P.cfg = SearchConfig{sl, wpg, wg};
+                P.cfg = SearchConfig{sl, wpg, wg, true};
                 double tmin = 1e30;
                 for (int rep = 0; rep < 5 && s == TE_OK && e == hipSuccess; ++rep) {
                     if (rep == 3 && tmin > 20.0)             // long runs: one warm-up and two timed
@@ -376,6 +379,7 @@ te_status te_plan_autotune(te_plan plan, const float *x, const float *y, const i
     hipEventDestroy(e0);
     hipEventDestroy(e1);
     P.pool.give(stg);
+    best.timed = false;
     P.cfg = (s == TE_OK && e == hipSuccess) ? best : saved;
     if (s != TE_OK)
         return s;

@@ -2,6 +2,7 @@
 import numpy as np
 import pytest
 
+import synth
 from synth.rng import derive_key, normal64
 
 pytestmark = pytest.mark.gpu
@@ -106,3 +107,53 @@ def test_persistent_waves_equal_the_unordered_search(te, monkeypatch, kind, d_y,
     np.testing.assert_array_equal(got[1], want[1])
     # eq. 9 sums N terms below 14 in another order: N rounding errors of 2^-53 * 14 N at most, over N
     np.testing.assert_allclose(got[2], want[2], rtol=0, atol=14 * max(sizes) * 2.0 ** -53, equal_nan=True)
+
+
+def _copies(points, S, d_y=2, d_x=2, W=13):
+    """`points` copies of one window of 50 W points."""
+    wl = synth.generic((6092, S), R=50, T=60, d_y=d_y, d_x=d_x, starts=(30,), windows=(W,), n_surrogates=S)
+    wl.window_start = np.full(points, 30, np.int32)
+    wl.window_len = np.full(points, W, np.int32)
+    wl.trials = np.full(points, 50, np.int32)
+    if S:
+        wl.perms = np.ascontiguousarray(np.repeat(wl.perms, points, axis=1))
+    return wl
+
+
+def _surrogates(te, wl):
+    import torch
+    perms = torch.from_numpy(wl.perms).cuda() if wl.n_surrogates else None
+    plan = te.Plan.from_workload(wl)
+    return plan, plan.surrogates(torch.from_numpy(wl.x).cuda(), torch.from_numpy(wl.y).cuda(), perms)
+
+
+def test_tuning_times_the_persistent_waves(te):
+    """The tuned shape is that of persistent waves; a plan small enough for several waves to a
+    block is timed in that form too.  The two forms examine different numbers of pairs: as many
+    per window as in a batch of persistent waves."""
+    import torch
+    n = 2300
+    plan, _ = _surrogates(te, _copies(n, 0))
+    wl = _copies(1, 0)
+    x, y = torch.from_numpy(wl.x).cuda(), torch.from_numpy(wl.y).cuda()
+    small = te.Plan.from_workload(wl)
+    te.profile_enable(True, work=True)
+    try:
+        te.profile_work(reset=True)
+        plan.surrogates(x, y)
+        persistent = te.profile_work(reset=True)
+        small.surrogates(x, y)
+        shared = te.profile_work(reset=True)
+        te.profile_read(reset=True)
+        small.autotune(x, y)
+        _, launches = te.profile_read(reset=True)
+        tuned = te.profile_work(reset=True)
+        small.surrogates(x, y)
+        after = te.profile_work(reset=True)
+    finally:
+        te.profile_enable(False)
+        te.tune_clear()
+    print("pairs", persistent, shared, tuned, launches, after, flush=True)
+    assert persistent[0] % n == 0 and persistent[0] // n != shared[0]
+    assert tuned[0] == launches * (persistent[0] // n)
+    assert after == shared
