@@ -127,6 +127,25 @@ def _surrogates(te, wl):
     return plan, plan.surrogates(torch.from_numpy(wl.x).cuda(), torch.from_numpy(wl.y).cuda(), perms)
 
 
+@pytest.mark.parametrize("d_y,d_x,S,points", [(2, 2, 3, 500), (1, 1, 4, 500), (3, 3, 5, 180), (4, 3, 2, 300), (2, 2, 0, 2300)])
+def test_persistent_launches_of_every_shape(te, monkeypatch, d_y, d_x, S, points):
+    """Launches of persistent waves, chunk sets and single chunks, in every kind of shape: the
+    estimates of the default shape, of single chunks and of one window alone, bit for bit."""
+    wl = _copies(points, S, d_y, d_x)
+    alone = _surrogates(te, _copies(1, S, d_y, d_x))[1]
+    for env in ({}, {"TE_NO_SETS": "1"}, {"TE_SLOTS": "4", "TE_WAVES_PER_WG": "1", "TE_WG_PER_CU": "3"},
+                {"TE_SLOTS": "16", "TE_WAVES_PER_WG": "2", "TE_WG_PER_CU": "1"},
+                {"TE_SLOTS": "8", "TE_WAVES_PER_WG": "1", "TE_WG_PER_CU": "7"},
+                {"TE_SLOTS": "8", "TE_WAVES_PER_WG": "4"}):
+        print("shape", d_y, d_x, S, points, env, flush=True)
+        with monkeypatch.context() as m:
+            for name, v in env.items():
+                m.setenv(name, v)
+            t0, ts, _ = _surrogates(te, wl)[1]
+        np.testing.assert_array_equal(t0, np.full_like(t0, alone[0][0, 0]))
+        np.testing.assert_array_equal(ts[0], np.repeat(alone[1][0], points, axis=0))
+
+
 def test_tuning_times_the_persistent_waves(te):
     """The tuned shape is that of persistent waves; a plan small enough for several waves to a
     block is timed in that form too.  The two forms examine different numbers of pairs: as many
