@@ -1031,11 +1031,11 @@ __global__ void take_perms_kernel(const int32_t *__restrict__ src, const PermTas
 // output: m = w (i + 1), j_i = m >> 32, rejected when (m mod 2^32) < 2^32 mod (i+1).
 // Draws are made in rounds: in round one draw t takes output t; each later round
 // gives the draws rejected so far, in draw order, the next unused outputs.
-// The swaps are resolved in parallel (draw_perms_kernel); rows of more than kDrawShared trials, and
-// rows with a rejected draw (about one in two thousand of 2 000 trials), by one wave: the rounds
-// across lanes, the swaps in order on one lane (draw_row).
+// The rejected draws (in one of 4 400 rows of 2 000 trials, one of 700 of 5 000) take their later
+// rounds on one wave (redraw); the swaps are resolved in parallel (draw_perms_kernel), in rows of more
+// than kDrawShared trials made in order by one lane (draw_long_perms_kernel).
 constexpr uint64_t kGolden = 0x9E3779B97F4A7C15ull;
-constexpr int kDrawShared = 6144;         // 10 bytes of LDS per trial
+constexpr int kDrawShared = 8192;         // 10 bytes of LDS per trial: 80 KB, one row per CU at most
 constexpr int kDrawThreads = 256;
 constexpr int kMaxRejects = 256;
 
@@ -1069,35 +1069,36 @@ __device__ __forceinline__ uint64_t row_key(uint64_t seed, const PermTask &tk)
     return fold_key(key, (uint64_t)(int64_t)tk.surr);
 }
 
-// One wave draws a row and makes its swaps in order, in the row itself.
-__device__ void draw_row(const PermTask &tk, int32_t *row, uint64_t key, int32_t *err)
-{
-    __shared__ int32_t pend[2][kMaxRejects];
-    __shared__ int32_t fix_t[kMaxRejects], fix_j[kMaxRejects];
-    const int lane = threadIdx.x & (kWave - 1);
-    const int n = tk.rc;
-    const int draws = n - 1;
-    const uint64_t lanes_below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+// The rejected draws of a row and what they draw in the end: draw t[f] gives j[f] for f < n.
+struct Redrawn {
+    int32_t n;                            // below 0: more rejected draws than the lists hold
+    int32_t t[kMaxRejects], j[kMaxRejects];
+};
 
-    // round one: find the rejected draws (rare), in draw order
-    int npend = 0;
-    for (int t0 = 0; t0 < draws; t0 += kWave) {
-        const int t = t0 + lane;
-        const bool rej = t < draws && lemire_draw(key, (uint64_t)t, (uint32_t)(n - t)) < 0;
-        const uint64_t mask = ballot(rej);
-        if (rej) {
-            const int idx = npend + __builtin_popcountll(mask & lanes_below);
-            if (idx < kMaxRejects)
-                pend[0][idx] = t;
-        }
-        npend += __builtin_popcountll(mask);
+// One wave: the later rounds of the npend draws listed, in any order, in pend[1].
+__device__ void redraw(uint64_t key, int n, int npend, int32_t (&pend)[2][kMaxRejects], Redrawn &out)
+{
+    const int lane = threadIdx.x & (kWave - 1);
+    const uint64_t lanes_below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+    if (npend > kMaxRejects) {
+        if (lane == 0)
+            out.n = -1;
+        return;
     }
-    bool overflow = npend > kMaxRejects;
-    // later rounds: pending draws take the next unused outputs, in draw order
-    uint64_t pos = (uint64_t)max(draws, 0);
+    // in draw order
+    for (int l = lane; l < npend; l += kWave) {
+        int rank = 0;
+        for (int m = 0; m < npend; ++m)
+            rank += pend[1][m] < pend[1][l];
+        pend[0][rank] = pend[1][l];
+    }
+    // pending draws take the next unused outputs, in draw order
+    uint64_t pos = (uint64_t)max(n - 1, 0);
     int nfix = 0, cur = 0;
-    while (npend > 0 && !overflow) {
+    while (npend > 0) {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         int nnext = 0;
         for (int b0 = 0; b0 < npend; b0 += kWave) {
             const int l = b0 + lane;
@@ -1111,46 +1112,39 @@ __device__ void draw_row(const PermTask &tk, int32_t *row, uint64_t key, int32_t
             const uint64_t ma = ballot(acc), mr = ballot(rej);
             if (acc) {
                 const int idx = nfix + __builtin_popcountll(ma & lanes_below);
-                if (idx < kMaxRejects) {
-                    fix_t[idx] = t;
-                    fix_j[idx] = j;
-                }
+                out.t[idx] = t;
+                out.j[idx] = j;
             }
-            if (rej) {
-                const int idx = nnext + __builtin_popcountll(mr & lanes_below);
-                if (idx < kMaxRejects)
-                    pend[cur ^ 1][idx] = t;
-            }
+            if (rej)
+                pend[cur ^ 1][nnext + __builtin_popcountll(mr & lanes_below)] = t;
             nfix += __builtin_popcountll(ma);
             nnext += __builtin_popcountll(mr);
         }
         pos += (uint64_t)npend;
         npend = nnext;
         cur ^= 1;
-        overflow = nfix > kMaxRejects || npend > kMaxRejects;
     }
-    if (overflow) {
-        for (int r = lane; r < n; r += kWave)
-            row[r] = r;
-        if (lane == 0)
-            atomicOr(err, 2);
-        return;
-    }
-    __builtin_amdgcn_wave_barrier();
-    // the swaps, in order, on one lane
+    if (lane == 0)
+        out.n = nfix;
+}
+
+// The swaps of a row of n trials, in order, by one wave's first lane.
+__device__ void swap_row(int32_t *row, uint64_t key, int n, const Redrawn &fix)
+{
+    const int lane = threadIdx.x & (kWave - 1);
     for (int r = lane; r < n; r += kWave)
         row[r] = r;
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     if (lane == 0) {
-        for (int t = 0; t < draws; ++t) {
+        for (int t = 0; t < n - 1; ++t) {
             const int i = n - 1 - t;
             int j = lemire_draw(key, (uint64_t)t, (uint32_t)(i + 1));
             if (j < 0)
-                for (int f = 0; f < nfix; ++f)
-                    if (fix_t[f] == t)
-                        j = fix_j[f];
+                for (int f = 0; f < fix.n; ++f)
+                    if (fix.t[f] == t)
+                        j = fix.j[f];
             if (j < 0 || j > i)              // cannot happen: every rejected draw has a fix
                 j = i;
             const int32_t vi = row[i], vj = row[j];
@@ -1160,6 +1154,48 @@ __device__ void draw_row(const PermTask &tk, int32_t *row, uint64_t key, int32_t
     }
 }
 
+// Rows of more than kDrawShared trials, a wave each: the swaps in order, in the row itself (9 000 trials: 2 ms).
+__global__ void __launch_bounds__(kWave) draw_long_perms_kernel(const PermTask *__restrict__ tasks,
+                                                                int32_t *__restrict__ dst, uint64_t seed, int32_t *err)
+{
+    __shared__ int32_t rejected, pend[2][kMaxRejects];
+    __shared__ Redrawn fix;
+    const PermTask tk = tasks[blockIdx.x];
+    const int n = tk.rc, lane = threadIdx.x;
+    if (n <= kDrawShared)
+        return;
+    int32_t *row = dst + tk.dst;
+    const bool too_big = n > kMaxPermTrials;
+    for (int r = too_big ? lane : n + lane; r < tk.len; r += kWave)
+        row[r] = r;
+    if (too_big) {
+        if (lane == 0)
+            atomicOr(err, 2);
+        return;
+    }
+    const uint64_t key = row_key(seed, tk);
+    if (lane == 0)
+        rejected = 0;
+    __syncthreads();
+    for (int t = lane; t < n - 1; t += kWave)
+        if (lemire_draw(key, (uint64_t)t, (uint32_t)(n - t)) < 0) {
+            const int l = atomicAdd(&rejected, 1);
+            if (l < kMaxRejects)
+                pend[1][l] = t;
+        }
+    __syncthreads();
+    redraw(key, n, rejected, pend, fix);
+    __syncthreads();
+    if (fix.n < 0) {
+        for (int r = lane; r < n; r += kWave)
+            row[r] = r;
+        if (lane == 0)
+            atomicOr(err, 2);
+        return;
+    }
+    swap_row(row, key, n, fix);
+}
+
 // One workgroup per row.  What position i holds in the end is what position j_i held when step i
 // swapped them (steps run from i = n-1 down): the entry that the last earlier step i' > i with
 // j_i' = j_i had put there, or j_i itself; step i' had put there what position i' held then, and so
@@ -1167,50 +1203,58 @@ __device__ void draw_row(const PermTask &tk, int32_t *row, uint64_t key, int32_t
 //   a[i] = end(s) for s = the smallest step above i with j_s = j_i, or j_i if there is none,
 // end(p) following next() to its end; a[0] = end(0).  The steps of equal j are chained by exchanges in
 // LDS (in any order: only minima are taken from a chain), chains and paths being a few steps long.
-// Bound by LDS latency: 62 us for 30 windows x 100 rows of up to 5 000 trials, where one lane making the
-// swaps in order took 1 225 us.
+// Bound by LDS latency: 500 rows of 5 000 / 8 192 trials 70 / 130 us a call, rejected draws among them (a
+// row with one costs a microsecond more); one lane making a row's swaps in order 890 / 1 440 us.
 __global__ void __launch_bounds__(kDrawThreads) draw_perms_kernel(const PermTask *__restrict__ tasks,
                                                                   int32_t *__restrict__ dst, uint64_t seed, int32_t *err)
 {
     extern __shared__ __attribute__((aligned(16))) char draw_lds[];
-    __shared__ int32_t rejected;
+    __shared__ int32_t rejected, pend[2][kMaxRejects];
+    __shared__ Redrawn fix;
     constexpr uint16_t kEnd = 0xffff;
     const PermTask tk = tasks[blockIdx.x];
     const int n = tk.rc, tid = threadIdx.x;
+    if (n > kDrawShared)                  // draw_long_perms_kernel
+        return;
     int32_t *row = dst + tk.dst;
-    const bool too_big = n < 1 || n > kMaxPermTrials;
-    for (int r = too_big ? tid : n + tid; r < tk.len; r += kDrawThreads)
+    for (int r = max(n, 0) + tid; r < tk.len; r += kDrawThreads)
         row[r] = r;
-    if (too_big) {
+    if (n < 1) {
         if (tid == 0)
             atomicOr(err, 2);
         return;
     }
     const uint64_t key = row_key(seed, tk);
-    if (n > kDrawShared) {
-        if (tid < kWave)
-            draw_row(tk, row, key, err);
-        return;
-    }
     int32_t *head = reinterpret_cast<int32_t *>(draw_lds);
     uint16_t *j = reinterpret_cast<uint16_t *>(head + n), *chain = j + n, *next = chain + n;
     if (tid == 0)
         rejected = 0;
     __syncthreads();
-    bool rej = false;
     for (int i = tid; i < n; i += kDrawThreads) {
         head[i] = kEnd;
         const int d = i > 0 ? lemire_draw(key, (uint64_t)(n - 1 - i), (uint32_t)(i + 1)) : 0;
-        rej |= d < 0;
+        if (d < 0) {
+            const int l = atomicAdd(&rejected, 1);
+            if (l < kMaxRejects)
+                pend[1][l] = n - 1 - i;
+        }
         j[i] = (uint16_t)max(d, 0);
     }
-    if (rej)
-        rejected = 1;
     __syncthreads();
-    if (rejected) {
+    if (rejected > 0) {
         if (tid < kWave)
-            draw_row(tk, row, key, err);
-        return;
+            redraw(key, n, rejected, pend, fix);
+        __syncthreads();
+        if (fix.n < 0) {
+            for (int r = tid; r < n; r += kDrawThreads)
+                row[r] = r;
+            if (tid == 0)
+                atomicOr(err, 2);
+            return;
+        }
+        for (int f = tid; f < fix.n; f += kDrawThreads)
+            j[n - 1 - fix.t[f]] = (uint16_t)fix.j[f];
+        __syncthreads();
     }
     for (int i = tid; i < n; i += kDrawThreads)
         if (i > 0)
@@ -1489,9 +1533,13 @@ hipError_t launch_perms(const int32_t *src, const PermTask *tasks, int n_tasks, 
         return hipSuccess;
     if (src != nullptr)
         hipLaunchKernelGGL(take_perms_kernel, dim3(n_tasks), dim3(256), 0, st, src, tasks, dst, err);
-    else
+    else {
         hipLaunchKernelGGL(draw_perms_kernel, dim3(n_tasks), dim3(kDrawThreads),
                            (size_t)10 * std::max(0, std::min(max_rc, kDrawShared)) + 16, st, tasks, dst, seed, err);
+        // apart, so that the rows that need no LDS do not wait for a CU's LDS each
+        if (max_rc > kDrawShared)
+            hipLaunchKernelGGL(draw_long_perms_kernel, dim3(n_tasks), dim3(kWave), 0, st, tasks, dst, seed, err);
+    }
     return hipGetLastError();
 }
 

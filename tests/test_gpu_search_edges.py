@@ -3,7 +3,7 @@ import numpy as np
 import pytest
 
 import synth
-from synth.rng import derive_key, normal64
+from synth.rng import derive_key, normal64, stream_u64
 
 pytestmark = pytest.mark.gpu
 
@@ -176,3 +176,24 @@ def test_tuning_times_the_persistent_waves(te):
     assert persistent[0] % n == 0 and persistent[0] // n != shared[0]
     assert tuned[0] == launches * (persistent[0] // n)
     assert after == shared
+
+
+def _rejections(key, n):
+    """Draws of a row of n trials that the first round rejects."""
+    s = np.arange(n, 1, -1, dtype=np.uint64)
+    low = ((stream_u64(key, n - 1) >> np.uint64(32)) * s) & np.uint64(0xFFFFFFFF)
+    return int(np.count_nonzero(low < (np.uint64(1 << 32) - s) % s))
+
+
+def test_rows_with_rejected_draws_at_the_longest_in_lds(te):
+    """Rejected draws redrawn in rows resolved in parallel (up to 8 192 trials) and in order (above)."""
+    seed, S, trials = 18, 250, (8191, 8192, 8193)
+    held = [sum(_rejections(derive_key(seed, 77, 0, c, s), n) for s in range(S)) for c, n in enumerate(trials)]
+    print("rejected draws", held, flush=True)
+    assert min(held) >= 1
+    wl = synth.configs.Workload(name="perm", x=np.zeros((1, 8193, 12), np.float32), y=np.zeros((1, 8193, 12), np.float32),
+                                d_y=1, d_x=1, tau=1, u=1, k=4, window_start=np.ones(3, np.int32),
+                                window_len=np.full(3, 8, np.int32), trials=np.array(trials, np.int32), n_surrogates=S)
+    wl.perm_seed = seed
+    want = synth.configs.make_perms(seed, 1, wl.trials, S, 8193)
+    np.testing.assert_array_equal(te.Plan.from_workload(wl).permutations().cpu().numpy(), want)
