@@ -100,20 +100,20 @@ __host__ __device__ constexpr int slab_count(int leaves, int rem)
 __host__ __device__ constexpr int slab_first(int leaves, int slabs, int i) { return (int)((int64_t)leaves * i / slabs); }
 
 // A space of more than kSlabMax points is first cut into slabs of at most that many, which
-// workgroups of their own then order in LDS; 0: too large for that (order_big_kernel).
+// workgroups of their own then order in LDS.  Up to kMaxSlabs x kSlabMax points split_kernel cuts
+// it, above that a sort by the first coordinate (order_big_kernel).
 constexpr int kSlabMax = 8192;
 constexpr int kMaxSlabs = 64;
+__host__ __device__ constexpr bool sorted_whole(int n) { return n > kMaxSlabs * kSlabMax; }
 __host__ __device__ constexpr int order_slabs(int n, int nd)
 {
     if (n <= kSlabMax)
         return 1;
     const int nl = (n - 1) / kWave + 1;
     const int least = (nl + kSlabMax / kWave - 1) / (kSlabMax / kWave);   // slabs of at most kSlabMax points
-    if (least > kMaxSlabs)
-        return 0;
     int s = slab_count(nl, nd);
     s = s < least ? least : s;
-    return s > kMaxSlabs ? kMaxSlabs : s;
+    return s > kMaxSlabs && !sorted_whole(n) ? kMaxSlabs : s;
 }
 
 // Copy of one pre-embedded chunk into its order, with its block boxes:

@@ -592,7 +592,8 @@ __device__ __forceinline__ void scan_digits(uint32_t *cnt, uint32_t *part)
     __syncthreads();
 }
 
-// Ordering, part 1 of 2, for spaces above kSlabMax points: one workgroup cuts the space into
+// Ordering, part 1 of 2, for spaces above kSlabMax points (and up to kMaxSlabs times as many): one
+// workgroup cuts the space into
 // order_slabs() slabs of whole blocks along the first target-past coordinate.  The coordinate
 // is coded in 15 bits (its orderable image less the smallest, shifted to fit, so the code keeps
 // at least the sign, the exponent and six bits of the mantissa, and everything where the values
@@ -620,7 +621,7 @@ __global__ void __launch_bounds__(kOrderThreads) split_kernel(CoordSource src, c
     const SortTask tk = tasks[blockIdx.x];
     const int n = tk.n, nd = tk.nd > 0 ? tk.nd : d_y;
     const int slabs = order_slabs(n, nd);
-    if (slabs <= 1)
+    if (slabs <= 1 || sorted_whole(n))
         return;
     const int t = threadIdx.x, lane = t & (kWave - 1), w = t / kWave;
     const int nl = (n + kWave - 1) / kWave;
@@ -776,7 +777,7 @@ __global__ void __launch_bounds__(kOrderThreads) order_kernel(CoordSource src, c
     const SortTask tk = tasks[blockIdx.x];
     const int nd = tk.nd > 0 ? tk.nd : d_y;
     const int slabs = order_slabs(tk.n, nd);
-    if ((int)blockIdx.y >= slabs)          // also: spaces that order_big_kernel orders (no slabs)
+    if ((int)blockIdx.y >= slabs)
         return;
     const int t = threadIdx.x, lane = t & (kWave - 1), w = t / kWave;
     const int nl_all = (tk.n + kWave - 1) / kWave;
@@ -880,73 +881,60 @@ __global__ void __launch_bounds__(kOrderThreads) order_kernel(CoordSource src, c
     }
 }
 
-// Spaces above kMaxSlabs x kSlabMax points: one workgroup, a bitonic network per level over
-// npad = 2^k keys (slab, coordinate, index; padding keys sort last) in global scratch.  Every
-// stage's passes with stride below kSortLds only pair elements of the same kSortLds-aligned
-// tile, so each tile is loaded into LDS once per stage for those passes and only the wider
-// strides touch global memory.
+// Ordering, part 1 of 2, for spaces above kMaxSlabs x kSlabMax points: one workgroup sorts the map by
+// the first target-past coordinate, a bitonic network over npad = 2^k keys (coordinate, index; padding
+// keys sort last) in global scratch; order_kernel orders its slabs like the others.  Every stage's
+// passes with stride below kSortLds only pair elements of the same kSortLds-aligned tile, so each tile
+// is loaded into LDS once per stage for those passes and only the wider strides touch global memory.
+// Bound by one workgroup's passes over global memory.  BIGFIGS
 __global__ void __launch_bounds__(kOrderThreads) order_big_kernel(CoordSource src, const SortTask *__restrict__ tasks,
-                                                                  int32_t *sigma, uint64_t *scratch, int d_y)
+                                                                  int32_t *sigma, uint64_t *scratch)
 {
     __shared__ uint64_t lds[kSortLds];
     const SortTask tk = tasks[blockIdx.x];
-    const int n = tk.n, np = tk.npad, nd = tk.nd > 0 ? tk.nd : d_y;
-    if (order_slabs(n, nd) > 0)
+    const int n = tk.n, np = tk.npad;
+    if (!sorted_whole(n))
         return;
-    const int nl = (n + kWave - 1) / kWave;
     int32_t *map = sigma + tk.sig;
     uint64_t *A = scratch + tk.scratch;
-    const int ib = 31 - __builtin_clz(np);                // index bits; slab bits above the coordinate's
-    const int sb = 32 - __builtin_clz(nl);
-    const int drop = max(0, ib + sb + 32 - 64);           // low coordinate bits without room in the key
-    const uint64_t imask = ((uint64_t)1 << ib) - 1;
-    for (int m = 0; m < nd; ++m) {
-        for (int i = threadIdx.x; i < np; i += blockDim.x) {
-            uint64_t key = ~0ull;
-            if (i < n) {
-                const uint64_t o = m == 0 ? (uint64_t)i : (A[i] & imask);
-                key = (uint64_t)slab_start(i / kWave, nl, nd, m) << (ib + 32 - drop) |
-                      (uint64_t)(orderable(src.at(tk, (int)o, m)) >> drop) << ib | o;
-            }
-            A[i] = key;
-        }
+    for (int i = threadIdx.x; i < np; i += blockDim.x)
+        A[i] = i < n ? (uint64_t)orderable(src.at(tk, i, 0)) << 32 | (uint32_t)i : ~0ull;
+    __syncthreads();
+    // stages that fit a tile: sort every tile in LDS
+    for (int t0 = 0; t0 < np; t0 += kSortLds) {
+        for (int i = threadIdx.x; i < kSortLds; i += blockDim.x)
+            lds[i] = A[t0 + i];
         __syncthreads();
-        // stages that fit a tile: sort every tile in LDS
+        bitonic_lds(lds, kSortLds, 2, kSortLds, t0);
+        for (int i = threadIdx.x; i < kSortLds; i += blockDim.x)
+            A[t0 + i] = lds[i];
+        __syncthreads();
+    }
+    for (int kk = 2 * kSortLds; kk <= np; kk <<= 1) {
+        for (int jj = kk >> 1; jj >= kSortLds; jj >>= 1) {
+            bitonic_pass(A, np, kk, jj, 0);
+            __syncthreads();
+        }
         for (int t0 = 0; t0 < np; t0 += kSortLds) {
             for (int i = threadIdx.x; i < kSortLds; i += blockDim.x)
                 lds[i] = A[t0 + i];
             __syncthreads();
-            bitonic_lds(lds, kSortLds, 2, kSortLds, t0);
+            // the remaining strides of stage kk, inside this tile
+            const int nwaves = blockDim.x / kWave;
+            const int seg = kSortLds / nwaves;
+            for (int jj = kSortLds >> 1; jj >= seg; jj >>= 1) {
+                bitonic_pass(lds, kSortLds, kk, jj, t0);
+                __syncthreads();
+            }
+            bitonic_wave_passes(lds, kSortLds, kk, seg >> 1, seg, t0);
+            __syncthreads();
             for (int i = threadIdx.x; i < kSortLds; i += blockDim.x)
                 A[t0 + i] = lds[i];
             __syncthreads();
         }
-        for (int kk = 2 * kSortLds; kk <= np; kk <<= 1) {
-            for (int jj = kk >> 1; jj >= kSortLds; jj >>= 1) {
-                bitonic_pass(A, np, kk, jj, 0);
-                __syncthreads();
-            }
-            for (int t0 = 0; t0 < np; t0 += kSortLds) {
-                for (int i = threadIdx.x; i < kSortLds; i += blockDim.x)
-                    lds[i] = A[t0 + i];
-                __syncthreads();
-                // the remaining strides of stage kk, inside this tile
-                const int nwaves = blockDim.x / kWave;
-                const int seg = kSortLds / nwaves;
-                for (int jj = kSortLds >> 1; jj >= seg; jj >>= 1) {
-                    bitonic_pass(lds, kSortLds, kk, jj, t0);
-                    __syncthreads();
-                }
-                bitonic_wave_passes(lds, kSortLds, kk, seg >> 1, seg, t0);
-                __syncthreads();
-                for (int i = threadIdx.x; i < kSortLds; i += blockDim.x)
-                    A[t0 + i] = lds[i];
-                __syncthreads();
-            }
-        }
     }
     for (int i = threadIdx.x; i < n; i += blockDim.x)
-        map[i] = (int32_t)(A[i] & imask);
+        map[i] = (int32_t)(uint32_t)A[i];
 }
 
 __global__ void gather_kernel(const float *__restrict__ src, const GatherTask *__restrict__ tasks,
@@ -1503,16 +1491,14 @@ hipError_t launch_sort(const float *y, const float *pts, int64_t ld, const SortT
         hipLaunchKernelGGL(order_kernel<false>, dim3(n_tasks), dim3(kOrderThreads), 0, st, src, tasks, sigma, d_y);
         return hipGetLastError();
     }
-    // the most slabs of any task: order_slabs grows with n up to kMaxSlabs; above that there are none
+    // the most slabs of any task: order_slabs grows with n
     int slabs = order_slabs(max_n, d_y > 0 ? d_y : 1);
     for (int nd = 2; d_y == 0 && nd <= 4; ++nd)
         slabs = std::max(slabs, order_slabs(max_n, nd));
     hipLaunchKernelGGL(split_kernel, dim3(n_tasks), dim3(kOrderThreads), 0, st, src, tasks, sigma, scratch, d_y);
-    if (slabs == 0)
-        hipLaunchKernelGGL(order_big_kernel, dim3(n_tasks), dim3(kOrderThreads), 0, st, src, tasks, sigma, scratch,
-                           d_y);
-    hipLaunchKernelGGL(order_kernel<true>, dim3(n_tasks, slabs == 0 ? kMaxSlabs : slabs), dim3(kOrderThreads), 0, st,
-                       src, tasks, sigma, d_y);
+    if (sorted_whole(max_n))
+        hipLaunchKernelGGL(order_big_kernel, dim3(n_tasks), dim3(kOrderThreads), 0, st, src, tasks, sigma, scratch);
+    hipLaunchKernelGGL(order_kernel<true>, dim3(n_tasks, slabs), dim3(kOrderThreads), 0, st, src, tasks, sigma, d_y);
     return hipGetLastError();
 }
 

@@ -392,7 +392,7 @@ __global__ void __launch_bounds__(kScoreThreads) rag_score_kernel(const float *_
 }
 
 // Words of one candidate's part of the search area: states in block order, boxes, order map, and the
-// ordering's scratch (codes, or the keys of spaces too large for slabs) above kSortLds points.
+// ordering's scratch (codes, or the keys of spaces that are sorted whole) above kSortLds points.
 struct RagPart {
     int64_t box, map, scratch, total;
 };
@@ -406,7 +406,7 @@ RagPart rag_part(int64_t N, int d)
     p.scratch = p.map + up(N);
     int64_t words = 0;
     if (N > kSortLds)
-        words = order_slabs((int)N, std::min(d, kOrderDims)) > 0 ? (N + 1) / 2 : 2 * (int64_t)sort_npad((int)N);
+        words = sorted_whole((int)N) ? 2 * (int64_t)sort_npad((int)N) : (N + 1) / 2;
     p.total = p.scratch + up(words);
     return p;
 }

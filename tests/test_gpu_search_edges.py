@@ -197,3 +197,28 @@ def test_rows_with_rejected_draws_at_the_longest_in_lds(te):
     wl.perm_seed = seed
     want = synth.configs.make_perms(seed, 1, wl.trials, S, 8193)
     np.testing.assert_array_equal(te.Plan.from_workload(wl).permutations().cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("d_y,sizes", [(1, [524289, 700]), (3, [9001, 530001, 64])])
+def test_spaces_sorted_whole_beside_smaller_ones(te, monkeypatch, d_y, sizes):
+    """Above 524 288 points a sort by the first coordinate cuts the slabs, more than 64 of them."""
+    pts = normal64(derive_key(603, d_y), sum(sizes) * (2 + d_y)).reshape(2 + d_y, -1).astype(np.float32)
+    print("sorted whole", d_y, sizes, flush=True)
+    got = _statistics(te, pts, sizes, d_y, 1, 4)
+    monkeypatch.setenv("TE_NO_SORT", "1")
+    want = _statistics(te, pts, sizes, d_y, 1, 4)
+    np.testing.assert_array_equal(got[0], want[0])
+    np.testing.assert_array_equal(got[1], want[1])
+
+
+def test_embedding_choice_over_more_points_than_slabs_hold(te):
+    import torch
+    from oracle import ragwitz as rg
+    R, W = 5243, 100                          # 524 300 points
+    y = normal64(derive_key(604), R * (W + 10)).reshape(R, W + 10).astype(np.float32)
+    sample = np.unique(np.round(np.linspace(0, R * W - 1, 25)).astype(int))
+    print("ragwitz", R * W, flush=True)
+    _, pred = te.ragwitz(torch.from_numpy(y).cuda(), 8, W, [(1, 1), (3, 2)], 3, want_pred=True)
+    for c, (d, tau) in enumerate([(1, 1), (3, 2)]):
+        S, tgt = rg.states(y, d, tau, 8, W)
+        np.testing.assert_array_equal(pred[c].cpu().numpy()[sample], rg.predictions_points(S, tgt, 3, sample))
