@@ -166,6 +166,7 @@ void Batch::finish_layout()
         set_first.push_back((int32_t)chunks.size());
 
     queue_bounds(use_sets ? leaders : chunks, n_items, &part_start);
+    sort_sizes = longest_first(&sorts);
 
     size_t o = 0;
     off_coords = o;
@@ -248,6 +249,16 @@ int32_t embed_box(int64_t n, int64_t scratch)
     if (n <= kWave)
         return -1;
     return n <= kSortLds ? 0 : (int32_t)(scratch / kBoxScratchUnit) + 1;
+}
+
+// Ordering tasks in the order that launch_sort takes.
+SortSizes longest_first(std::vector<SortTask> *tasks)
+{
+    std::stable_sort(tasks->begin(), tasks->end(), [](const SortTask &a, const SortTask &b) { return a.n > b.n; });
+    SortSizes s;
+    for (const SortTask &t : *tasks)
+        s.add(t.n);
+    return s;
 }
 
 // Padded sort length: the next power of two >= n.
@@ -493,8 +504,8 @@ te_status Plan::enqueue_batch(const Batch &b, const float *x, const float *y, co
     int max_n = 0;
     for (const EmbedTask &t : b.tasks)
         max_n = std::max(max_n, t.n);
-    e = launch_sort(y, nullptr, 0, reinterpret_cast<const SortTask *>(ws + b.off_sorts), (int)b.sorts.size(), max_n,
-                    sigma, scratch, p.n_trials, p.n_samples, p.d_y, p.tau, st);
+    e = launch_sort(y, nullptr, 0, reinterpret_cast<const SortTask *>(ws + b.off_sorts), b.sort_sizes, sigma, scratch,
+                    p.n_trials, p.n_samples, p.d_y, p.tau, st);
     if (e != hipSuccess)
         return hip_fail(e, "sort launch");
     e = launch_embed(x, y, parea, sigma, scratch, u_dev, reinterpret_cast<const EmbedTask *>(ws + b.off_tasks),

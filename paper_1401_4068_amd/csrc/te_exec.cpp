@@ -409,9 +409,10 @@ te_status Plan::estimate_each(const float *x, const float *y, const int32_t *per
         const int c = g % p.n_points;
         const int64_t items = (npts[c] + kWave - 1) / kWave;
         int32_t *gerr = ctr + 4 * (int64_t)g * S1 + 1;   // the window's error word: its original's
-        if (sorted && (e = launch_sort(y, nullptr, 0, ds + g, 1, (int)npts[c], sigma, scratch, p.n_trials, p.n_samples, p.d_y,
-                                       p.tau, st)) !=
-                          hipSuccess)
+        SortSizes sizes;
+        sizes.add((int)npts[c]);
+        if (sorted && (e = launch_sort(y, nullptr, 0, ds + g, sizes, sigma, scratch, p.n_trials, p.n_samples, p.d_y,
+                                       p.tau, st)) != hipSuccess)
             break;
         if (n_surr > 0 &&
             (e = launch_perms(perms, dp + (int64_t)g * n_surr, n_surr, trials[c], parea, p.seed, gerr, st)) != hipSuccess)
@@ -638,6 +639,7 @@ te_status knn_counts_run(const float *pts, int64_t dim_stride, const int64_t *of
     }
     std::memcpy(stg + off_chunks, sorted_chunks.data(), sizeof(ChunkDesc) * n_chunks);
     std::memcpy(stg + off_items, starts.data(), sizeof(int32_t) * n_chunks);
+    const SortSizes sizes = longest_first(&sorts);
     std::memcpy(stg + off_sorts, sorts.data(), sizeof(SortTask) * n_chunks);
     std::memcpy(stg + off_gathers, gathers.data(), sizeof(GatherTask) * n_chunks);
     hipError_t e = hipMemcpyAsync(ws, stg, tbytes, hipMemcpyHostToDevice, st);
@@ -646,8 +648,7 @@ te_status knn_counts_run(const float *pts, int64_t dim_stride, const int64_t *of
     if (e == hipSuccess)
         e = launch_fill_i32(ctr, 0, 4, st);
     if (e == hipSuccess && sorted)
-        e = launch_sort(nullptr, pts, dim_stride, reinterpret_cast<const SortTask *>(ws + off_sorts), n_chunks,
-                        sorted_chunks[0].n, sigma,
+        e = launch_sort(nullptr, pts, dim_stride, reinterpret_cast<const SortTask *>(ws + off_sorts), sizes, sigma,
                         reinterpret_cast<uint64_t *>(ws + off_scratch), 0, 0, d_y, 0, st);
     if (e == hipSuccess && sorted)
         e = launch_gather(pts, reinterpret_cast<const GatherTask *>(ws + off_gathers), n_chunks,

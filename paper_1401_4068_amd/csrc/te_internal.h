@@ -101,7 +101,7 @@ __host__ __device__ constexpr int slab_first(int leaves, int slabs, int i) { ret
 
 // A space of more than kSlabMax points is first cut into slabs of at most that many, which
 // workgroups of their own then order in LDS.  Up to kMaxSlabs x kSlabMax points split_kernel cuts
-// it, above that a sort by the first coordinate (order_big_kernel).
+// it, above that a sort by the first coordinate (whole_tiles_kernel).
 constexpr int kSlabMax = 8192;
 constexpr int kMaxSlabs = 64;
 __host__ __device__ constexpr bool sorted_whole(int n) { return n > kMaxSlabs * kSlabMax; }
@@ -115,6 +115,21 @@ __host__ __device__ constexpr int order_slabs(int n, int nd)
     s = s < least ? least : s;
     return s > kMaxSlabs && !sorted_whole(n) ? kMaxSlabs : s;
 }
+
+// What the launches that order a table of tasks, longest first, need to know of it.
+struct SortSizes {
+    int n_tasks = 0;
+    int max_n = 0;    // points of the longest
+    int n_cut = 0;    // tasks above kSlabMax points
+    int n_whole = 0;  // tasks that are sorted whole
+    void add(int n)
+    {
+        ++n_tasks;
+        max_n = max_n < n ? n : max_n;
+        n_cut += n > kSlabMax;
+        n_whole += sorted_whole(n);
+    }
+};
 
 // Copy of one pre-embedded chunk into its order, with its block boxes:
 // dst[dst + m n + q] = src[src + m ld + map[q]].
@@ -192,10 +207,10 @@ hipError_t launch_fill_i32(int32_t *p, int32_t v, int64_t n, hipStream_t st);
 hipError_t launch_embed(const float *x, const float *y, const int32_t *perms, int32_t *sigma, uint64_t *scratch,
                         const int32_t *u_dev, const EmbedTask *tasks, int n_tasks, int max_n, float *base, int R,
                         int T, int d_y, int d_x, int tau, int u, int cond, int32_t *err, hipStream_t st);
-// Order maps of n_tasks search spaces of at most max_n points by their d_y target-past coordinates
-// (0: the tasks' own, at most 4; ld: the stride between the coordinates of pts, mode 1; tau: the
-// embedding delay, mode 0).
-hipError_t launch_sort(const float *y, const float *pts, int64_t ld, const SortTask *tasks, int n_tasks, int max_n,
+// Order maps of the tasks' search spaces (longest first) by their d_y target-past coordinates (0: the
+// tasks' own, at most 4; ld: the stride between the coordinates of pts, mode 1; tau: the embedding
+// delay, mode 0).
+hipError_t launch_sort(const float *y, const float *pts, int64_t ld, const SortTask *tasks, const SortSizes &sizes,
                        int32_t *sigma, uint64_t *scratch, int R, int T, int d_y, int tau, hipStream_t st);
 hipError_t launch_gather(const float *src, const GatherTask *tasks, int n_tasks, int max_n, int32_t *sigma,
                          uint64_t *scratch, float *dst, int D, int d_y, hipStream_t st);

@@ -1,6 +1,6 @@
 // te_kernels.hip -- HIP kernels of libte for gfx950 (CDNA4, wave64) around the search.
 //
-//   split_kernel, order_kernel, order_big_kernel  order a search space so that
+//   split_kernel, whole_*_kernel, order_kernel  order a search space so that
 //                    64 consecutive points are close together in the target past.
 //   embed_kernel     eq. 6-7 / eq. 10: gathers the pooled points of a window
 //                    from the raw [pair][trial][sample] series into
@@ -620,9 +620,7 @@ __global__ void __launch_bounds__(kOrderThreads) split_kernel(CoordSource src, c
     __shared__ int32_t cut_code[kMaxSlabs];
     const SortTask tk = tasks[blockIdx.x];
     const int n = tk.n, nd = tk.nd > 0 ? tk.nd : d_y;
-    const int slabs = order_slabs(n, nd);
-    if (slabs <= 1 || sorted_whole(n))
-        return;
+    const int slabs = order_slabs(n, nd);                 // at least two: the launch has no other tasks
     const int t = threadIdx.x, lane = t & (kWave - 1), w = t / kWave;
     const int nl = (n + kWave - 1) / kWave;
     int32_t *map = sigma + tk.sig;
@@ -764,7 +762,7 @@ __global__ void __launch_bounds__(kOrderThreads) split_kernel(CoordSource src, c
 // behind it 128 and 1 238 us against 36 and 624 us.
 template <bool LIST>                       // slabs of larger spaces among the tasks: their points listed in LDS
 __global__ void __launch_bounds__(kOrderThreads) order_kernel(CoordSource src, const SortTask *__restrict__ tasks,
-                                                              int32_t *sigma, int d_y)
+                                                              int32_t *sigma, int d_y, int slab0)
 {
     __shared__ struct {
         uint32_t key[kSlabMax];
@@ -777,13 +775,14 @@ __global__ void __launch_bounds__(kOrderThreads) order_kernel(CoordSource src, c
     const SortTask tk = tasks[blockIdx.x];
     const int nd = tk.nd > 0 ? tk.nd : d_y;
     const int slabs = order_slabs(tk.n, nd);
-    if ((int)blockIdx.y >= slabs)
+    const int slab = slab0 + (int)blockIdx.y;
+    if (slab >= slabs)
         return;
     const int t = threadIdx.x, lane = t & (kWave - 1), w = t / kWave;
     const int nl_all = (tk.n + kWave - 1) / kWave;
-    const int first = slab_first(nl_all, slabs, (int)blockIdx.y);
+    const int first = slab_first(nl_all, slabs, slab);
     const int base = first * kWave;
-    const int n = min(tk.n, slab_first(nl_all, slabs, (int)blockIdx.y + 1) * kWave) - base;
+    const int n = min(tk.n, slab_first(nl_all, slabs, slab + 1) * kWave) - base;
     const int nl = (n + kWave - 1) / kWave;
     int32_t *map = sigma + tk.sig;
     uint16_t *map16 = reinterpret_cast<uint16_t *>(map);
@@ -881,60 +880,75 @@ __global__ void __launch_bounds__(kOrderThreads) order_kernel(CoordSource src, c
     }
 }
 
-// Ordering, part 1 of 2, for spaces above kMaxSlabs x kSlabMax points: one workgroup sorts the map by
-// the first target-past coordinate, a bitonic network over npad = 2^k keys (coordinate, index; padding
-// keys sort last) in global scratch; order_kernel orders its slabs like the others.  Every stage's
-// passes with stride below kSortLds only pair elements of the same kSortLds-aligned tile, so each tile
-// is loaded into LDS once per stage for those passes and only the wider strides touch global memory.
-// Bound by one workgroup's passes over global memory.  BIGFIGS
-__global__ void __launch_bounds__(kOrderThreads) order_big_kernel(CoordSource src, const SortTask *__restrict__ tasks,
-                                                                  int32_t *sigma, uint64_t *scratch)
+// Ordering, part 1 of 2, for spaces above kMaxSlabs x kSlabMax points: the map sorted by the first
+// target-past coordinate, which cuts it into slabs for order_kernel.  A bitonic network over npad = 2^k
+// keys (coordinate, index; padding keys sort last) in global scratch: the stages up to kSortLds keys in
+// the LDS of a workgroup per tile of that many, then per stage a launch for each wider stride and one for
+// the strides inside the tiles.  Bound by the passes over global memory: all of it in one workgroup took
+// 30.6 ms for 600 000 points (a call with d_y = 2 36.2 ms, now 5.7).
+__global__ void __launch_bounds__(kOrderThreads) whole_tiles_kernel(CoordSource src, const SortTask *__restrict__ tasks,
+                                                                    uint64_t *scratch)
 {
     __shared__ uint64_t lds[kSortLds];
-    const SortTask tk = tasks[blockIdx.x];
-    const int n = tk.n, np = tk.npad;
-    if (!sorted_whole(n))
+    const SortTask tk = tasks[blockIdx.y];
+    const int64_t t0 = (int64_t)blockIdx.x * kSortLds;
+    if (t0 >= tk.npad)
         return;
-    int32_t *map = sigma + tk.sig;
-    uint64_t *A = scratch + tk.scratch;
-    for (int i = threadIdx.x; i < np; i += blockDim.x)
-        A[i] = i < n ? (uint64_t)orderable(src.at(tk, i, 0)) << 32 | (uint32_t)i : ~0ull;
+    uint64_t *A = scratch + tk.scratch + t0;
+    for (int x = threadIdx.x; x < kSortLds; x += kOrderThreads) {
+        const int i = (int)t0 + x;
+        lds[x] = i < tk.n ? (uint64_t)orderable(src.at(tk, i, 0)) << 32 | (uint32_t)i : ~0ull;
+    }
     __syncthreads();
-    // stages that fit a tile: sort every tile in LDS
-    for (int t0 = 0; t0 < np; t0 += kSortLds) {
-        for (int i = threadIdx.x; i < kSortLds; i += blockDim.x)
-            lds[i] = A[t0 + i];
-        __syncthreads();
-        bitonic_lds(lds, kSortLds, 2, kSortLds, t0);
-        for (int i = threadIdx.x; i < kSortLds; i += blockDim.x)
-            A[t0 + i] = lds[i];
-        __syncthreads();
-    }
-    for (int kk = 2 * kSortLds; kk <= np; kk <<= 1) {
-        for (int jj = kk >> 1; jj >= kSortLds; jj >>= 1) {
-            bitonic_pass(A, np, kk, jj, 0);
-            __syncthreads();
-        }
-        for (int t0 = 0; t0 < np; t0 += kSortLds) {
-            for (int i = threadIdx.x; i < kSortLds; i += blockDim.x)
-                lds[i] = A[t0 + i];
-            __syncthreads();
-            // the remaining strides of stage kk, inside this tile
-            const int nwaves = blockDim.x / kWave;
-            const int seg = kSortLds / nwaves;
-            for (int jj = kSortLds >> 1; jj >= seg; jj >>= 1) {
-                bitonic_pass(lds, kSortLds, kk, jj, t0);
-                __syncthreads();
-            }
-            bitonic_wave_passes(lds, kSortLds, kk, seg >> 1, seg, t0);
-            __syncthreads();
-            for (int i = threadIdx.x; i < kSortLds; i += blockDim.x)
-                A[t0 + i] = lds[i];
-            __syncthreads();
+    bitonic_lds(lds, kSortLds, 2, kSortLds, (int)t0);
+    for (int x = threadIdx.x; x < kSortLds; x += kOrderThreads)
+        A[x] = lds[x];
+}
+
+// Stride jj >= kSortLds of stage kk.
+__global__ void __launch_bounds__(256) whole_stride_kernel(const SortTask *__restrict__ tasks, uint64_t *scratch, int kk,
+                                                           int jj)
+{
+    const SortTask tk = tasks[blockIdx.y];
+    if (kk > tk.npad)
+        return;
+    uint64_t *A = scratch + tk.scratch;
+    for (int p = blockIdx.x * 256 + threadIdx.x; p < tk.npad / 2; p += gridDim.x * 256) {
+        const int i = (p & ~(jj - 1)) * 2 + (p & (jj - 1)), l = i + jj;
+        const uint64_t u0 = A[i], u1 = A[l];
+        if ((u0 > u1) == ((i & kk) == 0)) {
+            A[i] = u1;
+            A[l] = u0;
         }
     }
-    for (int i = threadIdx.x; i < n; i += blockDim.x)
-        map[i] = (int32_t)(uint32_t)A[i];
+}
+
+// The strides of stage kk inside the tiles; after a space's last stage the map.
+__global__ void __launch_bounds__(kOrderThreads) whole_merge_kernel(const SortTask *__restrict__ tasks, int32_t *sigma,
+                                                                    uint64_t *scratch, int kk)
+{
+    __shared__ uint64_t lds[kSortLds];
+    const SortTask tk = tasks[blockIdx.y];
+    const int64_t t0 = (int64_t)blockIdx.x * kSortLds;
+    if (kk > tk.npad || t0 >= tk.npad)
+        return;
+    uint64_t *A = scratch + tk.scratch + t0;
+    for (int x = threadIdx.x; x < kSortLds; x += kOrderThreads)
+        lds[x] = A[x];
+    __syncthreads();
+    constexpr int seg = kSortLds / kOrderWaves;
+    for (int jj = kSortLds >> 1; jj >= seg; jj >>= 1) {
+        bitonic_pass(lds, kSortLds, kk, jj, (int)t0);
+        __syncthreads();
+    }
+    bitonic_wave_passes(lds, kSortLds, kk, seg >> 1, seg, (int)t0);
+    __syncthreads();
+    for (int x = threadIdx.x; x < kSortLds; x += kOrderThreads) {
+        if (kk < tk.npad)
+            A[x] = lds[x];
+        else if (t0 + x < tk.n)
+            sigma[tk.sig + t0 + x] = (int32_t)(uint32_t)lds[x];
+    }
 }
 
 __global__ void gather_kernel(const float *__restrict__ src, const GatherTask *__restrict__ tasks,
@@ -1481,24 +1495,40 @@ hipError_t launch_argmax_u(const double *results, int n_groups, int n_u, const i
     return hipGetLastError();
 }
 
-hipError_t launch_sort(const float *y, const float *pts, int64_t ld, const SortTask *tasks, int n_tasks, int max_n,
+hipError_t launch_sort(const float *y, const float *pts, int64_t ld, const SortTask *tasks, const SortSizes &sizes,
                        int32_t *sigma, uint64_t *scratch, int R, int T, int d_y, int tau, hipStream_t st)
 {
-    if (n_tasks <= 0)
-        return hipSuccess;
     const CoordSource src{y, pts, ld, R, T, tau};
-    if (max_n <= kSlabMax) {
-        hipLaunchKernelGGL(order_kernel<false>, dim3(n_tasks), dim3(kOrderThreads), 0, st, src, tasks, sigma, d_y);
-        return hipGetLastError();
+    const dim3 block(kOrderThreads);
+    if (sizes.n_cut > 0) {
+        // the most slabs of any task: order_slabs grows with n
+        int slabs = order_slabs(sizes.max_n, d_y > 0 ? d_y : 1);
+        for (int nd = 2; d_y == 0 && nd <= 4; ++nd)
+            slabs = std::max(slabs, order_slabs(sizes.max_n, nd));
+        if (sizes.n_cut > sizes.n_whole)
+            hipLaunchKernelGGL(split_kernel, dim3(sizes.n_cut - sizes.n_whole), block, 0, st, src, tasks + sizes.n_whole,
+                               sigma, scratch, d_y);
+        if (sizes.n_whole > 0) {
+            int64_t np = kSortLds;
+            while (np < sizes.max_n)
+                np *= 2;
+            const dim3 tiles((unsigned)(np / kSortLds), sizes.n_whole);
+            hipLaunchKernelGGL(whole_tiles_kernel, tiles, block, 0, st, src, tasks, scratch);
+            for (int64_t kk = 2 * kSortLds; kk <= np; kk *= 2) {
+                for (int64_t jj = kk / 2; jj >= kSortLds; jj /= 2)
+                    hipLaunchKernelGGL(whole_stride_kernel, dim3((unsigned)std::min<int64_t>(8192, np / 2048), sizes.n_whole),
+                                       dim3(256), 0, st, tasks, scratch, (int)kk, (int)jj);
+                hipLaunchKernelGGL(whole_merge_kernel, tiles, block, 0, st, tasks, sigma, scratch, (int)kk);
+            }
+        }
+        constexpr int kGridY = 65535;
+        for (int s0 = 0; s0 < slabs; s0 += kGridY)
+            hipLaunchKernelGGL(order_kernel<true>, dim3(sizes.n_cut, std::min(kGridY, slabs - s0)), block, 0, st, src,
+                               tasks, sigma, d_y, s0);
     }
-    // the most slabs of any task: order_slabs grows with n
-    int slabs = order_slabs(max_n, d_y > 0 ? d_y : 1);
-    for (int nd = 2; d_y == 0 && nd <= 4; ++nd)
-        slabs = std::max(slabs, order_slabs(max_n, nd));
-    hipLaunchKernelGGL(split_kernel, dim3(n_tasks), dim3(kOrderThreads), 0, st, src, tasks, sigma, scratch, d_y);
-    if (sorted_whole(max_n))
-        hipLaunchKernelGGL(order_big_kernel, dim3(n_tasks), dim3(kOrderThreads), 0, st, src, tasks, sigma, scratch);
-    hipLaunchKernelGGL(order_kernel<true>, dim3(n_tasks, slabs), dim3(kOrderThreads), 0, st, src, tasks, sigma, d_y);
+    if (sizes.n_tasks > sizes.n_cut)
+        hipLaunchKernelGGL(order_kernel<false>, dim3(sizes.n_tasks - sizes.n_cut), block, 0, st, src,
+                           tasks + sizes.n_cut, sigma, d_y, 0);
     return hipGetLastError();
 }
 

@@ -554,11 +554,14 @@ te_status te_ragwitz(const float *y, int32_t n_trials, int32_t n_samples, int32_
         if (o > area + area_words)
             return fail(TE_ERR_NOMEM, "the search area does not hold a candidate's part");
         SortTask *tasks = reinterpret_cast<SortTask *>(wsf + area);
+        SortSizes sizes;
+        for (int c = 0; c < a.n; ++c)
+            sizes.add(N);
         rag_embed_kernel<<<dim3((unsigned)((N + 255) / 256), (unsigned)a.n), dim3(256), 0, st>>>(
             y, n_samples, window_start, window_len, N, a, wsf, tasks, c0 == 0 ? tgt : nullptr, npad, bad);
         if ((e = hipGetLastError()) != hipSuccess)
             return hip_fail(e, "rag_embed_kernel");
-        if ((e = launch_sort(nullptr, wsf, N, tasks, a.n, N, reinterpret_cast<int32_t *>(ws),
+        if ((e = launch_sort(nullptr, wsf, N, tasks, sizes, reinterpret_cast<int32_t *>(ws),
                              reinterpret_cast<uint64_t *>(ws), 0, 0, 0, 0, st)) != hipSuccess)
             return hip_fail(e, "ordering");
         rag_gather_kernel<<<dim3((unsigned)std::min(1024, (N + 1023) / 1024), (unsigned)a.n), dim3(256), 0, st>>>(a, wsf, N);

@@ -35,6 +35,7 @@ bool sorting_enabled();
 int sort_npad(int n);
 int64_t box_offset(int64_t n, int64_t at, size_t off_sigma, size_t off_scratch, size_t off_base);
 int32_t embed_box(int64_t n, int64_t scratch);
+SortSizes longest_first(std::vector<SortTask> *tasks);
 void queue_bounds(const std::vector<ChunkDesc> &pieces, int64_t n_items, std::vector<int32_t> *part_start);
 te_status knn_counts_run(const float *pts, int64_t dim_stride, const int64_t *offsets, int32_t n_chunks, int32_t d_y,
                          int32_t d_x, int32_t k, char *ws, size_t ws_bytes, hipStream_t st, float *eps,
@@ -55,7 +56,8 @@ struct Batch {
     std::vector<PermTask> perm_tasks;     // one per surrogate chunk: its trial permutation
     int max_rc = 0;                       // trials of the longest of them
     int64_t n_perm = 0;                   // int32 entries of the batch's permutation area
-    std::vector<SortTask> sorts;          // one per window group (empty when chunks are not sorted)
+    std::vector<SortTask> sorts;          // one per window group, longest first (empty when chunks are not sorted)
+    SortSizes sort_sizes;
     int64_t n_sigma = 0;                  // int32 entries of the sorted-to-original maps
     int64_t n_scratch = 0;                // uint64 sort scratch entries
     int64_t n_items = 0;

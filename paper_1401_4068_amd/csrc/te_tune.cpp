@@ -187,10 +187,11 @@ te_status te_autotune(int32_t d_y, int32_t d_x, int32_t k, int32_t n_points, int
     float *raw = reinterpret_cast<float *>(ws + off_raw);
     if (e == hipSuccess)
         e = launch_fill_uniform(raw, total * D, 0x7e5eed, st);
+    const SortSizes sizes = longest_first(&sorts);       // they are all of one length
     if (e == hipSuccess && sorted)
-        e = launch_sort(nullptr, raw, total, reinterpret_cast<const SortTask *>(ws + off_sorts), n_chunks,
-                        n_points, reinterpret_cast<int32_t *>(ws + off_sigma), reinterpret_cast<uint64_t *>(ws + off_scratch), 0,
-                        0, d_y, 0, st);
+        e = launch_sort(nullptr, raw, total, reinterpret_cast<const SortTask *>(ws + off_sorts), sizes,
+                        reinterpret_cast<int32_t *>(ws + off_sigma), reinterpret_cast<uint64_t *>(ws + off_scratch),
+                        0, 0, d_y, 0, st);
     if (e == hipSuccess && sorted)
         e = launch_gather(raw, reinterpret_cast<const GatherTask *>(ws + off_gathers), n_chunks, n_points,
                           reinterpret_cast<int32_t *>(ws + off_sigma), reinterpret_cast<uint64_t *>(ws + off_scratch),
