@@ -762,7 +762,7 @@ __global__ void __launch_bounds__(kOrderThreads) split_kernel(CoordSource src, c
 // behind it 128 and 1 238 us against 36 and 624 us.
 template <bool LIST>                       // slabs of larger spaces among the tasks: their points listed in LDS
 __global__ void __launch_bounds__(kOrderThreads) order_kernel(CoordSource src, const SortTask *__restrict__ tasks,
-                                                              int32_t *sigma, int d_y, int slab0)
+                                                              int32_t *sigma, int d_y, int n_cut, int per_cut, int64_t first_wg)
 {
     __shared__ struct {
         uint32_t key[kSlabMax];
@@ -772,10 +772,12 @@ __global__ void __launch_bounds__(kOrderThreads) order_kernel(CoordSource src, c
         uint8_t slab[kSlabMax / kWave];
     } sh;
     __shared__ uint32_t list[LIST ? kSlabMax : 1];
-    const SortTask tk = tasks[blockIdx.x];
+    // per_cut workgroups for each of the n_cut largest spaces, one for each of the others
+    const int64_t wg = first_wg + blockIdx.x, cut_wgs = (int64_t)n_cut * per_cut;
+    const SortTask tk = tasks[wg < cut_wgs ? wg / per_cut : n_cut + (wg - cut_wgs)];
+    const int slab = wg < cut_wgs ? (int)(wg % per_cut) : 0;
     const int nd = tk.nd > 0 ? tk.nd : d_y;
     const int slabs = order_slabs(tk.n, nd);
-    const int slab = slab0 + (int)blockIdx.y;
     if (slab >= slabs)
         return;
     const int t = threadIdx.x, lane = t & (kWave - 1), w = t / kWave;
@@ -1500,35 +1502,36 @@ hipError_t launch_sort(const float *y, const float *pts, int64_t ld, const SortT
 {
     const CoordSource src{y, pts, ld, R, T, tau};
     const dim3 block(kOrderThreads);
-    if (sizes.n_cut > 0) {
-        // the most slabs of any task: order_slabs grows with n
-        int slabs = order_slabs(sizes.max_n, d_y > 0 ? d_y : 1);
-        for (int nd = 2; d_y == 0 && nd <= 4; ++nd)
-            slabs = std::max(slabs, order_slabs(sizes.max_n, nd));
-        if (sizes.n_cut > sizes.n_whole)
-            hipLaunchKernelGGL(split_kernel, dim3(sizes.n_cut - sizes.n_whole), block, 0, st, src, tasks + sizes.n_whole,
-                               sigma, scratch, d_y);
-        if (sizes.n_whole > 0) {
-            int64_t np = kSortLds;
-            while (np < sizes.max_n)
-                np *= 2;
-            const dim3 tiles((unsigned)(np / kSortLds), sizes.n_whole);
-            hipLaunchKernelGGL(whole_tiles_kernel, tiles, block, 0, st, src, tasks, scratch);
-            for (int64_t kk = 2 * kSortLds; kk <= np; kk *= 2) {
-                for (int64_t jj = kk / 2; jj >= kSortLds; jj /= 2)
-                    hipLaunchKernelGGL(whole_stride_kernel, dim3((unsigned)std::min<int64_t>(8192, np / 2048), sizes.n_whole),
-                                       dim3(256), 0, st, tasks, scratch, (int)kk, (int)jj);
-                hipLaunchKernelGGL(whole_merge_kernel, tiles, block, 0, st, tasks, sigma, scratch, (int)kk);
-            }
-        }
-        constexpr int kGridY = 65535;
-        for (int s0 = 0; s0 < slabs; s0 += kGridY)
-            hipLaunchKernelGGL(order_kernel<true>, dim3(sizes.n_cut, std::min(kGridY, slabs - s0)), block, 0, st, src,
-                               tasks, sigma, d_y, s0);
+    if (sizes.n_cut == 0) {
+        if (sizes.n_tasks > 0)
+            hipLaunchKernelGGL(order_kernel<false>, dim3(sizes.n_tasks), block, 0, st, src, tasks, sigma, d_y, 0, 1, (int64_t)0);
+        return hipGetLastError();
     }
-    if (sizes.n_tasks > sizes.n_cut)
-        hipLaunchKernelGGL(order_kernel<false>, dim3(sizes.n_tasks - sizes.n_cut), block, 0, st, src,
-                           tasks + sizes.n_cut, sigma, d_y, 0);
+    if (sizes.n_cut > sizes.n_whole)
+        hipLaunchKernelGGL(split_kernel, dim3(sizes.n_cut - sizes.n_whole), block, 0, st, src, tasks + sizes.n_whole, sigma,
+                           scratch, d_y);
+    if (sizes.n_whole > 0) {
+        int64_t np = kSortLds;
+        while (np < sizes.max_n)
+            np *= 2;
+        const dim3 tiles((unsigned)(np / kSortLds), sizes.n_whole);
+        const dim3 strides((unsigned)std::min<int64_t>(8192, np / 2048), sizes.n_whole);
+        hipLaunchKernelGGL(whole_tiles_kernel, tiles, block, 0, st, src, tasks, scratch);
+        for (int64_t kk = 2 * kSortLds; kk <= np; kk *= 2) {
+            for (int64_t jj = kk / 2; jj >= kSortLds; jj /= 2)
+                hipLaunchKernelGGL(whole_stride_kernel, strides, dim3(256), 0, st, tasks, scratch, (int)kk, (int)jj);
+            hipLaunchKernelGGL(whole_merge_kernel, tiles, block, 0, st, tasks, sigma, scratch, (int)kk);
+        }
+    }
+    // the most slabs of any task: order_slabs grows with n
+    int slabs = order_slabs(sizes.max_n, d_y > 0 ? d_y : 1);
+    for (int nd = 2; d_y == 0 && nd <= 4; ++nd)
+        slabs = std::max(slabs, order_slabs(sizes.max_n, nd));
+    const int64_t wgs = (int64_t)sizes.n_cut * slabs + (sizes.n_tasks - sizes.n_cut);
+    constexpr int64_t kGrid = 1 << 21;                    // a grid holds fewer than 2^32 threads
+    for (int64_t w0 = 0; w0 < wgs; w0 += kGrid)
+        hipLaunchKernelGGL(order_kernel<true>, dim3((unsigned)std::min(kGrid, wgs - w0)), block, 0, st, src, tasks, sigma,
+                           d_y, sizes.n_cut, slabs, w0);
     return hipGetLastError();
 }
 
