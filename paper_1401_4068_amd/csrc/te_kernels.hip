@@ -822,6 +822,8 @@ __global__ void __launch_bounds__(kOrderThreads) order_kernel(CoordSource src, c
         if (m > level0 && t < nl)
             sh.slab[t] = (uint8_t)slab_start(t, nl, nd - level0, m - level0);
         block_range(lo, hi, sh.part);
+        if (lo == hi)                                     // nothing to sort by
+            continue;
         const int shift = code_shift(lo, hi, 16);
 #pragma unroll
         for (int e = 0; e < kOrderEach; ++e) {
