@@ -31,7 +31,8 @@ struct RagCand {
     int d, tau, id;
     int64_t rows;                         // states [d][N] in point order
     int64_t copy;                         // states [d][N] in block order
-    int64_t box;                          // smallest and largest of each block per coordinate, [2 d][blocks]
+    int64_t box;                          // smallest and largest of each block per coordinate, [2 d][blocks], and its
+                                          // smallest point index [blocks]
     int64_t map;                          // order map (order_at)
     int64_t scratch;                      // the ordering's scratch, 64-bit words
 };
@@ -91,17 +92,25 @@ __global__ void rag_gather_kernel(RagArgs a, float *__restrict__ ws, int N)
         const bool ok = qb + lane < N;
         const int q = ok ? qb + lane : N - 1;
         const int o = min(max(order_at(map, N, q), 0), N - 1);
-        for (int m = 0; m < c.d; ++m) {
-            const float v = ws[c.rows + (int64_t)m * N + o];
-            if (ok)
-                ws[c.copy + (int64_t)m * N + q] = v;
-            float lo, hi;
-            wave_box(v, &lo, &hi);
-            if (lane == 0) {
-                ws[c.box + (int64_t)(2 * m) * nb + qb / kWave] = lo;
-                ws[c.box + (int64_t)(2 * m + 1) * nb + qb / kWave] = hi;
+        const uint32_t least = ~wave_max_u32(~(uint32_t)o);
+        if (lane == 0)
+            reinterpret_cast<uint32_t *>(ws)[c.box + (int64_t)(2 * c.d) * nb + qb / kWave] = least;
+        float x[kRagMaxDim];                              // all loads in flight
+#pragma unroll
+        for (int m = 0; m < kRagMaxDim; ++m)
+            x[m] = m < c.d ? ws[c.rows + (int64_t)m * N + o] : 0.0f;
+#pragma unroll
+        for (int m = 0; m < kRagMaxDim; ++m)
+            if (m < c.d) {
+                if (ok)
+                    ws[c.copy + (int64_t)m * N + q] = x[m];
+                float lo, hi;
+                wave_box(x[m], &lo, &hi);
+                if (lane == 0) {
+                    ws[c.box + (int64_t)(2 * m) * nb + qb / kWave] = lo;
+                    ws[c.box + (int64_t)(2 * m + 1) * nb + qb / kWave] = hi;
+                }
             }
-        }
     }
 }
 
@@ -121,21 +130,19 @@ __device__ __forceinline__ void insert_key(uint64_t (&b)[KC], uint64_t x)
     b[0] = x < b[0] ? x : b[0];
 }
 // The k nearest of every point of a block of 64 (block order), the prediction -- the neighbours'
-// targets summed in rank order in fp64 -- and its squared error.  Four waves of 16 references each:
-// the block's own points first, every group of 16 lanes a quarter of them and the groups' lists
+// targets summed in rank order in fp64 -- and its squared error.  W waves of 64 / W references each:
+// the block's own points first, every group of 64 / W lanes every W-th of them and the groups' lists
 // merged; then, lane = candidate, the blocks whose box the references' current k-th distances
 // reach, nearer ones first (a box farther than the k-th distance holds nothing nearer, and nothing
 // equally near; rounding is monotone, so the box bound holds for binary32 differences).
 // Bound by the latency of a wave's chain of block visits: 175 us for the window of 15 000 points and the
 // twelve candidates (d = 1..6, tau = 1, 2; k = 4), all in one launch; every pair of points in index order,
 // a launch per candidate, took 2 960 us and merging its segments' lists 1 050 us.
-constexpr int kRagWaves = 4;
-constexpr int kRagRefs = kWave / kRagWaves;
-
-template <int D, int KC>
+template <int D, int KC, int W>
 __device__ __forceinline__ void rag_block(const RagCand &c, const float *ws, const float *tgt, int N, int k,
                                           double *pred, double *sq, float *lds)
 {
+    constexpr int RPW = kWave / W;             // references per wave
     constexpr int RW = (D + 2 + 3) & ~3;       // LDS row: coordinates, k-th distance, its index
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = threadIdx.x / kWave;
@@ -143,9 +150,9 @@ __device__ __forceinline__ void rag_block(const RagCand &c, const float *ws, con
     const int blk = blockIdx.x;
     const float *pts = ws + c.copy;
     const int32_t *map = reinterpret_cast<const int32_t *>(ws) + c.map;
-    float *rows = lds + wave * kRagRefs * RW;
-    const int i = blk * kWave + wave * kRagRefs + (lane & (kRagRefs - 1));
-    const bool valid = i < N && lane < kRagRefs;
+    float *rows = lds + wave * RPW * RW;
+    const int i = blk * kWave + wave * RPW + (lane & (RPW - 1));
+    const bool valid = i < N && lane < RPW;
     const int ii = min(i, N - 1);
     float ref[D];
 #pragma unroll
@@ -161,8 +168,8 @@ __device__ __forceinline__ void rag_block(const RagCand &c, const float *ws, con
     // own block (with a ragged last block, the one before it too)
     const int ob0 = (blk > 0 && N - blk * kWave < kWave) ? blk - 1 : blk;
     const int e0 = min(N, (blk + 1) * kWave);
-    for (int j0 = ob0 * kWave; j0 < e0; j0 += kRagWaves) {
-        const int j = j0 + lane / kRagRefs, jj = min(j, e0 - 1);
+    for (int j0 = ob0 * kWave; j0 < e0; j0 += W) {
+        const int j = j0 + lane / RPW, jj = min(j, e0 - 1);
         float dist = absdiff(pts[jj], ref[0]);
 #pragma unroll
         for (int m = 1; m < D; ++m)
@@ -170,7 +177,7 @@ __device__ __forceinline__ void rag_block(const RagCand &c, const float *ws, con
         insert_key<KC>(b, j < e0 && j != i ? rank_key(dist, order_at(map, N, jj)) : kNone);
     }
 #pragma unroll
-    for (int o = kRagRefs; o < kWave; o <<= 1) {
+    for (int o = RPW; o < kWave; o <<= 1) {
         uint64_t other[KC];
 #pragma unroll
         for (int p = 0; p < KC; ++p)
@@ -183,7 +190,7 @@ __device__ __forceinline__ void rag_block(const RagCand &c, const float *ws, con
     uint64_t &last = b[KC - 1];
     auto reach = [&]() { return valid ? __builtin_bit_cast(float, (uint32_t)(last >> 32)) : 0.0f; };
 
-    if (lane < kRagRefs) {
+    if (lane < RPW) {
 #pragma unroll
         for (int m = 0; m < D; ++m)
             rows[lane * RW + m] = ref[m];
@@ -199,7 +206,7 @@ __device__ __forceinline__ void rag_block(const RagCand &c, const float *ws, con
     for (int m = 0; m < D; ++m) {
         float lo = ref[m] != ref[m] ? -kInf : ref[m], hi = ref[m] != ref[m] ? kInf : ref[m];
 #pragma unroll
-        for (int o = 1; o < kRagRefs; o <<= 1) {
+        for (int o = 1; o < RPW; o <<= 1) {
             lo = fminf(lo, __shfl_xor(lo, o, 64));
             hi = fmaxf(hi, __shfl_xor(hi, o, 64));
         }
@@ -226,6 +233,14 @@ __device__ __forceinline__ void rag_block(const RagCand &c, const float *ws, con
             uint64_t want = ballot(bl < nb && (bl < ob0 || bl > blk) && g >= lim && (g < nlim || sw == 3) && !(g > cm));
             if (want == 0)
                 continue;
+            if ((want & ballot(g == cm)) != 0) {
+                // boxes at the largest k-th distance itself: their points' indices decide
+                const uint32_t worst = wave_max_u32(valid && reach() == cm ? (uint32_t)last : 0u);
+                const uint32_t least = reinterpret_cast<const uint32_t *>(bx)[(int64_t)(2 * D) * nb + bb];
+                want &= ~ballot(g == cm && least >= worst);
+                if (want == 0)
+                    continue;
+            }
             do {
                 const int cc = __builtin_ctzll(want);
                 want = clear_bit(want, cc);
@@ -307,25 +322,204 @@ __device__ __forceinline__ void rag_block(const RagCand &c, const float *ws, con
     sq[o] = e * e;
 }
 
-template <int KC>
-__global__ void __launch_bounds__(kRagWaves * kWave) rag_search_kernel(RagArgs a, const float *__restrict__ ws,
-                                                                      const float *__restrict__ tgt, int N, int k,
-                                                                      double *pred, double *sq)
+template <int KC, int W>
+__global__ void __launch_bounds__(W * kWave) rag_search_kernel(RagArgs a, const float *__restrict__ ws,
+                                                               const float *__restrict__ tgt, int N, int k,
+                                                               double *pred, double *sq)
 {
     __shared__ __attribute__((aligned(16))) float lds[kWave * ((kRagMaxDim + 2 + 3) & ~3)];
     const RagCand c = a.c[blockIdx.y];
     double *p = pred != nullptr ? pred + (int64_t)c.id * N : nullptr;
     double *q = sq + (int64_t)c.id * N;
     switch (c.d) {
-    case 1: rag_block<1, KC>(c, ws, tgt, N, k, p, q, lds); break;
-    case 2: rag_block<2, KC>(c, ws, tgt, N, k, p, q, lds); break;
-    case 3: rag_block<3, KC>(c, ws, tgt, N, k, p, q, lds); break;
-    case 4: rag_block<4, KC>(c, ws, tgt, N, k, p, q, lds); break;
-    case 5: rag_block<5, KC>(c, ws, tgt, N, k, p, q, lds); break;
-    case 6: rag_block<6, KC>(c, ws, tgt, N, k, p, q, lds); break;
-    case 7: rag_block<7, KC>(c, ws, tgt, N, k, p, q, lds); break;
-    default: rag_block<8, KC>(c, ws, tgt, N, k, p, q, lds); break;
+    case 1: rag_block<1, KC, W>(c, ws, tgt, N, k, p, q, lds); break;
+    case 2: rag_block<2, KC, W>(c, ws, tgt, N, k, p, q, lds); break;
+    case 3: rag_block<3, KC, W>(c, ws, tgt, N, k, p, q, lds); break;
+    case 4: rag_block<4, KC, W>(c, ws, tgt, N, k, p, q, lds); break;
+    case 5: rag_block<5, KC, W>(c, ws, tgt, N, k, p, q, lds); break;
+    case 6: rag_block<6, KC, W>(c, ws, tgt, N, k, p, q, lds); break;
+    case 7: rag_block<7, KC, W>(c, ws, tgt, N, k, p, q, lds); break;
+    default: rag_block<8, KC, W>(c, ws, tgt, N, k, p, q, lds); break;
     }
+}
+
+// Few points: no order, every pair.  A wave takes R references and has its lanes take every 64th point
+// each, a list of the k nearest of them per lane; the k-th smallest of the lanes' nearest distances bounds
+// the reference's k-th, so that after a few rounds hardly a point is inserted.  The lists are merged by
+// taking their smallest entry k times, and prediction and error are formed as above.
+// Bound by issue: one candidate of d = 8, 15 000 points, k = 4: 239 us a call, 342 in block order.
+constexpr int kFewWaves = 4;
+
+template <int D, int KC, int R>
+__device__ __forceinline__ void rag_few(const RagCand &c, const float *ws, const float *tgt, int N, int k, double *pred,
+                                        double *sq)
+{
+    constexpr int U = D <= 4 ? 4 : 2;          // rounds whose loads are in flight together
+    const int lane = threadIdx.x & (kWave - 1);
+    const int i0 = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * kFewWaves + threadIdx.x / kWave) * R);
+    if (i0 >= N)
+        return;
+    const float *rows = ws + c.rows;
+    float ref[R][D], bound[R];
+    uint64_t b[R][KC];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        bound[r] = kInf;
+#pragma unroll
+        for (int m = 0; m < D; ++m)
+            ref[r][m] = uload(rows + (int64_t)m * N + min(i0 + r, N - 1));
+#pragma unroll
+        for (int p = 0; p < KC; ++p)
+            b[r][p] = kNone;
+    }
+    int next = 2;                              // rounds after which the bounds are taken again
+    for (int j0 = 0, round = 0; j0 < N; j0 += U * kWave) {
+        float x[U][D];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int m = 0; m < D; ++m)
+                x[u][m] = vload_at(rows + (int64_t)m * N, (uint32_t)min(j0 + u * kWave + lane, N - 1) * 4u);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int j = j0 + u * kWave + lane;
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                float dist = absdiff(x[u][0], ref[r][0]);
+#pragma unroll
+                for (int m = 1; m < D; ++m)
+                    dist = fmaxf(dist, absdiff(x[u][m], ref[r][m]));
+                const bool in = j < N && j != i0 + r && dist < bound[r];
+                if (ballot(in)) {
+                    keep_branch();
+                    insert_key<KC>(b[r], in ? rank_key(dist, j) : kNone);
+                }
+            }
+        }
+        round += U;
+        if (round >= next && j0 + U * kWave < N) {
+            next = 2 * round;
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                uint32_t h = (uint32_t)(b[r][0] >> 32), v;
+                int left = k;
+                do {
+                    v = ~wave_max_u32(~h);
+                    left -= __builtin_popcountll(ballot(h == v));
+                    h = h == v ? ~0u : h;
+                } while (left > 0);
+                bound[r] = __builtin_bit_cast(float, v);
+            }
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        int near = 0;                          // lane p: the p-th nearest
+        for (int p = 0; p < k; ++p) {
+            const uint32_t hi = (uint32_t)(b[r][0] >> 32), lo = (uint32_t)b[r][0];
+            const uint32_t v = ~wave_max_u32(~hi);
+            const uint32_t l = ~wave_max_u32(hi == v ? ~lo : 0u);
+            if (hi == v && lo == l) {
+#pragma unroll
+                for (int q = 0; q + 1 < KC; ++q)
+                    b[r][q] = b[r][q + 1];
+                b[r][KC - 1] = kNone;
+            }
+            near = lane == p ? (int)l : near;
+        }
+        const float t = tgt[min((uint32_t)near, (uint32_t)(N - 1))];
+        double s = 0.0;
+        for (int p = 0; p < k; ++p)
+            s += (double)readlane_f(t, p);
+        const int i = i0 + r;
+        if (lane == 0 && i < N) {
+            const double yhat = s / (double)k;
+            if (pred != nullptr)
+                pred[i] = yhat;
+            const double e = (double)tgt[i] - yhat;
+            sq[i] = e * e;
+        }
+    }
+}
+
+template <int KC, int R>
+__global__ void __launch_bounds__(kFewWaves * kWave) rag_few_kernel(RagArgs a, const float *__restrict__ ws,
+                                                                    const float *__restrict__ tgt, int N, int k,
+                                                                    double *pred, double *sq)
+{
+    const RagCand c = a.c[blockIdx.y];
+    double *p = pred != nullptr ? pred + (int64_t)c.id * N : nullptr;
+    double *q = sq + (int64_t)c.id * N;
+    switch (c.d) {
+    case 1: rag_few<1, KC, R>(c, ws, tgt, N, k, p, q); break;
+    case 2: rag_few<2, KC, R>(c, ws, tgt, N, k, p, q); break;
+    case 3: rag_few<3, KC, R>(c, ws, tgt, N, k, p, q); break;
+    case 4: rag_few<4, KC, R>(c, ws, tgt, N, k, p, q); break;
+    case 5: rag_few<5, KC, R>(c, ws, tgt, N, k, p, q); break;
+    case 6: rag_few<6, KC, R>(c, ws, tgt, N, k, p, q); break;
+    case 7: rag_few<7, KC, R>(c, ws, tgt, N, k, p, q); break;
+    default: rag_few<8, KC, R>(c, ws, tgt, N, k, p, q); break;
+    }
+}
+
+template <int KC>
+void launch_rag_search(const RagArgs &a, const float *ws, const float *tgt, int N, int k, double *pred, double *sq, int w,
+                       hipStream_t st)
+{
+    const dim3 grid((unsigned)((N + kWave - 1) / kWave), (unsigned)a.n), block(w * kWave);
+    if (w == 8)
+        rag_search_kernel<KC, 8><<<grid, block, 0, st>>>(a, ws, tgt, N, k, pred, sq);
+    else
+        rag_search_kernel<KC, 4><<<grid, block, 0, st>>>(a, ws, tgt, N, k, pred, sq);
+}
+
+// (the list capacity is the smallest of 4, 8, 16 that holds k)
+hipError_t launch_rag_search(const RagArgs &a, const float *ws, const float *tgt, int N, int k, double *pred, double *sq,
+                             hipStream_t st)
+{
+    // blocks of the launch to eight waves each while those are few for the chip (us a call, eight / four
+    // waves: 705 blocks (15 000 points, d = 2, 4, 6, k = 4) 263 / 287, 1 880 (d = 1..8) 428 / 417 and at k = 8
+    // 556 / 578, 2 820 (d = 1..6, two delays) 365 / 362 and 511 / 497)
+    const int w = (int64_t)((N + kWave - 1) / kWave) * a.n <= 2048 ? 8 : 4;
+    if (k <= 4)
+        launch_rag_search<4>(a, ws, tgt, N, k, pred, sq, w, st);
+    else if (k <= 8)
+        launch_rag_search<8>(a, ws, tgt, N, k, pred, sq, w, st);
+    else
+        launch_rag_search<16>(a, ws, tgt, N, k, pred, sq, w, st);
+    return hipGetLastError();
+}
+
+// Launches of at most so many pairs of points go without an order.  us a call, k = 4, every pair / ordered
+// (AR series, values rounded to integers): 4 000 points, 12 candidates (192 M pairs) 175 / 200 and 147 / 226;
+// 24 candidates (256 + 128 M) 338 / 378 and 281 / 418; 15 000 points, one of d = 8 (225 M) 239 / 342 and
+// 224 / 429, one of d = 3 183 / 178 and 156 / 185; d = 2, 4, 6 (675 M) 382 / 263 and 327 / 301.
+constexpr int64_t kFewPairs = 1 << 28;
+
+template <int KC>
+void launch_rag_few(const RagArgs &a, const float *ws, const float *tgt, int N, int k, double *pred, double *sq,
+                    hipStream_t st)
+{
+    // two references to a wave share the points' loads; one while the waves are few (us a call, one / two:
+    // 4 000 points, k = 16, one candidate 115 / 127, 12 candidates 514 / 508)
+    const int r = (int64_t)N * a.n <= 8192 ? 1 : 2;
+    const dim3 grid((unsigned)((N + kFewWaves * r - 1) / (kFewWaves * r)), (unsigned)a.n), block(kFewWaves * kWave);
+    if (r == 1)
+        rag_few_kernel<KC, 1><<<grid, block, 0, st>>>(a, ws, tgt, N, k, pred, sq);
+    else
+        rag_few_kernel<KC, 2><<<grid, block, 0, st>>>(a, ws, tgt, N, k, pred, sq);
+}
+
+hipError_t launch_rag_few(const RagArgs &a, const float *ws, const float *tgt, int N, int k, double *pred, double *sq,
+                          hipStream_t st)
+{
+    if (k <= 4)
+        launch_rag_few<4>(a, ws, tgt, N, k, pred, sq, st);
+    else if (k <= 8)
+        launch_rag_few<8>(a, ws, tgt, N, k, pred, sq, st);
+    else
+        launch_rag_few<16>(a, ws, tgt, N, k, pred, sq, st);
+    return hipGetLastError();
 }
 
 // Fixed-order sum over a workgroup of kScoreThreads threads.
@@ -402,7 +596,7 @@ RagPart rag_part(int64_t N, int d)
     auto up = [](int64_t v) { return (v + 15) / 16 * 16; };
     RagPart p;
     p.box = up(N * d);
-    p.map = p.box + up(2 * d * ((N + kWave - 1) / kWave));
+    p.map = p.box + up((2 * d + 1) * ((N + kWave - 1) / kWave));
     p.scratch = p.map + up(N);
     int64_t words = 0;
     if (N > kSortLds)
@@ -554,28 +748,26 @@ te_status te_ragwitz(const float *y, int32_t n_trials, int32_t n_samples, int32_
         if (o > area + area_words)
             return fail(TE_ERR_NOMEM, "the search area does not hold a candidate's part");
         SortTask *tasks = reinterpret_cast<SortTask *>(wsf + area);
-        SortSizes sizes;
-        for (int c = 0; c < a.n; ++c)
-            sizes.add(N);
         rag_embed_kernel<<<dim3((unsigned)((N + 255) / 256), (unsigned)a.n), dim3(256), 0, st>>>(
             y, n_samples, window_start, window_len, N, a, wsf, tasks, c0 == 0 ? tgt : nullptr, npad, bad);
         if ((e = hipGetLastError()) != hipSuccess)
             return hip_fail(e, "rag_embed_kernel");
+        if ((int64_t)N * N * a.n <= kFewPairs) {
+            if ((e = launch_rag_few(a, wsf, tgt, N, k, pred, sq, st)) != hipSuccess)
+                return hip_fail(e, "rag_few_kernel");
+            c0 += a.n;
+            continue;
+        }
+        SortSizes sizes;
+        for (int c = 0; c < a.n; ++c)
+            sizes.add(N);
         if ((e = launch_sort(nullptr, wsf, N, tasks, sizes, reinterpret_cast<int32_t *>(ws),
                              reinterpret_cast<uint64_t *>(ws), 0, 0, 0, 0, st)) != hipSuccess)
             return hip_fail(e, "ordering");
-        rag_gather_kernel<<<dim3((unsigned)std::min(1024, (N + 1023) / 1024), (unsigned)a.n), dim3(256), 0, st>>>(a, wsf, N);
+        rag_gather_kernel<<<dim3((unsigned)std::min(1024, (N + 255) / 256), (unsigned)a.n), dim3(256), 0, st>>>(a, wsf, N);
         if ((e = hipGetLastError()) != hipSuccess)
             return hip_fail(e, "rag_gather_kernel");
-        const dim3 grid((unsigned)((N + kWave - 1) / kWave), (unsigned)a.n), block(kRagWaves * kWave);
-        // the list capacity is the smallest of 4, 8, 16 that holds k
-        if (k <= 4)
-            rag_search_kernel<4><<<grid, block, 0, st>>>(a, wsf, tgt, N, k, pred, sq);
-        else if (k <= 8)
-            rag_search_kernel<8><<<grid, block, 0, st>>>(a, wsf, tgt, N, k, pred, sq);
-        else
-            rag_search_kernel<16><<<grid, block, 0, st>>>(a, wsf, tgt, N, k, pred, sq);
-        if ((e = hipGetLastError()) != hipSuccess)
+        if ((e = launch_rag_search(a, wsf, tgt, N, k, pred, sq, st)) != hipSuccess)
             return hip_fail(e, "rag_search_kernel");
         c0 += a.n;
     }

@@ -222,3 +222,25 @@ def test_embedding_choice_over_more_points_than_slabs_hold(te):
     for c, (d, tau) in enumerate([(1, 1), (3, 2)]):
         S, tgt = rg.states(y, d, tau, 8, W)
         np.testing.assert_array_equal(pred[c].cpu().numpy()[sample], rg.predictions_points(S, tgt, 3, sample))
+
+
+@pytest.mark.parametrize("kind", ["gauss", "grid", "constant"])
+@pytest.mark.parametrize("R,W,n", [(1, 18, 3), (3, 43, 1), (16, 16, 2), (3, 910, 3), (3, 911, 3),    # every pair: one and two
+                                   (17, 241, 16), (64, 65, 16), (121, 68, 16)])       # references a wave; 8 and 4 waves a block
+def test_embedding_choice_at_the_lines_of_its_searches(te, kind, R, W, n):
+    import torch
+    from oracle import ragwitz as rg
+    y = normal64(derive_key(605, R, W), R * (W + 20)).reshape(R, W + 20)
+    if kind == "grid":
+        y = np.round(y)
+    elif kind == "constant":
+        y[:] = 2.0
+    y = y.astype(np.float32)
+    cands = [(8, 1), (3, 2), (1, 1)][:n] if n < 16 else [(d, tau) for d in range(1, 9) for tau in (1, 2)]
+    sample = np.unique(np.round(np.linspace(0, R * W - 1, 30)).astype(int))
+    for k in (1, 3, 5, 16):
+        print("ragwitz", kind, R * W, n, k, flush=True)
+        _, pred = te.ragwitz(torch.from_numpy(y).cuda(), 18, W, cands, k, want_pred=True)
+        for c in range(0, len(cands), 1 if n < 16 else 5):
+            S, tgt = rg.states(y, *cands[c], 18, W)
+            np.testing.assert_array_equal(pred[c].cpu().numpy()[sample], rg.predictions_points(S, tgt, k, sample))
