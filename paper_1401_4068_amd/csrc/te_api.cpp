@@ -254,7 +254,9 @@ int32_t embed_box(int64_t n, int64_t scratch)
 // Ordering tasks in the order that launch_sort takes.
 SortSizes longest_first(std::vector<SortTask> *tasks)
 {
-    std::stable_sort(tasks->begin(), tasks->end(), [](const SortTask &a, const SortTask &b) { return a.n > b.n; });
+    auto longer = [](const SortTask &a, const SortTask &b) { return a.n > b.n; };
+    if (!std::is_sorted(tasks->begin(), tasks->end(), longer))
+        std::stable_sort(tasks->begin(), tasks->end(), longer);
     SortSizes s;
     for (const SortTask &t : *tasks)
         s.add(t.n);

@@ -639,8 +639,11 @@ te_status knn_counts_run(const float *pts, int64_t dim_stride, const int64_t *of
     }
     std::memcpy(stg + off_chunks, sorted_chunks.data(), sizeof(ChunkDesc) * n_chunks);
     std::memcpy(stg + off_items, starts.data(), sizeof(int32_t) * n_chunks);
-    const SortSizes sizes = longest_first(&sorts);
-    std::memcpy(stg + off_sorts, sorts.data(), sizeof(SortTask) * n_chunks);
+    SortSizes sizes;
+    for (int i = 0; i < n_chunks; ++i) {
+        reinterpret_cast<SortTask *>(stg + off_sorts)[i] = sorts[order[i]];
+        sizes.add(sorts[order[i]].n);
+    }
     std::memcpy(stg + off_gathers, gathers.data(), sizeof(GatherTask) * n_chunks);
     hipError_t e = hipMemcpyAsync(ws, stg, tbytes, hipMemcpyHostToDevice, st);
     int32_t *ctr = reinterpret_cast<int32_t *>(ws + off_ctr);
