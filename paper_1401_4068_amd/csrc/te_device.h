@@ -165,21 +165,29 @@ __device__ __forceinline__ int order_at(const int32_t *map, int n, int i)
     return n <= kSortLds ? (int)reinterpret_cast<const uint16_t *>(map)[i] : map[i];
 }
 
+// Middle one of three (one v_med3_u32).
+__device__ __forceinline__ uint32_t med3_u32(uint32_t a, uint32_t b, uint32_t c)
+{
+    return max(min(a, b), min(max(a, b), c));
+}
+
 // Sorted-list insertion of x into the KP1 smallest values b[0] <= ... <= b[KP1-1]:
 // from the top down, bi' = med3(b(i-1), bi, x), then b0' = min(b0, x).  Each
 // step reads only entries not yet updated, so the list is rewritten in place
 // (KP1 VALU ops, no copies).  Leaves the list unchanged when x >= b[KP1-1], so
 // it can run on every lane of the wave.  All values are non-negative floats
-// (+0 .. +inf), whose bit patterns order like unsigned integers; the minimum
-// is taken on the bits (no NaN canonicalisation needed).
+// (+0 .. +inf) or no numbers, taken by their bit patterns, which order like
+// unsigned integers: one that is no number is beyond every other (the float
+// median would take it for the smallest).
 template <int KP1>
 __device__ __forceinline__ void insert_sorted(float (&b)[KP1], float x)
 {
+    const uint32_t u = __builtin_bit_cast(uint32_t, x);
 #pragma unroll
     for (int i = KP1 - 1; i >= 1; --i)
-        b[i] = __builtin_amdgcn_fmed3f(b[i - 1], b[i], x);
-    const uint32_t lo = min(__builtin_bit_cast(uint32_t, b[0]), __builtin_bit_cast(uint32_t, x));
-    b[0] = __builtin_bit_cast(float, lo);
+        b[i] = __builtin_bit_cast(float, med3_u32(__builtin_bit_cast(uint32_t, b[i - 1]),
+                                                  __builtin_bit_cast(uint32_t, b[i]), u));
+    b[0] = __builtin_bit_cast(float, min(__builtin_bit_cast(uint32_t, b[0]), u));
 }
 
 template <int KP1, bool GENERIC>

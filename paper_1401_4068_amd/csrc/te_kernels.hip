@@ -104,15 +104,14 @@ __global__ void __launch_bounds__(kMaxWavesPerWG * 64) search_unordered_kernel(S
         float thr = kInf;
 
         // current k+1-th distance of this lane: a candidate can only enter the
-        // list if its joint distance is strictly below it (one that is no number is
-        // beyond every other one)
+        // list if its joint distance is strictly below it
         auto cur = [&]() { return GENERIC ? thr : best[KP1 - 1]; };
         auto visit = [&](const float (&c)[D]) {
             const PairDist<DY, DX> d = pair_dist<DY, DX>(ref, c);
             const float dj = fmaxf(d.t, fmaxf(d.p, d.s));
             if (ballot(dj < cur())) {
                 keep_branch();
-                insert_sorted<KP1>(best, fminf(dj, kInf));
+                insert_sorted<KP1>(best, dj);
                 if (GENERIC)
                     thr = kth<KP1, GENERIC>(best, k);
             }
@@ -148,7 +147,7 @@ __global__ void __launch_bounds__(kMaxWavesPerWG * 64) search_unordered_kernel(S
                 for (int u = 0; u < 4; ++u)
                     if (ballot(dj[u] < cur())) {
                         keep_branch();
-                        insert_sorted<KP1>(best, fminf(dj[u], kInf));
+                        insert_sorted<KP1>(best, dj[u]);
                         if (GENERIC)
                             thr = kth<KP1, GENERIC>(best, k);
                     }

@@ -150,8 +150,7 @@ __device__ __forceinline__ void block_search(const SearchArgs &a)
             for (int s = 0; s < KP1; ++s)
                 best[v][s] = s < fill ? 0.0f : kInf;
         auto cur = [&](int v) { return best[v][KP1 - 1]; };
-        // (pre-embedded points: a distance that is no number is beyond every other one)
-        auto insert = [&](int v, float x) { insert_sorted<KP1>(best[v], OUT ? fminf(x, kInf) : x); };
+        auto insert = [&](int v, float x) { insert_sorted<KP1>(best[v], x); };
         // largest current radius over the variants (0 in lanes past the chunk's end): a
         // candidate at least that far away is of no use to any variant
         auto curmax = [&]() {
