@@ -226,7 +226,7 @@ struct ordered_search {
     size_t lds;
 };
 ordered_search pick_ordered(int d_y, int d_x, int k, int slots, bool sets, int waves_per_wg);
-int waves_to_a_block(int64_t n_items, int set_coords, int k);
+int waves_to_a_block(int64_t n_items, int set_coords, int k, bool queues);
 ordered_search pick_shared(int d_y, int d_x, int k, bool sets, int w);
 // With pv != nullptr the launch also computes the n_groups p-values (results laid
 // out [group][original, surrogates...]; NaN when *err is set) and copies *err to

@@ -1434,7 +1434,7 @@ hipError_t launch_search(const SearchArgs &a, int d_y, int d_x, const SearchConf
     const int blocks = (grid_waves + wpg - 1) / wpg;
     ordered_search s{nullptr, 0};
     const int set_coords = a.set_first != nullptr ? 1 + d_y + set_variants(d_y, d_x) * d_x : 0;
-    const int w = a.sorted && !cfg.timed ? waves_to_a_block(a.n_items, set_coords, a.k) : 0;
+    const int w = a.sorted && !cfg.timed ? waves_to_a_block(a.n_items, set_coords, a.k, a.n_parts > 1) : 0;
     if (w > 0) {
         s = pick_shared(d_y, d_x, a.k, a.set_first != nullptr, w);
         if (!s.fn)
