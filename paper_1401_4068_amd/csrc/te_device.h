@@ -21,9 +21,8 @@ typedef const __attribute__((address_space(4))) f4v __attribute__((aligned(4))) 
 // scalar and vector-typed values are loaded this way (aggregate copies would
 // be lowered to vector-memory loads).
 __device__ __forceinline__ float uload(const float *p) { return *(cfloat_t *)p; }
-__device__ __forceinline__ f4v uload4(const float *p) { return *(cf4_t *)p; }
-// the same at a 32-bit byte offset from a wave-uniform base: one SGPR offset shared
-// by several bases, so the loads need no 64-bit address arithmetic
+// four at a 32-bit byte offset from a wave-uniform base: one SGPR offset shared by
+// several bases, so the loads need no 64-bit address arithmetic
 __device__ __forceinline__ f4v uload4_at(const float *p, uint32_t byte_off)
 {
     typedef const __attribute__((address_space(4))) char cchar_t;

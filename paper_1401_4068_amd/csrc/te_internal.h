@@ -171,7 +171,8 @@ struct SearchArgs {
 // (1, 3) 19 939 / 20 189 / 23 806, (2, 2) 7 978 / 7 601 / 8 073, (3, 3) 12 530 / 12 873 / 13 109,
 // (4, 4) 19 773 / 19 796 / -; 40 windows of 2 400 points x 101: (3, 3) 4 704 / 4 434 / 4 386,
 // (4, 4) 5 995 / 5 738 / 6 247; with one source coordinate: (1, 1) 2 592 / 2 497 / 2 367,
-// (2, 1) 2 738 / 2 573 / 2 399.
+// (2, 1) 2 738 / 2 573 / 2 399.  Two are 1 to 3 % ahead on large windows at (1, 3) and (3, 3) and 4 to 6 %
+// behind on small ones, so three serve all sizes.
 constexpr int set_variants(int d_y, int d_x)
 {
     return d_x == 1 ? 4 : 3;

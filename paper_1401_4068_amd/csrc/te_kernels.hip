@@ -761,7 +761,8 @@ __global__ void __launch_bounds__(kOrderThreads) split_kernel(CoordSource src, c
 // behind it 128 and 1 238 us against 36 and 624 us.
 template <bool LIST>                       // slabs of larger spaces among the tasks: their points listed in LDS
 __global__ void __launch_bounds__(kOrderThreads) order_kernel(CoordSource src, const SortTask *__restrict__ tasks,
-                                                              int32_t *sigma, int d_y, int n_cut, int per_cut, int64_t first_wg)
+                                                              int32_t *sigma, int d_y, int n_cut, int per_cut,
+                                                              int64_t first_wg)
 {
     __shared__ struct {
         uint32_t key[kSlabMax];
@@ -1505,12 +1506,13 @@ hipError_t launch_sort(const float *y, const float *pts, int64_t ld, const SortT
     const dim3 block(kOrderThreads);
     if (sizes.n_cut == 0) {
         if (sizes.n_tasks > 0)
-            hipLaunchKernelGGL(order_kernel<false>, dim3(sizes.n_tasks), block, 0, st, src, tasks, sigma, d_y, 0, 1, (int64_t)0);
+            hipLaunchKernelGGL(order_kernel<false>, dim3(sizes.n_tasks), block, 0, st, src, tasks, sigma, d_y, 0, 1,
+                               (int64_t)0);
         return hipGetLastError();
     }
     if (sizes.n_cut > sizes.n_whole)
-        hipLaunchKernelGGL(split_kernel, dim3(sizes.n_cut - sizes.n_whole), block, 0, st, src, tasks + sizes.n_whole, sigma,
-                           scratch, d_y);
+        hipLaunchKernelGGL(split_kernel, dim3(sizes.n_cut - sizes.n_whole), block, 0, st, src, tasks + sizes.n_whole,
+                           sigma, scratch, d_y);
     if (sizes.n_whole > 0) {
         int64_t np = kSortLds;
         while (np < sizes.max_n)

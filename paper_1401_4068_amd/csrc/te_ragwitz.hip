@@ -764,7 +764,8 @@ te_status te_ragwitz(const float *y, int32_t n_trials, int32_t n_samples, int32_
         if ((e = launch_sort(nullptr, wsf, N, tasks, sizes, reinterpret_cast<int32_t *>(ws),
                              reinterpret_cast<uint64_t *>(ws), 0, 0, 0, 0, st)) != hipSuccess)
             return hip_fail(e, "ordering");
-        rag_gather_kernel<<<dim3((unsigned)std::min(1024, (N + 255) / 256), (unsigned)a.n), dim3(256), 0, st>>>(a, wsf, N);
+        const dim3 gather((unsigned)std::min(1024, (N + 255) / 256), (unsigned)a.n);   // a wave per block of points
+        rag_gather_kernel<<<gather, dim3(256), 0, st>>>(a, wsf, N);
         if ((e = hipGetLastError()) != hipSuccess)
             return hip_fail(e, "rag_gather_kernel");
         if ((e = launch_rag_search(a, wsf, tgt, N, k, pred, sq, st)) != hipSuccess)

@@ -61,8 +61,8 @@ ordered_search pick_ordered(int d_y, int d_x, int k, int slots, bool sets, int w
 //     k = 8 0.971 / 1.016 / 1.056 / 1.067 (large spaces gain longer: five of 10 240 points, (3, 3), 198 against 231 us)
 //   2 waves against 4, 3 000 / 4 100 / 6 200: k = 1 0.955 / 0.931 / 0.886, k = 4 1.007 / 0.978 / 0.938, k = 6 1.023 /
 //     0.989 / 0.947
-//   2 waves against persistent ones and one queue, 8 200 / 12 500 / 16 400 / 25 000: k = 1 0.799 / 0.877 / 0.933 / 0.997,
-//     k = 3 0.875 / 0.944 / 0.997 / 1.060, k = 4 0.905 / 0.966 / 1.025 / 1.082, k = 6 1.026 / 1.076 / 1.131 / 1.202;
+//   2 waves against persistent ones and one queue, 8 200 / 12 500 / 16 400 / 25 000: k = 1 0.799 / 0.877 / 0.933 /
+//     0.997, k = 3 0.875 / 0.944 / 0.997 / 1.060, k = 4 0.905 / 0.966 / 1.025 / 1.082, k = 6 1.026 / 1.076 / 1.131 / 1.202;
 //     queues, 16 400 / 24 600 / 32 800 / 49 000: k = 1 0.50 / 0.70 / 0.75 / 0.85, k = 4 0.61 / 0.82 / 0.87 / 0.97,
 //     k = 6 0.74 / 0.96 / 1.01 / 1.11, k = 8 0.82 / 1.05 / 1.10 / 1.21 (the line is where spaces of
 //     15 500 points stop gaining: 0.90 / 0.98 / 1.13 at k = 4)
@@ -73,8 +73,9 @@ ordered_search pick_ordered(int d_y, int d_x, int k, int slots, bool sets, int w
 //   sets (queues), 8 / 4 / 2 waves against persistent ones:
 //     (1, 1) 512 / 700 / 1 000 blocks 0.51 / 0.54 / 0.81, 0.56 / 0.55 / 0.78, 0.69 / 0.59 / 0.75; 3 000 / 9 200 / 12 500
 //       1.09 / 0.83 / 0.86, 1.40 / 0.97 / 0.89, 1.62 / 1.11 / 0.99
-//     (2, 2) 0.46 / 0.48 / 0.76, 0.51 / 0.50 / 0.74, 0.66 / 0.58 / 0.75; 1.24 / 0.93 / 0.98, 1.60 / 1.09 / 1.00, 1.74 / 1.16 / 1.04
-//     (3, 3) 0.41 / 0.43 / 0.68, 0.45 / 0.44 / 0.67, 0.57 / 0.51 / 0.67; 3 000 / 9 200 1.13 / 0.96 / 1.01, 1.50 / 1.18 / 1.09
+//     (2, 2) 0.46 / 0.48 / 0.76, 0.51 / 0.50 / 0.74, 0.66 / 0.58 / 0.75; 1.24 / 0.93 / 0.98, 1.60 / 1.09 / 1.00,
+//       1.74 / 1.16 / 1.04
+//     (3, 3) 0.41 / 0.43 / 0.68, 0.45 / 0.44 / 0.67, 0.57 / 0.51 / 0.67; 1.13 / 0.96 / 1.01, 1.50 / 1.18 / 1.09
 //     (4, 4) 0.39 / 0.43 / 0.66, 0.43 / 0.44 / 0.65, 0.57 / 0.50 / 0.68; 1.10 / 0.94 / 1.07, 1.39 / 1.10 / 1.20
 // A set's pairs of up to nine coordinates leave the persistent waves idle up to 9 000 blocks, wider ones do not.
 int waves_to_a_block(int64_t n_items, int set_coords, int k, bool queues)

@@ -432,19 +432,20 @@ bool Server::admit_one(Job *j)
     int32_t *perm = reinterpret_cast<int32_t *>(bat + b.off_perm);
     if (e == hipSuccess && !b.perm_tasks.empty())
         e = launch_perms(j->n_perm ? reinterpret_cast<const int32_t *>(reg + j->off_perm) : nullptr,
-                         reinterpret_cast<const PermTask *>(bat + b.off_ptasks), (int)b.perm_tasks.size(), b.max_rc, perm,
-                         P.p.seed, ctr + 1, setup_stream);
+                         reinterpret_cast<const PermTask *>(bat + b.off_ptasks), (int)b.perm_tasks.size(), b.max_rc,
+                         perm, P.p.seed, ctr + 1, setup_stream);
     int32_t *sigma = reinterpret_cast<int32_t *>(bat + b.off_sigma);
     uint64_t *scratch = reinterpret_cast<uint64_t *>(bat + b.off_scratch);
+    const float *x = reinterpret_cast<const float *>(reg + j->off_x);
+    const float *y = reinterpret_cast<const float *>(reg + j->off_y);
     if (e == hipSuccess)
-        e = launch_sort(reinterpret_cast<const float *>(reg + j->off_y), nullptr, 0,
-                        reinterpret_cast<const SortTask *>(bat + b.off_sorts), b.sort_sizes, sigma, scratch, P.p.n_trials,
-                        P.p.n_samples, P.p.d_y, P.p.tau, setup_stream);
+        e = launch_sort(y, nullptr, 0, reinterpret_cast<const SortTask *>(bat + b.off_sorts), b.sort_sizes, sigma,
+                        scratch, P.p.n_trials, P.p.n_samples, P.p.d_y, P.p.tau, setup_stream);
     if (e == hipSuccess)
-        e = launch_embed(reinterpret_cast<const float *>(reg + j->off_x), reinterpret_cast<const float *>(reg + j->off_y),
-                         perm, sigma, scratch, nullptr, reinterpret_cast<const EmbedTask *>(bat + b.off_tasks),
+        e = launch_embed(x, y, perm, sigma, scratch, nullptr, reinterpret_cast<const EmbedTask *>(bat + b.off_tasks),
                          (int)b.tasks.size(), embed_max_n(b), reinterpret_cast<float *>(bat + b.off_coords),
-                         P.p.n_trials, P.p.n_samples, P.p.d_y, P.p.d_x, P.p.tau, P.p.u, P.p.cond_source, ctr + 1, setup_stream);
+                         P.p.n_trials, P.p.n_samples, P.p.d_y, P.p.d_x, P.p.tau, P.p.u, P.p.cond_source, ctr + 1,
+                         setup_stream);
     if (e == hipSuccess)
         e = hipEventCreateWithFlags(&j->ready_ev, hipEventDisableTiming);
     if (e == hipSuccess)
