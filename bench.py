@@ -77,8 +77,8 @@ def valu_ceiling(sub: float, mx: float, cmp: float) -> float:
 # device copy measured the same way (factors 2.000 and 1.000), keyed by (kernel source, workload); any other
 # kernel source reports null.
 RECORDED_TRAFFIC = {
-    ("751bdc6e0620", "uneven_chunks_200_surrogates"): 112927948800,
-    ("751bdc6e0620", "nonlinear_ar_ensemble"): 435912328,
+    ("e53b5b614822", "uneven_chunks_200_surrogates"): 113796510800,
+    ("e53b5b614822", "nonlinear_ar_ensemble"): 432240168,
 }
 KERNEL_SRC = [os.path.join(ROOT, "paper_1401_4068_amd", "csrc", f)
               for f in ("te_device.h", "te_search.hip", "te_search.h", "te_search_sets.hip")]
