@@ -533,8 +533,8 @@ __device__ __forceinline__ void block_search(const SearchArgs &a)
         unsigned long long evaluated2 = 0;                // candidate-reference pairs examined in pass 2
         // Pre-embedded points may be infinite or no numbers: a coordinate without a difference says nothing
         // about its pair (fmaxf passes it over), but a pair without any in one space is outside the balls of
-        // both, so there the larger of two distances is no number if one of them is none.
-        auto larger = [](float d, float e) { return OUT ? __builtin_elementwise_maximum(d, e) : fmaxf(d, e); };
+        // both, so there n_TP and n_PS are taken from both spaces' comparisons.  (The larger of the distances
+        // as a maximum that keeps a NaN, v_maximum3_f32, was 1 to 2 % slower.)
         // counts of the references in todo over NS blocks of candidates
         auto count = [&](uint64_t todo, auto ns, const float (*ct)[DT], const float (*cs)[V][DX]) {
             constexpr int NS = decltype(ns)::value;
@@ -559,7 +559,7 @@ __device__ __forceinline__ void block_search(const SearchArgs &a)
 #pragma unroll
                     for (int m = 2; m < DT; ++m)
                         dp = fmaxf(dp, absdiff(rr[m], ct[sl][m]));
-                    const float dtp = larger(absdiff(rr[0], ct[sl][0]), dp);
+                    const float dt = absdiff(rr[0], ct[sl][0]);
 #pragma unroll
                     for (int v = 0; v < V; ++v) {
                         float ds = absdiff(rr[DT + v * DX], cs[sl][v][0]);
@@ -567,9 +567,11 @@ __device__ __forceinline__ void block_search(const SearchArgs &a)
                         for (int m = 1; m < DX; ++m)
                             ds = fmaxf(ds, absdiff(rr[DT + v * DX + m], cs[sl][v][m]));
                         const float er = rr[DT + V * DX + v];
-                        sP[v] += (uint32_t)__builtin_popcountll(ballot(dp < er));
-                        sTP[v] += (uint32_t)__builtin_popcountll(ballot(dtp < er));
-                        sPS[v] += (uint32_t)__builtin_popcountll(ballot(larger(dp, ds) < er));
+                        const uint64_t in_p = ballot(dp < er);
+                        sP[v] += (uint32_t)__builtin_popcountll(in_p);
+                        sTP[v] += (uint32_t)__builtin_popcountll(OUT ? in_p & ballot(dt < er) : ballot(fmaxf(dt, dp) < er));
+                        sPS[v] += (uint32_t)__builtin_popcountll(OUT ? in_p & ballot(ds < er)
+                                                                      : ballot(fmaxf(dp, ds) < er));
                     }
                 }
 #pragma unroll
